@@ -96,7 +96,9 @@ typedef enum {
  * at most eta max|A|, far below the rounding of the transforms.  A plan whose
  * tau and grid leave nothing to drop runs the same kernels with every mode kept.
  * MBO_PATH_FULL runs the same kernels with every mode kept; MBO_PATH_GENERIC the
- * general kernels (any d, any row length), which the other calls always use.
+ * general kernels (any d, any row length).  mbo_diffuse, mbo_step, mbo_energy
+ * and, for d = 2, mbo_step_vjp and mbo_diffuse_dtau run the kernels that
+ * mbo_iterate runs; the other calls always use the general ones.
  * The band-limited kernels serve d = 2 with a first axis of at least 64 points
  * (every last axis a plan accepts); other shapes run the general kernels. */
 typedef enum {
@@ -121,7 +123,7 @@ mbo_status mbo_plan_destroy(mbo_plan_t plan);
 /* Change the diffusion time; the heat-symbol tables are rebuilt. */
 mbo_status mbo_plan_set_tau(mbo_plan_t plan, double tau);
 
-/* Choose the kernels of mbo_iterate (see mbo_path; a batched plan applies the
+/* Choose the kernels of mbo_iterate and the calls that share them (see mbo_path; a batched plan applies the
  * choice to every field class).  Synchronises the plan's stream; a captured
  * iteration graph is rebuilt on the next mbo_iterate.  MBO_ERR_INVALID_ARG for an
  * unknown path. */

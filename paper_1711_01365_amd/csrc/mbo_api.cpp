@@ -115,6 +115,12 @@ struct mbo_plan_s {
     double* dsum = nullptr;     // [batch]
     void* ws_a = nullptr;       // adjoint step workspaces, one field each (lazy)
     void* ws_g = nullptr;
+    // the adjoint step's band-limited passes (lazy, sized by the kept band):
+    // transformed columns of A_{s-1}, dot-product partials
+    void* ws_spec = nullptr;
+    double* ws_dot = nullptr;
+    size_t ws_spec_bytes = 0, ws_dot_bytes = 0;
+    bool adj_ready = false;  // their dynamic-LDS limits are set
     unsigned long long* counters = nullptr;  // project: [0] nonfinite, [1] fallbacks
 
     // per-field diffusion times (fields of a batched plan): tables per field
@@ -279,6 +285,8 @@ void destroy(mbo_plan_t p)
     free_dev(p->dsum);
     free_dev(p->ws_a);
     free_dev(p->ws_g);
+    free_dev(p->ws_spec);
+    free_dev(p->ws_dot);
     free_dev(p->taus_dev);
     free_dev(p->foff_dev);
     free_dev(p->counters);
@@ -1598,15 +1606,26 @@ mbo_status energy_into(mbo_plan_t p, const void* A, double* E, const std::vector
 {
     mbo_status s = ensure_logs(p, 0);
     if (s != MBO_OK) return s;
-    HIP_TRY(p, enqueue_forward(p, A, 0, true, p->stream));
-    ColArgs h = col_args(p, p->heat);
-    h.K = 0;
-    h.slot = 0;
-    h.epart = p->epart;
-    HIP_TRY(p, run_col(p, p->heat, CM_ENERGY, h, p->stream));
+    if (p->fast) {
+        FastRowArgs r0 = fast_row_args(p);
+        r0.Ain = A;
+        r0.flags = RF_LOAD_REAL | RF_FORWARD;
+        HIP_TRY(p, run_row_fast(p, r0, p->stream));
+        FastColArgs hf = fast_col_args(p);
+        hf.epart = p->epart;
+        hf.apply = 0;
+        HIP_TRY(p, run_heat_fast(p, hf, p->stream));
+    } else {
+        HIP_TRY(p, enqueue_forward(p, A, 0, true, p->stream));
+        ColArgs h = col_args(p, p->heat);
+        h.K = 0;
+        h.slot = 0;
+        h.epart = p->epart;
+        HIP_TRY(p, run_col(p, p->heat, CM_ENERGY, h, p->stream));
+    }
     ReduceArgs ra;
     ra.epart = p->epart;
-    ra.nwg = energy_partials(p);
+    ra.nwg = p->fast ? fast_energy_partials(p) : energy_partials(p);
     ra.K = 0;
     ra.batch = (int)p->batch;
     ra.n = p->n;
@@ -1668,8 +1687,21 @@ std::vector<int> member_fields(mbo_plan_t g, int mi)
 // out = e^{tau Delta} in (one diffusion step), enqueued on st.
 hipError_t enqueue_diffuse(mbo_plan_t p, const void* in, void* out, hipStream_t st)
 {
-    hipError_t e = enqueue_forward(p, in, 0, true, st);
-    if (e != hipSuccess) return e;
+    hipError_t e;
+    if (p->fast) {
+        // the passes of mbo_iterate with the projection left out
+        FastRowArgs r0 = fast_row_args(p);
+        r0.Ain = in;
+        r0.flags = RF_LOAD_REAL | RF_FORWARD;
+        if ((e = run_row_fast(p, r0, st)) != hipSuccess) return e;
+        FastColArgs hf = fast_col_args(p);
+        if ((e = run_heat_fast(p, hf, st)) != hipSuccess) return e;
+        FastRowArgs r1 = fast_row_args(p);
+        r1.Aout = out;
+        r1.flags = RF_INVERSE | RF_STORE_REAL;
+        return run_row_fast(p, r1, st);
+    }
+    if ((e = enqueue_forward(p, in, 0, true, st)) != hipSuccess) return e;
     ColArgs h = col_args(p, p->heat);
     if ((e = run_col(p, p->heat, CM_HEAT, h, st)) != hipSuccess) return e;
     if (p->d == 3) {
@@ -1680,6 +1712,148 @@ hipError_t enqueue_diffuse(mbo_plan_t p, const void* in, void* out, hipStream_t 
     r.Aout = out;
     r.flags = RF_INVERSE | RF_STORE_REAL;
     return run_row(p, r, st);
+}
+
+// A lazily allocated workspace of at least `bytes`.
+template <typename T>
+mbo_status grow(mbo_plan_t p, T*& ptr, size_t& have, size_t bytes)
+{
+    if (ptr && have >= bytes) return MBO_OK;
+    free_dev(ptr);
+    have = 0;
+    HIP_TRY(p, hipMalloc((void**)&ptr, bytes));
+    have = bytes;
+    return MBO_OK;
+}
+
+// The adjoint's band-limited column passes (2-D): launch grid, partials per
+// field, workspaces and dynamic-LDS limits, and one pass.
+dim3 adj_heat_grid(mbo_plan_t p)
+{
+    const int tx = heat_fast_adj_tile(ilog2((int)p->N[0]));
+    return dim3((unsigned)((int64_t)p->PL * (p->band_W / tx)), (unsigned)p->batch);
+}
+
+int adj_partials(mbo_plan_t p)
+{
+    const int tx = heat_fast_adj_tile(ilog2((int)p->N[0]));
+    return (int)adj_heat_grid(p).x * (tx * (int)(p->N[0] / 8) / 64);
+}
+
+mbo_status ensure_adjoint(mbo_plan_t p, bool dot)
+{
+    mbo_status s;
+    if (dot && ((s = grow(p, p->ws_spec, p->ws_spec_bytes,
+                          (size_t)p->batch * p->PL * p->band_W * (size_t)p->N[0] * 2 * p->esz)) != MBO_OK ||
+                (s = grow(p, p->ws_dot, p->ws_dot_bytes,
+                          (size_t)p->batch * adj_partials(p) * sizeof(double))) != MBO_OK))
+        return s;
+    if (p->adj_ready) return MBO_OK;
+    FastRowArgs r;
+    std::memset(&r, 0, sizeof r);
+    if (row_fast_vjp_served(p->pk, p->n))
+        (void)launch_row_fast_vjp(p->pk, p->n, ilog2((int)p->N[1]), r, dim3(1), nullptr, true);
+    FastColArgs h;
+    std::memset(&h, 0, sizeof h);
+    (void)launch_heat_fast_adj(p->pk, ilog2((int)p->N[0]), HF_SAVE, h, dim3(1), nullptr, true);
+    (void)hipGetLastError();
+    p->adj_ready = true;
+    return MBO_OK;
+}
+
+hipError_t run_heat_adj(mbo_plan_t p, int mode, bool spec, bool apply, hipStream_t st)
+{
+    FastColArgs h = fast_col_args(p);
+    h.tiles = p->band_W / heat_fast_adj_tile(ilog2((int)p->N[0]));
+    h.nwg = adj_partials(p);
+    h.N1 = (int)p->N[1];
+    h.band = p->band_c;
+    h.spec = spec ? p->ws_spec : nullptr;
+    h.dpart = p->ws_dot;
+    h.apply = apply ? 1 : 0;
+    return launch_heat_fast_adj(p->pk, ilog2((int)p->N[0]), mode, h, adj_heat_grid(p), st);
+}
+
+// mbo_step_vjp of a 2-D plan through the band-limited passes.  The column pass
+// of A_{s-1} leaves the transformed columns in ws_spec, the row pass turns
+// e^{tau Delta} A_{s-1} into the projection's cotangent G~ without leaving LDS
+// (n = 2, 3; n = 4 through vjp_kernel), and the column pass of G~ takes
+// <G~, d/dtau e^{tau Delta} A_{s-1}> from both spectra by Parseval (the heat
+// operator is diagonal there): six launches, where diffusing A_{s-1} twice and
+// G~ once by the general passes took eleven (n = 3, 256^2 in float: 64 -> 36 us
+// of kernels).
+mbo_status step_vjp_fast(mbo_plan_t p, const void* A_prev, void* G, double* dtau)
+{
+    hipStream_t st = p->stream;
+    const bool fused = row_fast_vjp_served(p->pk, p->n);
+    const mbo_status s = ensure_adjoint(p, dtau != nullptr);
+    if (s != MBO_OK) return s;
+    const size_t fbytes = (size_t)p->batch * p->n * p->n * (size_t)p->npts * p->esz;
+    if (!fused && !p->ws_a) HIP_TRY(p, hipMalloc(&p->ws_a, fbytes));
+    if (!fused && !p->ws_g) HIP_TRY(p, hipMalloc(&p->ws_g, fbytes));
+    auto heat = [&](int mode) {
+        return dtau ? run_heat_adj(p, mode, true, true, st) : run_heat_fast(p, fast_col_args(p), st);
+    };
+    FastRowArgs r0 = fast_row_args(p);
+    r0.Ain = A_prev;
+    r0.flags = RF_LOAD_REAL | RF_FORWARD;
+    HIP_TRY(p, run_row_fast(p, r0, st));
+    HIP_TRY(p, heat(HF_SAVE));
+    const int fb = p->prec == MBO_F32_F64FALLBACK ? RF_FALLBACK : 0;
+    FastRowArgs r1 = fast_row_args(p);
+    if (fused) {
+        r1.Gin = G;
+        r1.flags = RF_INVERSE | RF_FORWARD | fb;
+        HIP_TRY(p, launch_row_fast_vjp(p->pk, p->n, ilog2((int)p->N[1]), r1,
+                                       dim3((unsigned)fast_row_groups(p), (unsigned)p->batch), st));
+    } else {
+        r1.Aout = p->ws_a;
+        r1.flags = RF_INVERSE | RF_STORE_REAL;
+        HIP_TRY(p, run_row_fast(p, r1, st));
+        VjpArgs v;
+        v.npts = p->npts;
+        v.A = p->ws_a;
+        v.G = G;
+        v.GA = p->ws_g;
+        v.nonfinite = p->counters;
+        v.fallback = fb != 0;
+        v.sigma_fb = p->sigma_fb;
+        HIP_TRY(p, launch_vjp(p->pk, p->n, v, (int)p->batch, st));
+        r0.Ain = p->ws_g;
+        HIP_TRY(p, run_row_fast(p, r0, st));
+    }
+    HIP_TRY(p, heat(HF_DOT));
+    FastRowArgs r2 = fast_row_args(p);
+    r2.Aout = G;
+    r2.flags = RF_INVERSE | RF_STORE_REAL;
+    HIP_TRY(p, run_row_fast(p, r2, st));
+    if (dtau) HIP_TRY(p, launch_sum_rows(p->ws_dot, adj_partials(p), (int)p->batch, dtau, st, true));
+    return MBO_OK;
+}
+
+// out (nullable) = d/dtau e^{tau Delta} A and, with G, dot[b] = <G_b, out_b>, by
+// the same passes (2-D): the sums are those of step_vjp_fast.
+mbo_status diffuse_dtau_fast(mbo_plan_t p, const void* A, void* out, const void* G, double* dot, hipStream_t st)
+{
+    const mbo_status s = ensure_adjoint(p, G != nullptr);
+    if (s != MBO_OK) return s;
+    FastRowArgs r0 = fast_row_args(p);
+    r0.Ain = A;
+    r0.flags = RF_LOAD_REAL | RF_FORWARD;
+    HIP_TRY(p, run_row_fast(p, r0, st));
+    HIP_TRY(p, run_heat_adj(p, HF_DTAU, G != nullptr, out != nullptr, st));
+    if (out) {
+        FastRowArgs r1 = fast_row_args(p);
+        r1.Aout = out;
+        r1.flags = RF_INVERSE | RF_STORE_REAL;
+        HIP_TRY(p, run_row_fast(p, r1, st));
+    }
+    if (!G) return MBO_OK;
+    r0.Ain = G;
+    HIP_TRY(p, run_row_fast(p, r0, st));
+    HIP_TRY(p, run_heat_adj(p, HF_DOT, true, false, st));
+    HIP_TRY(p, launch_sum_rows(p->ws_dot, adj_partials(p), (int)p->batch, dot, st));
+    return MBO_OK;
 }
 
 // dot[b] += <G_b, d/dtau e^{tau Delta} A_b> (device accumulator), enqueued on st.
@@ -2468,17 +2642,7 @@ mbo_status mbo_diffuse(mbo_plan_t p, const void* A_in, void* A_out)
         }
         return MBO_OK;
     }
-    HIP_TRY(p, enqueue_forward(p, A_in, 0, true, p->stream));
-    ColArgs h = col_args(p, p->heat);
-    HIP_TRY(p, run_col(p, p->heat, CM_HEAT, h, p->stream));
-    if (p->d == 3) {
-        ColArgs y = col_args(p, p->ypass);
-        HIP_TRY(p, run_col(p, p->ypass, CM_INVERSE, y, p->stream));
-    }
-    RowArgs r = row_args(p);
-    r.Aout = A_out;
-    r.flags = RF_INVERSE | RF_STORE_REAL;
-    HIP_TRY(p, run_row(p, r, p->stream));
+    HIP_TRY(p, enqueue_diffuse(p, A_in, A_out, p->stream));
     return MBO_OK;
 }
 
@@ -2541,21 +2705,27 @@ mbo_status mbo_diffuse_dtau(mbo_plan_t p, const void* A, void* out, const void* 
     if (!out && !want_dot) return fail(p, MBO_ERR_INVALID_ARG, "neither out nor (G, dot) given");
     if ((G == nullptr) != (dot == nullptr)) return fail(p, MBO_ERR_INVALID_ARG, "G and dot go together");
     HIP_TRY(p, hipSetDevice(p->device));
-    HIP_TRY(p, enqueue_forward(p, A, 0, true, p->stream));
-    ColArgs h = col_args(p, p->heat);
-    HIP_TRY(p, run_col(p, p->heat, CM_DTAU, h, p->stream));
-    if (p->d == 3) {
-        ColArgs y = col_args(p, p->ypass);
-        HIP_TRY(p, run_col(p, p->ypass, CM_INVERSE, y, p->stream));
+    if (p->fast && p->d == 2 && !(want_dot && out == G)) {  // out is written before G is read
+        const mbo_status s = diffuse_dtau_fast(p, A, out, want_dot ? G : nullptr, p->dsum, p->stream);
+        if (s != MBO_OK) return s;
+    } else {
+        HIP_TRY(p, enqueue_forward(p, A, 0, true, p->stream));
+        ColArgs h = col_args(p, p->heat);
+        HIP_TRY(p, run_col(p, p->heat, CM_DTAU, h, p->stream));
+        if (p->d == 3) {
+            ColArgs y = col_args(p, p->ypass);
+            HIP_TRY(p, run_col(p, p->ypass, CM_INVERSE, y, p->stream));
+        }
+        RowArgs r = row_args(p);
+        r.Aout = out;
+        r.flags = RF_INVERSE | (out ? RF_STORE_REAL : 0) | (want_dot ? RF_DOT : 0);
+        r.Gdot = G;
+        r.dpart = p->dpart;
+        HIP_TRY(p, run_row(p, r, p->stream));
+        if (want_dot)
+            HIP_TRY(p, launch_sum_rows(p->dpart, (int64_t)p->row_grid.x, (int)p->batch, p->dsum, p->stream));
     }
-    RowArgs r = row_args(p);
-    r.Aout = out;
-    r.flags = RF_INVERSE | (out ? RF_STORE_REAL : 0) | (want_dot ? RF_DOT : 0);
-    r.Gdot = G;
-    r.dpart = p->dpart;
-    HIP_TRY(p, run_row(p, r, p->stream));
     if (want_dot) {
-        HIP_TRY(p, launch_sum_rows(p->dpart, (int64_t)p->row_grid.x, (int)p->batch, p->dsum, p->stream));
         HIP_TRY(p, hipMemcpyAsync(dot, p->dsum, (size_t)p->batch * sizeof(double), hipMemcpyDeviceToHost,
                                   p->stream));
         HIP_TRY(p, hipStreamSynchronize(p->stream));
@@ -2630,6 +2800,7 @@ mbo_status mbo_step_vjp(mbo_plan_t p, const void* A_prev, void* G, double* dtau)
     if (!A_prev || !G) return fail(p, MBO_ERR_INVALID_ARG, "A_prev / G is NULL");
     if (A_prev == (const void*)G) return fail(p, MBO_ERR_INVALID_ARG, "G must not alias A_prev");
     HIP_TRY(p, hipSetDevice(p->device));
+    if (p->fast && p->d == 2) return step_vjp_fast(p, A_prev, G, dtau);
     const size_t fbytes = (size_t)p->batch * p->n * p->n * (size_t)p->npts * p->esz;
     if (!p->ws_a) HIP_TRY(p, hipMalloc(&p->ws_a, fbytes));
     if (!p->ws_g) HIP_TRY(p, hipMalloc(&p->ws_g, fbytes));

@@ -947,6 +947,162 @@ __device__ __forceinline__ T polar_vjp(const T* a, const T* g, T* ga)
     return smin;
 }
 
+// Vector-Jacobian product of the projection from the polar factor itself
+// (n = 2, 3), without singular vectors: with Q = U V^t and H = Q^t a =
+// V Sigma V^t, ga = Q Y, where the skew Y = V K V^t solves H Y + Y H =
+// Q^t g - g^t Q (the formula of polar_vjp in the basis V).
+
+// n = 3: the three entries of Y from the symmetric system whose eigenvalues are
+// the sums sigma_i + sigma_j, by L D L^t (positive definite: sigma_2 > 0).
+template <typename T>
+__device__ __forceinline__ void polar_vjp3_solve(const T* a, const T* q, const T* g, T* ga)
+{
+    T h[6], b[3];  // H: 00 01 02 11 12 22; Q^t g - g^t Q: 01 02 12
+#pragma unroll
+    for (int k = 0; k < 6; ++k) h[k] = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b[k] = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const T q0 = q[3 * i], q1 = q[3 * i + 1], q2 = q[3 * i + 2];
+        const T a0 = a[3 * i], a1 = a[3 * i + 1], a2 = a[3 * i + 2];
+        const T g0 = g[3 * i], g1 = g[3 * i + 1], g2 = g[3 * i + 2];
+        h[0] += q0 * a0; h[3] += q1 * a1; h[5] += q2 * a2;
+        h[1] += (T)0.5 * (q0 * a1 + q1 * a0);
+        h[2] += (T)0.5 * (q0 * a2 + q2 * a0);
+        h[4] += (T)0.5 * (q1 * a2 + q2 * a1);
+        b[0] += q0 * g1 - q1 * g0;
+        b[1] += q0 * g2 - q2 * g0;
+        b[2] += q1 * g2 - q2 * g1;
+    }
+    // rows (01), (02), (12): [h00+h11, h12, -h02; ., h00+h22, h01; ., ., h11+h22]
+    const T i0 = num<T>::rcp(h[0] + h[3]);
+    const T l1 = h[4] * i0, l2 = -h[2] * i0;
+    const T i1 = num<T>::rcp(h[0] + h[5] - l1 * h[4]);
+    const T m = h[1] + l1 * h[2];
+    const T l3 = m * i1;
+    const T i2 = num<T>::rcp(h[3] + h[5] + l2 * h[2] - l3 * m);
+    const T y0 = b[0], y1 = b[1] - l1 * y0, y2 = b[2] - l2 * y0 - l3 * y1;
+    const T c2 = y2 * i2, c1 = y1 * i1 - l3 * c2, c0 = y0 * i0 - l1 * c1 - l2 * c2;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        ga[3 * i] = -(q[3 * i + 1] * c0 + q[3 * i + 2] * c1);
+        ga[3 * i + 1] = q[3 * i] * c0 - q[3 * i + 2] * c2;
+        ga[3 * i + 2] = q[3 * i] * c1 + q[3 * i + 1] * c2;
+    }
+}
+
+// K of polar_vjp (three entries for n = 3) and ga from the SVD in precision
+// T, entry by entry as it is formed: the registers of the full product forms
+// would not fit beside a row pass.  Entry k of the cotangent is G[k gs].
+template <typename T, typename Tio>
+__device__ __forceinline__ T vjp3_jacobi(const Tio* a, const Tio* G, int64_t gs, Tio* ga)
+{
+    const int ex = scale_exponent<Tio, 3>(a);
+    T U[3][3], V[3][3], sig[3], smin;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            U[i][j] = ldexp((T)a[i * 3 + j], -ex);
+            V[i][j] = (i == j) ? (T)1 : (T)0;
+        }
+    jacobi_sweeps<T, 3>(U, V);
+    int ds;
+    Tio q[9];
+    jacobi_finish<T, 3, Tio>(U, V, ex, q, ds, smin, sig);
+    if (!(sig[0] > (T)0) && !(sig[1] > (T)0) && !(sig[2] > (T)0)) {  // zero matrix
+#pragma unroll
+        for (int k = 0; k < 9; ++k) ga[k] = 0;
+        return smin;
+    }
+    T k[3];
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+        const int i = e == 2 ? 1 : 0, j = e == 0 ? 1 : 2;
+        T m = 0;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                m += (T)G[(3 * r + c) * gs] * (U[r][i] * V[c][j] - U[r][j] * V[c][i]);
+        const T den = sig[i] + sig[j];
+        k[e] = den > (T)0 ? m / den : (T)0;
+    }
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            ga[3 * r + c] = (Tio)(k[0] * (U[r][0] * V[c][1] - U[r][1] * V[c][0]) +
+                                  k[1] * (U[r][0] * V[c][2] - U[r][2] * V[c][0]) +
+                                  k[2] * (U[r][1] * V[c][2] - U[r][2] * V[c][1]));
+    return smin;
+}
+
+// polar_vjp of an n = 3 point, with the double fallback of float plans.
+template <typename T>
+__device__ __forceinline__ void polar_vjp3_fb(const T* a, const T* G, int64_t gs, T* ga, bool fallback,
+                                              double sigma_fb)
+{
+    const T smin = vjp3_jacobi<T, T>(a, G, gs, ga);
+    if constexpr (sizeof(T) == 4) {
+        if (fallback && (double)smin < sigma_fb) (void)vjp3_jacobi<double, float>(a, G, gs, ga);
+    }
+}
+
+// n = 2: Q in closed form (polar2), Y has one entry, (Q^t g - g^t Q)_01 /
+// (sigma_1 + sigma_2).  As in jacobi_finish a singular value of at most
+// n eps sigma_max counts as zero (the rotation is taken), and the zero matrix
+// gives 0 (no pair has a positive denominator).  Returns the smallest singular
+// value.
+template <typename T>
+__device__ __forceinline__ T polar_vjp2(const T* a_in, const T* g, T* ga)
+{
+    const int ex = scale_exponent<T, 2>(a_in);
+    T a[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] = ldexp(a_in[k], -ex);
+    const T det = a[0] * a[3] - a[1] * a[2];
+    const T f2 = a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
+    const T ad = det < (T)0 ? -det : det;
+    const T lo = f2 - 2 * ad;
+    const T smax = (T)0.5 * (num<T>::sqrt_(f2 + 2 * ad) + num<T>::sqrt_(lo > (T)0 ? lo : (T)0));
+    const T smin = smax > (T)0 ? ad * num<T>::rcp(smax) : (T)0;
+    const bool rot = det >= (T)0 || smin <= (T)2 * num<T>::eps * smax;
+    const T p = rot ? a[0] + a[3] : a[0] - a[3];
+    const T s = rot ? a[2] - a[1] : a[1] + a[2];
+    const T rr = p * p + s * s;  // (sigma_1 + sigma_2)^2
+    const T inv = rr > (T)0 ? num<T>::rsq(rr) : (T)0;
+    const T c = p * inv, sn = s * inv;
+    const T q1 = rot ? -sn : sn, q3 = rot ? c : -c;
+    const T b = c * g[1] + sn * g[3] - q1 * g[0] - q3 * g[2];
+    const T y = ldexp(b * inv, -ex);
+    ga[0] = -q1 * y;
+    ga[1] = c * y;
+    ga[2] = -q3 * y;
+    ga[3] = sn * y;
+    return ldexp(smin, ex);
+}
+
+template <typename T>
+__device__ __forceinline__ void polar_vjp2_fb(const T* a, const T* g, T* ga, bool fallback, double sigma_fb)
+{
+    const T smin = polar_vjp2<T>(a, g, ga);
+    if constexpr (sizeof(T) == 4) {
+        if (fallback && (double)smin < sigma_fb) {
+            double ad[4], gd[4], od[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ad[k] = (double)a[k];
+                gd[k] = (double)g[k];
+            }
+            (void)polar_vjp2<double>(ad, gd, od);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) ga[k] = (T)od[k];
+        }
+    }
+}
+
 // Cofactor matrix of a row-major 3x3 matrix (cof(X) = det(X) X^{-T}).
 template <typename T>
 __device__ __forceinline__ void cofactor3(const T* x, T* c)
@@ -1175,7 +1331,6 @@ template <typename T, int n>
 __device__ __forceinline__ bool project_point_fb(const T* a, T* q, int& dsign, bool fallback,
                                                  double sigma_fb)
 {
-    constexpr int NN = n * n;
     if constexpr (sizeof(T) == 4 && n >= 3) {
         // well-conditioned points (sigma_min >= sigma_fb): Newton, no fallback
         if (polar_newton<float, n>(a, q, dsign, (float)sigma_fb)) return false;
@@ -1215,6 +1370,48 @@ __device__ __forceinline__ bool all_finite(const T* a)
 #pragma unroll
     for (int i = 0; i < m; ++i) ok = ok && (a[i] - a[i] == (T)0);
     return ok;
+}
+
+// The projection's vector-Jacobian product at a point, in the plan's precision
+// T with the double fallback of float plans (g: the cotangent, also at G[k gs]).
+// n = 2 in closed form; n = 3 from the Newton polar factor where sigma_min is
+// certainly not small, else from the SVD; n = 4 from the SVD.  n = 3 against
+// the SVD for every point, 256^2 in float: 9.5 -> 5 us per vjp_kernel launch.
+template <typename T, int n>
+__device__ __forceinline__ bool polar_vjp_newton3(const T* a, const T* g, T* ga, double sigma_fb)
+{
+    static_assert(n == 3, "3x3 matrices");
+    T q[9];
+    int ds;
+    if (!polar_newton<T, 3>(a, q, ds, sizeof(T) == 4 ? (T)sigma_fb : (T)kNewtonMinSigmaF64)) return false;
+    polar_vjp3_solve<T>(a, q, g, ga);
+    return true;
+}
+
+template <typename T, int n>
+__device__ __forceinline__ void polar_vjp_fb(const T* a, const T* g, T* ga, const T* G, int64_t gs, bool fallback,
+                                             double sigma_fb)
+{
+    if constexpr (n == 2) {
+        polar_vjp2_fb<T>(a, g, ga, fallback, sigma_fb);
+    } else if constexpr (n == 3) {
+        if (!polar_vjp_newton3<T, 3>(a, g, ga, sigma_fb)) polar_vjp3_fb<T>(a, G, gs, ga, fallback, sigma_fb);
+    } else {
+        const T smin = polar_vjp<T, n>(a, g, ga);
+        if constexpr (sizeof(T) == 4) {
+            if (fallback && (double)smin < sigma_fb) {
+                double ad[n * n], gd[n * n], od[n * n];
+#pragma unroll
+                for (int k = 0; k < n * n; ++k) {
+                    ad[k] = a[k];
+                    gd[k] = g[k];
+                }
+                (void)polar_vjp<double, n>(ad, gd, od);
+#pragma unroll
+                for (int k = 0; k < n * n; ++k) ga[k] = (T)od[k];
+            }
+        }
+    }
 }
 
 }  // namespace mbo

@@ -154,9 +154,13 @@ struct RowFastShape {
     static constexpr int WAVES = WAVE_LINE ? 4 : (THREADS + 255) / 256;
 };
 
-template <typename T, int n, int LOG2L, bool PM>
-__global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
-    row_fast(const FastRowArgs a)
+// What the points of a row pass go through between the two line transforms:
+// FM_ITER the steps that the flags name (projection, load, store), FM_VJP the
+// projection's vector-Jacobian product with the cotangent field a.Gin.
+enum { FM_ITER = 0, FM_VJP = 1 };
+
+template <typename T, int n, int LOG2L, bool PM, int MODE>
+__device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
 {
     typedef RowFastShape<T, n, LOG2L> S;
     constexpr int NN = S::NN, PL = S::PL, L = S::L, Tn = S::Tn, RPW = S::RPW, LP = S::LP;
@@ -166,7 +170,7 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFast
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* lr = reinterpret_cast<T*>(smem_raw);
     T* li = lr + (size_t)S::LINES * LP;
-    __shared__ unsigned short fq[(HELPER || S::DEFER4) ? S::P : 1];
+    __shared__ unsigned short fq[(HELPER || S::DEFER4 || (MODE == FM_VJP && n == 3)) ? S::P : 1];
     __shared__ int fq_n, fq_claim;
     // rows of at most 512 points (every wave holds points): the last wave's
     // Newton points, handed to the other waves when it runs the queue
@@ -370,7 +374,61 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFast
     }
     __syncthreads();
 
-    if (flags & RF_PROJECT) {
+    if constexpr (MODE == FM_VJP) {
+        // Points certainly well conditioned (n = 3) or in closed form (n = 2):
+        // polar_vjp_newton3 / polar_vjp2_fb; the others (n = 3) are queued for the
+        // first wave done, which runs Jacobi (in double below sigma_fb).
+        const T* G = reinterpret_cast<const T*>(a.Gin) + field_base(a.foff, b, NN * npts);
+        auto put = [&](T* lrq, T* liq, const T (&ov)[NN]) {
+#pragma unroll
+            for (int k = 0; k < NN; ++k) {
+                if (k & 1) liq[(k >> 1) * LP] = ov[k];
+                else lrq[(k >> 1) * LP] = ov[k];
+            }
+            if (NN & 1) liq[(NN >> 1) * LP] = (T)0;
+        };
+#pragma unroll 1
+        for (int pp = 0; pp < PPT; ++pp) {
+            int64_t xp;
+            T *lrq, *liq;
+            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+                T av[NN], gv[NN], ov[NN];
+#pragma unroll
+                for (int k = 0; k < NN; ++k) gv[k] = G[(int64_t)k * npts + xp];
+                load_point(lrq, liq, av);
+                if constexpr (n == 2) {
+                    polar_vjp2_fb<T>(av, gv, ov, fallback, a.sigma_fb);
+                    put(lrq, liq, ov);
+                } else {
+                    if (polar_vjp_newton3<T, 3>(av, gv, ov, a.sigma_fb)) {
+                        put(lrq, liq, ov);
+                    } else {
+                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * 512 + tid);
+                    }
+                }
+            }
+        }
+        if constexpr (n == 3) {
+            __syncthreads();
+            if (fq_n > 0) {  // uniform
+                if (tid < 64) {
+                    __builtin_amdgcn_s_setprio(3);
+#pragma unroll 1
+                    for (int qi = tid; qi < fq_n; qi += 64) {
+                        int64_t xp;
+                        T *lrq, *liq;
+                        (void)point_of(fq[qi], xp, lrq, liq);
+                        T av[NN], ov[NN];
+                        load_point(lrq, liq, av);
+                        polar_vjp3_fb<T>(av, G + xp, npts, ov, fallback, a.sigma_fb);
+                        put(lrq, liq, ov);
+                    }
+                    __builtin_amdgcn_s_setprio(0);
+                }
+            }
+        }
+        __syncthreads();
+    } else if (flags & RF_PROJECT) {
         if constexpr (HELPER) {
             // which points are certainly well conditioned: the Newton
             // iteration; the others are queued
@@ -538,6 +596,18 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFast
             }
         }
         __syncthreads();
+    } else if ((flags & (RF_INVERSE | RF_STORE_REAL)) == (RF_INVERSE | RF_STORE_REAL)) {
+        // the transformed values as they are (a diffusion step without projection)
+#pragma unroll 1
+        for (int pp = 0; pp < PPT; ++pp) {
+            int64_t xp;
+            T *lrq, *liq;
+            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+#pragma unroll
+                for (int k = 0; k < NN; ++k)
+                    Aout[(int64_t)k * npts + xp] = (k & 1) ? liq[(k >> 1) * LP] : lrq[(k >> 1) * LP];
+            }
+        }
     }
 
     // ---- phase 3: forward FFT of the lines, store the kept modes
@@ -625,6 +695,20 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFast
     }
 }
 
+template <typename T, int n, int LOG2L, bool PM>
+__global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
+    row_fast(const FastRowArgs a)
+{
+    row_fast_body<T, n, LOG2L, PM, FM_ITER>(a);
+}
+
+template <typename T, int n, int LOG2L>
+__global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
+    row_fast_vjp(const FastRowArgs a)
+{
+    row_fast_body<T, n, LOG2L, false, FM_VJP>(a);
+}
+
 // ---------------------------------------------------------------------------
 // Column pass over the stored columns
 // ---------------------------------------------------------------------------
@@ -640,8 +724,8 @@ struct HeatFastShape {
     static constexpr size_t LDS = LINES + (TW_LDS ? TW_BYTES : 0);
 };
 
-template <typename T, int LOG2L, int TX>
-__global__ void __launch_bounds__(TX * (1 << LOG2L) / 8) heat_fast(const FastColArgs a)
+template <typename T, int LOG2L, int TX, int MODE>
+__device__ __forceinline__ void heat_fast_body(const FastColArgs& a)
 {
     typedef typename cx<T>::type C;
     typedef FftShape<LOG2L> F;
@@ -711,6 +795,40 @@ __global__ void __launch_bounds__(TX * (1 << LOG2L) / 8) heat_fast(const FastCol
         if ((tid & 63) == 0)
             a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + wg * (blockDim.x >> 6) + (tid >> 6)] = s;
     }
+    if constexpr (MODE != HF_PLAIN) {
+        // a thread's eight values side by side: the two passes run the same
+        // launch shape, so the layout of a.spec is their own
+        C* S = reinterpret_cast<C*>(a.spec) + ((size_t)b * gridDim.x + wg) * (size_t)(TX * L) + tid;
+        if (MODE == HF_SAVE || (MODE == HF_DTAU && a.spec)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                C v;
+                v.x = r[0][e];
+                v.y = im[0][e];
+                S[e * (TX * Tn)] = v;
+            }
+        }
+        if constexpr (MODE == HF_DOT || MODE == HF_DTAU) {
+            const T kx = (T)(a.W == a.N1 ? (2 * col < a.N1 ? col : col - a.N1) : (col <= a.band ? col : col - a.W));
+            double acc = 0.0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int m = t + e * Tn;
+                const T ky = (T)(2 * m < L ? m : m - L);
+                const T mu = lam[e] * ((T)-39.478417604357434475337963999505 * (kx * kx + ky * ky));  // -4 pi^2 |k|^2
+                if constexpr (MODE == HF_DTAU) {
+                    lam[e] = mu;
+                } else {
+                    const C v = S[e * (TX * Tn)];
+                    acc += (double)mu * ((double)r[0][e] * (double)v.x + (double)im[0][e] * (double)v.y);
+                }
+            }
+            if constexpr (MODE == HF_DOT) {
+                const double s = wave_sum(acc);
+                if ((tid & 63) == 0) a.dpart[(int64_t)b * a.nwg + wg * (blockDim.x >> 6) + (tid >> 6)] = s;
+            }
+        }
+    }
     if (!a.apply) return;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -725,6 +843,18 @@ __global__ void __launch_bounds__(TX * (1 << LOG2L) / 8) heat_fast(const FastCol
         v.y = im[0][e];
         Zc[(int64_t)(t + e * Tn) * a.W] = v;
     }
+}
+
+template <typename T, int LOG2L, int TX>
+__global__ void __launch_bounds__(TX * (1 << LOG2L) / 8) heat_fast(const FastColArgs a)
+{
+    heat_fast_body<T, LOG2L, TX, HF_PLAIN>(a);
+}
+
+template <typename T, int LOG2L, int TX, int MODE>
+__global__ void __launch_bounds__(TX * (1 << LOG2L) / 8) heat_fast_adj(const FastColArgs a)
+{
+    heat_fast_body<T, LOG2L, TX, MODE>(a);
 }
 
 // ---------------------------------------------------------------------------

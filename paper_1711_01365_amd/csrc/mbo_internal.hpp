@@ -383,6 +383,7 @@ struct FastRowArgs {
     const int64_t* foff;     // nullable field offsets of the real fields
     unsigned long long* cnt_part;  // nullable: packed flips | fallbacks << 21 | non-finite << 42
                                    // per workgroup [batch][K][gridDim.x]
+    const void* Gin;         // row_fast_vjp: cotangent field [batch][n*n][npts]
 };
 
 struct FastColArgs {
@@ -411,12 +412,32 @@ struct FastColArgs {
     const void* tw_y;
     const void* lam_y;
     int64_t lam_y_stride;
+    // the adjoint step's passes (heat_fast_adj)
+    int N1, band;            // last axis length and kept half-width
+    void* spec;              // transformed columns [batch][gridDim.x][8][threads] complex
+    double* dpart;           // [batch][nwg]
 };
+
+// What a column pass does with the transformed columns besides the heat step
+// (the adjoint's calls): HF_SAVE stores them in a.spec, HF_DOT adds up
+// Re(conj(column) a.spec) (-4 pi^2 |k|^2) symbol, one double per wave, in
+// a.dpart [batch][nwg]; HF_DTAU multiplies by -4 pi^2 |k|^2 symbol in place of
+// the symbol, and stores the columns as HF_SAVE does when a.spec is set.
+enum { HF_PLAIN = 0, HF_SAVE = 1, HF_DOT = 2, HF_DTAU = 3 };
 
 hipError_t launch_row_fast(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
                            bool prepare = false, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t launch_heat_fast(int prec, int log2L, int TX, const FastColArgs& a, dim3 grid, hipStream_t st,
                             bool prepare = false, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// The adjoint step's passes: row_fast_vjp (row_fast_vjp_served says where it
+// exists) and heat_fast_adj (mode HF_SAVE, HF_DOT or HF_DTAU,
+// tiles of heat_fast_adj_tile columns).
+bool row_fast_vjp_served(int prec, int n);
+hipError_t launch_row_fast_vjp(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
+                               bool prepare = false);
+hipError_t launch_heat_fast_adj(int prec, int log2L, int mode, const FastColArgs& a, dim3 grid, hipStream_t st,
+                                bool prepare = false);
+int heat_fast_adj_tile(int log2L);
 // the 3-D plane pass (float): one workgroup per (packed plane, stored x mode)
 hipError_t launch_plane_fast(int log2Y, int log2Z, const FastColArgs& a, dim3 grid, hipStream_t st,
                              bool prepare = false, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);

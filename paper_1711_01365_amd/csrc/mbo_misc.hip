@@ -63,20 +63,7 @@ __global__ void __launch_bounds__(256) vjp_kernel(const VjpArgs a)
         if constexpr (n == 1) {
             ov[0] = 0;  // sign thresholding is locally constant
         } else {
-            const T smin = polar_vjp<T, n>(av, gv, ov);
-            if constexpr (sizeof(T) == 4) {
-                if (a.fallback && (double)smin < a.sigma_fb) {
-                    double ad[NN], gd[NN], od[NN];
-#pragma unroll
-                    for (int k = 0; k < NN; ++k) {
-                        ad[k] = av[k];
-                        gd[k] = gv[k];
-                    }
-                    (void)polar_vjp<double, n>(ad, gd, od);
-#pragma unroll
-                    for (int k = 0; k < NN; ++k) ov[k] = (T)od[k];
-                }
-            }
+            polar_vjp_fb<T, n>(av, gv, ov, G + p, a.npts, a.fallback != 0, a.sigma_fb);
         }
 #pragma unroll
         for (int k = 0; k < NN; ++k) GA[(int64_t)k * a.npts + p] = ov[k];
