@@ -195,6 +195,13 @@ struct mbo_plan_s {
     unsigned* vtcnt = nullptr;    // [batch][chunks]
     long long* vnplus = nullptr;  // [batch]
     unsigned* vdone = nullptr;    // [batch] finished-workgroup counters of the tie count
+    // the band-limited volume-preserving iteration: second set of row spectra
+    // (vz_bytes) and, in the same allocation, the selection's lists
+    void* vz = nullptr;
+    size_t vz_bytes = 0;
+    unsigned long long* vkey = nullptr;  // [batch][npts] listed keys
+    unsigned* vcnt = nullptr;            // [batch] listed points
+    unsigned* vidx = nullptr;            // [batch][npts] their indices
     // relaxed flows: cached graph of mbo_relaxed_flow, penalty partials
     hipGraphExec_t rexec = nullptr;
     void* rg_A = nullptr;
@@ -303,6 +310,7 @@ void destroy(mbo_plan_t p)
     free_dev(p->vtcnt);
     free_dev(p->vnplus);
     free_dev(p->vdone);
+    free_dev(p->vz);
     free_dev(p->pen);
     free_dev(p->pen_sum);
     for (hipEvent_t e : p->ev) (void)hipEventDestroy(e);
@@ -1011,7 +1019,7 @@ hipError_t enqueue_iterate_fast(mbo_plan_t p, void* A, int K, double tol, bool w
         hipEvent_t re = p->timing ? p->ev[4 * (s - 1) + 1] : nullptr;
         if ((e = run_row_fast(p, r, st, rs, re)) != hipSuccess) return e;
     }
-    if ((e = launch_sum_counts(p->cnt_part, fast_row_groups(p), K, (int)p->batch, p->flips, p->fallbacks,
+    if ((e = launch_sum_counts(p->cnt_part, fast_row_groups(p), K, 0, (int)p->batch, p->flips, p->fallbacks,
                                p->nonfinite, st)) != hipSuccess)
         return e;
     if (!want_energy) return hipSuccess;
@@ -1186,10 +1194,137 @@ hipError_t enqueue_volume_step(mbo_plan_t p, int load_flags, const void* Ain, vo
     return run_row_vp(p, apply, st);
 }
 
+// Workspace of the band-limited volume-preserving iteration (2-D), one
+// allocation: the second set of row spectra, then the listed keys, their counts
+// and indices.
+mbo_status ensure_volume_fast(mbo_plan_t p)
+{
+    const size_t B = (size_t)p->batch, np = B * (size_t)p->npts;
+    const size_t zb = B * p->PL * (size_t)p->N[0] * p->band_W * 2 * p->esz;  // a multiple of 256
+    if (p->vz && p->vz_bytes >= zb) return MBO_OK;
+    drop_graph(p);  // a captured iteration holds the old buffer
+    free_dev(p->vz);
+    p->vz_bytes = 0;
+    FastRowArgs r;
+    std::memset(&r, 0, sizeof r);
+    (void)launch_row_fast_vkey(p->pk, p->n, ilog2((int)p->N[1]), r, dim3(1), nullptr, true);
+    (void)hipGetLastError();
+    HIP_TRY(p, hipMalloc(&p->vz, zb + np * 8 + (np + B) * 4));
+    p->vkey = reinterpret_cast<unsigned long long*>(static_cast<char*>(p->vz) + zb);
+    p->vcnt = reinterpret_cast<unsigned*>(p->vkey + np);
+    p->vidx = p->vcnt + B;
+    HIP_TRY(p, launch_fill_i32(reinterpret_cast<int*>(p->vcnt), (int64_t)B, 0, p->stream));
+    p->vz_bytes = zb;
+    return MBO_OK;
+}
+
+// Enqueue mbo_iterate_volume through the band-limited passes.  Per iteration:
+// the heat pass, the row pass that projects every point onto the side that its
+// determinant says and writes Delta E (row_fast_vkey, into the other set of row
+// spectra), the three-launch selection, and volume_fix on the points that the
+// selection moves: 52 us at n = 3, 512^2 in float (heat 7, row 17, selection 15,
+// volume_fix 13), where the general passes (both candidates of every point,
+// twice) and the seven-launch selection took 92 (13 + 17.5 + 33 + 27.5).
+// With the caller's own volume the first selection may move most of the
+// points: that iteration runs the general selection and reassignment on the
+// diffused field; from then on the field holds that volume.
+hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy, hipStream_t st)
+{
+    const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
+    hipError_t e;
+    if ((e = launch_fill_u64(p->flips, cs, 0ull, st)) != hipSuccess) return e;
+    if ((e = launch_fill_u64(p->fallbacks, cs, 0ull, st)) != hipSuccess) return e;
+    if ((e = launch_fill_u64(p->nonfinite, cs, 0ull, st)) != hipSuccess) return e;
+    if ((e = launch_fill_i32(p->stop_iter, p->batch, K, st)) != hipSuccess) return e;
+    const int fb = p->prec == MBO_F32_F64FALLBACK ? RF_FALLBACK : 0;
+    FastRowArgs r0 = fast_row_args(p);
+    r0.Ain = A;
+    r0.flags = RF_LOAD_REAL | RF_FORWARD | RF_SIGN_INIT;
+    if ((e = run_row_fast(p, r0, st)) != hipSuccess) return e;
+    if (from_a0 && (e = launch_count_pos(p->sgn, p->npts, (int)p->batch, p->vnplus, st)) != hipSuccess)
+        return e;
+    auto heat = [&](void* Z, int slot, int apply) {
+        FastColArgs h = fast_col_args(p);
+        h.Z = Z;
+        h.K = K;
+        h.slot = slot;
+        h.stop_iter = slot < 0 ? p->stop_iter : nullptr;
+        h.epart = want_energy ? p->epart : nullptr;
+        h.apply = apply;
+        return run_heat_fast(p, h, st);
+    };
+    int first = 1;
+    if (!from_a0 && K > 0) {
+        if ((e = heat(p->Z, 0, 1)) != hipSuccess) return e;
+        FastRowArgs r1 = fast_row_args(p);
+        r1.Aout = A;
+        r1.flags = RF_INVERSE | RF_STORE_REAL;
+        if ((e = run_row_fast(p, r1, st)) != hipSuccess) return e;
+        RowArgs r = row_args(p);
+        r.Aout = A;
+        r.iter = 1;
+        r.K = K;
+        r.flips = p->flips;
+        r.fallbacks = p->fallbacks;
+        r.nonfinite = p->nonfinite;
+        r.flags = RF_SIGN | RF_STORE_REAL;
+        if ((e = enqueue_volume_step(p, RF_LOAD_REAL, A, p->vde, r, st)) != hipSuccess) return e;
+        r0.flags = RF_LOAD_REAL | RF_FORWARD;
+        if ((e = run_row_fast(p, r0, st)) != hipSuccess) return e;
+        first = 2;
+    }
+    SelListArgs sa;
+    sa.s = sel_args(p, p->vde);
+    sa.key = p->vkey;
+    sa.idx = p->vidx;
+    sa.count = p->vcnt;
+    void *Zin = p->Z, *Zout = p->vz;
+    const dim3 rg((unsigned)fast_row_groups(p), (unsigned)p->batch);
+    for (int s = first; s <= K; ++s) {
+        if ((e = heat(Zin, s - 1, 1)) != hipSuccess) return e;
+        FastRowArgs r = fast_row_args(p);
+        r.Z = Zin;
+        r.Zout = Zout;
+        r.Aout = A;
+        r.vde = p->vde;
+        r.iter = s;
+        r.K = K;
+        r.cnt_part = p->cnt_part;
+        r.flags = RF_INVERSE | fb;
+        if (s < K || want_energy) r.flags |= RF_FORWARD;
+        if (s == K) r.flags |= RF_STORE_REAL;
+        if ((e = launch_row_fast_vkey(p->pk, p->n, ilog2((int)p->N[1]), r, rg, st)) != hipSuccess) return e;
+        if ((e = launch_select_list(p->pk, sa, (int)p->batch, st)) != hipSuccess) return e;
+        VolFixArgs f;
+        f.r = r;
+        f.vsel = p->vsel;
+        if ((e = launch_volume_fix(p->pk, p->n, f, rg, st)) != hipSuccess) return e;
+        std::swap(Zin, Zout);
+    }
+    if ((e = launch_sum_counts(p->cnt_part, fast_row_groups(p), K, first - 1, (int)p->batch, p->flips, p->fallbacks,
+                               p->nonfinite, st)) != hipSuccess)
+        return e;
+    if (!want_energy) return hipSuccess;
+    if ((e = heat(Zin, -1, 0)) != hipSuccess) return e;
+    ReduceArgs ra;
+    ra.epart = p->epart;
+    ra.nwg = fast_energy_partials(p);
+    ra.K = K;
+    ra.batch = (int)p->batch;
+    ra.n = p->n;
+    ra.npts = p->npts;
+    ra.tau = p->tau;
+    ra.taus = p->taus_dev;
+    ra.stop_iter = p->stop_iter;
+    ra.energy = p->energy;
+    return launch_reduce(ra, st);
+}
+
 // Enqueue the whole of mbo_iterate_volume on stream st.  from_a0: the points to
 // select are the points of A_0 with det >= 0 (else vnplus holds them).
 hipError_t enqueue_iterate_volume(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy, hipStream_t st)
 {
+    if (p->fast && p->d == 2) return enqueue_iterate_volume_fast(p, A, K, from_a0, want_energy, st);
     const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
     hipError_t e;
     if ((e = launch_fill_u64(p->flips, cs, 0ull, st)) != hipSuccess) return e;
@@ -3102,6 +3237,7 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
     mbo_status s;
     if ((s = ensure_logs(p, K)) != MBO_OK) return s;
     if ((s = ensure_volume(p)) != MBO_OK) return s;
+    if (p->fast && p->d == 2 && (s = ensure_volume_fast(p)) != MBO_OK) return s;
     if (!from_a0 && (s = upload_nplus(p, n_plus)) != MBO_OK) return s;
     const int key = (want_energy ? 1 : 0) | (from_a0 ? 2 : 0);
     if (use_graphs()) {

@@ -800,22 +800,11 @@ __device__ __forceinline__ void polar_jacobi(const T* a_in, T* q, int& dsign, T&
     jacobi_finish<T, n>(W, V, ex, q, dsign, smin);
 }
 
-// The same in double, warm-started from the right singular vectors V0 of a
-// float run on the same matrix, for a result that is rounded to float: V0 is
-// re-orthonormalised in double (modified Gram-Schmidt), W = A V0 is then nearly
-// column-orthogonal, and the sweeps (rotations of order float rounding) run to
-// the double stopping rule: the points that come here may have an
-// ill-conditioned polar factor (2 / (sigma_{n-1} + sigma_n) up to ~1e7), which
-// would carry a looser stop into the float result.  A is read as float (its
-// entries widen exactly, so the products are those of a double copy and the
-// float exponent is the double one) and Q is rounded to float as it is formed;
-// the sign of det Q is taken from the rounded Q (orthogonal: |det| = 1 up to
-// rounding).  Both save the registers of a double copy.
+// V = the columns of V0 (orthonormal to float rounding) orthonormalised in
+// double, by modified Gram-Schmidt.
 template <int n>
-__device__ __forceinline__ void polar_jacobi_warm(const float* a_in, const float (&V0)[n][n], float* q, int& dsign)
+__device__ __forceinline__ void orthonormal_columns(const float (&V0)[n][n], double (&V)[n][n])
 {
-    const int ex = scale_exponent<float, n>(a_in);
-    double V[n][n], W[n][n];
 #pragma unroll
     for (int i = 0; i < n; ++i)
 #pragma unroll
@@ -837,6 +826,26 @@ __device__ __forceinline__ void polar_jacobi_warm(const float* a_in, const float
 #pragma unroll
         for (int i = 0; i < n; ++i) V[i][j] *= inv;
     }
+}
+
+// The same in double, warm-started from the right singular vectors V0 of a
+// float run on the same matrix, for a result that is rounded to float: V0 is
+// re-orthonormalised in double (modified Gram-Schmidt), W = A V0 is then nearly
+// column-orthogonal, and the sweeps (rotations of order float rounding) run to
+// the double stopping rule: the points that come here may have an
+// ill-conditioned polar factor (2 / (sigma_{n-1} + sigma_n) up to ~1e7), which
+// would carry a looser stop into the float result.  A is read as float (its
+// entries widen exactly, so the products are those of a double copy and the
+// float exponent is the double one) and Q is rounded to float as it is formed;
+// the sign of det Q is taken from the rounded Q (orthogonal: |det| = 1 up to
+// rounding).  Both save the registers of a double copy.
+// Returns the smallest singular value.
+template <int n>
+__device__ __forceinline__ double polar_jacobi_warm(const float* a_in, const float (&V0)[n][n], float* q, int& dsign)
+{
+    const int ex = scale_exponent<float, n>(a_in);
+    double V[n][n], W[n][n];
+    orthonormal_columns<n>(V0, V);
 #pragma unroll
     for (int i = 0; i < n; ++i)
 #pragma unroll
@@ -849,6 +858,7 @@ __device__ __forceinline__ void polar_jacobi_warm(const float* a_in, const float
     jacobi_sweeps<double, n>(W, V);
     double smin;
     jacobi_finish<double, n, float>(W, V, ex, q, dsign, smin);
+    return smin;
 }
 
 // Closest orthogonal matrix of a (n*n values).  Returns sgn det Q and the
@@ -1375,8 +1385,9 @@ __device__ __forceinline__ bool all_finite(const T* a)
 // The projection's vector-Jacobian product at a point, in the plan's precision
 // T with the double fallback of float plans (g: the cotangent, also at G[k gs]).
 // n = 2 in closed form; n = 3 from the Newton polar factor where sigma_min is
-// certainly not small, else from the SVD; n = 4 from the SVD.  n = 3 against
-// the SVD for every point, 256^2 in float: 9.5 -> 5 us per vjp_kernel launch.
+// certainly not small, else from the SVD (the SVD of every point took vjp_kernel
+// 9.5 us at n = 3, 256^2 in float; row_fast_vjp, which holds this, takes 7.6 with
+// both line transforms); n = 4 from the SVD.
 template <typename T, int n>
 __device__ __forceinline__ bool polar_vjp_newton3(const T* a, const T* g, T* ga, double sigma_fb)
 {

@@ -37,6 +37,7 @@
 #pragma once
 
 #include "mbo_kernels.hpp"
+#include "mbo_volume.hpp"
 
 namespace mbo {
 
@@ -156,8 +157,9 @@ struct RowFastShape {
 
 // What the points of a row pass go through between the two line transforms:
 // FM_ITER the steps that the flags name (projection, load, store), FM_VJP the
-// projection's vector-Jacobian product with the cotangent field a.Gin.
-enum { FM_ITER = 0, FM_VJP = 1 };
+// projection's vector-Jacobian product with the cotangent field a.Gin, FM_VKEY
+// the projection with Delta E of the volume-preserving step into a.vde.
+enum { FM_ITER = 0, FM_VJP = 1, FM_VKEY = 2 };
 
 template <typename T, int n, int LOG2L, bool PM, int MODE>
 __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
@@ -170,7 +172,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* lr = reinterpret_cast<T*>(smem_raw);
     T* li = lr + (size_t)S::LINES * LP;
-    __shared__ unsigned short fq[(HELPER || S::DEFER4 || (MODE == FM_VJP && n == 3)) ? S::P : 1];
+    __shared__ unsigned short fq[(HELPER || S::DEFER4 || (MODE != FM_ITER && n == 3)) ? S::P : 1];
     __shared__ int fq_n, fq_claim;
     // rows of at most 512 points (every wave holds points): the last wave's
     // Newton points, handed to the other waves when it runs the queue
@@ -202,6 +204,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     const int64_t row0 = RPW * (((nwgx & 7) || !pm) ? (int64_t)blockIdx.x
                                                     : (int64_t)(blockIdx.x & 7) * (nwgx >> 3) + (blockIdx.x >> 3));
     C* Zb = reinterpret_cast<C*>(a.Z) + (size_t)b * PL * a.rows * W;
+    C* Zo = MODE == FM_VKEY ? reinterpret_cast<C*>(a.Zout) + (size_t)b * PL * a.rows * W : Zb;
 
     // Every global load that does not depend on another is issued first (the
     // kept modes of the first round of lines, the twiddles, the previous det
@@ -425,6 +428,71 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                     }
                     __builtin_amdgcn_s_setprio(0);
                 }
+            }
+        }
+        __syncthreads();
+    } else if constexpr (MODE == FM_VKEY) {
+        // Q = U V^t of every point and Delta E = +-2 sigma_min with the sign bit
+        // of det Q (also where sigma_min is 0: volume_fix reads the side there).
+        // Float points below sigma_fb are queued and done in double afterwards.
+        T* vde = reinterpret_cast<T*>(a.vde) + (size_t)b * npts;
+        auto key_out = [&](int64_t xp, T* lrq, T* liq, const T (&qv)[NN], int ds, T smin) {
+            vde[xp] = ds > 0 ? smin + smin : -(smin + smin);
+            finish(xp, lrq, liq, qv, ds, (int8_t)0);
+        };
+        constexpr bool QUEUE = sizeof(T) == 4 && n >= 3;
+#pragma unroll 1
+        for (int pp = 0; pp < PPT; ++pp) {
+            int64_t xp;
+            T *lrq, *liq;
+            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+                T av[NN], qv[NN];
+                load_point(lrq, liq, av);
+                nbad += all_finite<T, NN>(av) ? 0ull : 1ull;
+                if constexpr (n <= 2) {
+                    T tm[NN], de;
+                    nfb += vp_point<T, n>(av, qv, tm, de, fallback, a.sigma_fb) ? 1ull : 0ull;
+                    const bool plus = de >= (T)0;
+                    if (!plus) {
+#pragma unroll
+                        for (int k = 0; k < NN; ++k) qv[k] = tm[k];
+                    }
+                    const T half = (de < (T)0 ? -de : de) * (T)0.5;
+                    key_out(xp, lrq, liq, qv, plus ? 1 : -1, half);
+                } else {
+                    int ds;
+                    T smin;
+                    polar_jacobi<T, n>(av, qv, ds, smin);
+                    if (QUEUE && fallback && (double)smin < a.sigma_fb)
+                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * 512 + tid);
+                    else
+                        key_out(xp, lrq, liq, qv, ds, smin);
+                }
+            }
+        }
+        if constexpr (QUEUE) {
+            __syncthreads();
+            if (fq_n > 0 && tid < 64) {
+                __builtin_amdgcn_s_setprio(3);
+#pragma unroll 1
+                for (int qi = tid; qi < fq_n; qi += 64) {
+                    int64_t xp;
+                    T *lrq, *liq;
+                    (void)point_of(fq[qi], xp, lrq, liq);
+                    float aq[NN], qv[NN];
+                    load_point(lrq, liq, aq);
+                    float V[n][n];
+                    int ds;
+                    float sm;
+                    {
+                        // float Jacobi again for its V (sigma_fb = inf: it stops there)
+                        (void)polar_jacobi_f32_fb<n>(aq, qv, ds, V, INFINITY);
+                        sm = (float)polar_jacobi_warm<n>(aq, V, qv, ds);
+                    }
+                    ++nfb;
+                    key_out(xp, lrq, liq, qv, ds, sm);
+                }
+                __builtin_amdgcn_s_setprio(0);
             }
         }
         __syncthreads();
@@ -660,16 +728,16 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                     v.y = im3[0][e];
                     if (kx < W - c) {
                         if (kx > c) { v.x = 0; v.y = 0; }
-                        Zb[zat(pl, row, kx)] = v;
+                        Zo[zat(pl, row, kx)] = v;
                     } else if (kx >= L - c) {
-                        Zb[zat(pl, row, W - L + kx)] = v;
+                        Zo[zat(pl, row, W - L + kx)] = v;
                     }
                 }
             }
         }
     }
 
-    if (flags & (RF_PROJECT | RF_TRACK)) {
+    if (MODE == FM_VKEY || (flags & (RF_PROJECT | RF_TRACK))) {
         // counts of the workgroup: packed 21 bits each (at most 2048 per workgroup)
         unsigned long long packed = wave_sum(nflip | (nfb << 21) | (nbad << 42));
         unsigned long long dbits = (unsigned long long)__double_as_longlong(dmax);
@@ -707,6 +775,208 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFast
     row_fast_vjp(const FastRowArgs a)
 {
     row_fast_body<T, n, LOG2L, false, FM_VJP>(a);
+}
+
+// n = 4: the Jacobi of every point with its singular values takes more than 128
+// registers; one workgroup per CU without scratch memory (whose set-up delays
+// the start of the workgroups) rather than two with it: 256^2 in float, six
+// steps 596 -> 571 us.
+template <typename T, int n, int LOG2L>
+__global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS),
+                                  (n == 4 ? (RowFastShape<T, n, LOG2L>::THREADS + 255) / 256
+                                          : RowFastShape<T, n, LOG2L>::WAVES))
+    row_fast_vkey(const FastRowArgs a)
+{
+    row_fast_body<T, n, LOG2L, false, FM_VKEY>(a);
+}
+
+// ---------------------------------------------------------------------------
+// The points that the volume-preserving selection puts on the other side
+// ---------------------------------------------------------------------------
+// One workgroup per row_fast workgroup (at least 512 points, whole rows).  A
+// point whose membership differs from the sign of its Delta E changes from Q to
+// the candidate of the other determinant, T = Q - 2 u v^t (Lemma 7.1).  Few do:
+// the selection moves the cut only as far as the volume drifted in one step.
+// Each of them is read back from the kept row modes by a direct sum (16 lanes
+// per point), the change T - Q is formed by vp_change and added to
+// the row spectra that row_fast_vkey wrote, again by direct sums over the kept
+// modes.  Rows without such points end after reading Delta E and the det signs:
+// the pass costs 5 us at 512^2, n = 3 in float, where transforming every row
+// again cost 27.
+// Threads: 512 in float up to n = 3 (32 points at a time; two workgroups per CU),
+// else 256.  Dynamic LDS: the twiddle table.
+template <typename T, int n>
+struct VolumeFixShape {
+    static constexpr int NT = sizeof(T) == 4 && n <= 3 ? 512 : 256;
+    static constexpr int WAVES = NT == 512 ? 4 : 1;
+};
+
+template <typename T, int n>
+__global__ void __launch_bounds__((VolumeFixShape<T, n>::NT), (VolumeFixShape<T, n>::WAVES))
+    volume_fix(const VolFixArgs f)
+{
+    constexpr int NN = n * n, PL = (NN + 1) / 2, NT = VolumeFixShape<T, n>::NT, NB = NT / 16, PER = 2048 / NT;
+    typedef typename cx<T>::type C;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C* twl = reinterpret_cast<C*>(smem_raw);
+    const FastRowArgs& a = f.r;
+    __shared__ unsigned short list[2048];
+    __shared__ int wcnt[PER][NT / 64];
+    __shared__ T delta[NB][2 * PL];
+    __shared__ int xs[NB], rs[NB];  // column and row (within the workgroup) of each point in work
+    __shared__ unsigned wflip[NT / 64];
+    const int b = blockIdx.y, tid = threadIdx.x, L = a.L, W = a.W, c = a.band;
+    const int lg = 31 - __clz(L), rpw = L >= 512 ? 1 : 512 >> lg;
+    const int64_t row0 = (int64_t)blockIdx.x * rpw;
+    const int64_t p0 = row0 * L;
+    const int64_t left = a.npts - p0;
+    const int P = (int)(left < (int64_t)rpw * L ? left : (int64_t)rpw * L);  // points of this workgroup, <= 2048
+    const T* vde = reinterpret_cast<const T*>(a.vde) + (size_t)b * a.npts + p0;
+    int8_t* sgn = a.sgn + (size_t)b * a.npts + p0;
+    T de[PER];
+    int8_t old[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = k * NT + tid;
+        de[k] = i < P ? vde[i] : (T)0;
+        old[k] = i < P ? sgn[i] : (int8_t)0;
+    }
+    const VpSel sel = f.vsel[b];
+    // the changed points, listed in index order
+    unsigned flips = 0, chg = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (k * NT >= P) continue;  // uniform
+        const int i = k * NT + tid;
+        bool ch = false;
+        if (i < P) {
+            const bool in = vp_member(sel, vp_key(de[k]), p0 + i);
+            ch = in == (bool)__builtin_signbit(de[k]);
+            const int8_t now = in ? 1 : -1;
+            if (old[k] != now) {
+                sgn[i] = now;
+                ++flips;
+            }
+        }
+        chg |= ch ? 1u << k : 0u;
+        const unsigned long long bal = __ballot(ch);
+        if ((tid & 63) == 0) wcnt[k][tid >> 6] = __popcll(bal);
+    }
+    flips = (unsigned)wave_sum((unsigned long long)flips);
+    if ((tid & 63) == 0) wflip[tid >> 6] = flips;
+    __syncthreads();
+    int m = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (k * NT >= P) continue;
+        const unsigned long long bal = __ballot((chg >> k) & 1u);
+        int at = m;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            at += w < (tid >> 6) ? wcnt[k][w] : 0;
+            m += wcnt[k][w];
+        }
+        at += __popcll(bal & ((1ull << (tid & 63)) - 1ull));
+        if ((chg >> k) & 1u) list[at] = (unsigned short)(k * NT + tid);
+    }
+    if (tid == 0 && a.cnt_part) {
+        unsigned all = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) all += wflip[w];
+        if (all) a.cnt_part[((int64_t)b * a.K + (a.iter - 1)) * gridDim.x + blockIdx.x] += all;
+    }
+    if (m == 0) return;  // uniform
+    __syncthreads();     // the list is written
+
+    for (int i = tid; i < L; i += NT) twl[i] = reinterpret_cast<const C*>(a.tw)[i];
+    const C* tw = reinterpret_cast<const C*>(a.tw);
+    const C* Zi = reinterpret_cast<const C*>(a.Z) + (size_t)b * PL * a.rows * W;
+    C* Zo = reinterpret_cast<C*>(a.Zout) + (size_t)b * PL * a.rows * W;
+    T* Aout = reinterpret_cast<T*>(a.Aout) + field_base(a.foff, b, NN * a.npts);
+    const int lane = tid & 15, g = tid >> 4;
+    const bool fallback = (a.flags & RF_FALLBACK) != 0;
+    for (int j0 = 0; j0 < m; j0 += NB) {
+        const int nb = m - j0 < NB ? m - j0 : NB;
+        if (g < nb) {
+            const int i = list[j0 + g];
+            const int x = i & (L - 1);
+            const int64_t row = row0 + (i >> lg);
+            if (lane == 0) {
+                xs[g] = x;
+                rs[g] = i >> lg;
+            }
+            T av[2 * PL];
+#pragma unroll
+            for (int k = 0; k < 2 * PL; ++k) av[k] = (T)0;
+            // four modes per lane and step, every load of a step in flight
+            for (int w0 = lane; w0 < W; w0 += 64) {
+                C t[4], z[4][PL];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int w = w0 + 16 * q < W ? w0 + 16 * q : 0;
+                    const int kx = (W == L || w <= c) ? w : L - W + w;  // unused slots hold zeros
+                    t[q] = tw[(kx * x) & (L - 1)];
+#pragma unroll
+                    for (int p = 0; p < PL; ++p) z[q][p] = Zi[((size_t)p * a.rows + row) * W + w];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (w0 + 16 * q >= W) continue;
+#pragma unroll
+                    for (int p = 0; p < PL; ++p) {
+                        av[2 * p] += z[q][p].x * t[q].x + z[q][p].y * t[q].y;  // z exp(+2 pi i kx x / L)
+                        av[2 * p + 1] += z[q][p].y * t[q].x - z[q][p].x * t[q].y;
+                    }
+                }
+            }
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1)
+#pragma unroll
+                for (int k = 0; k < 2 * PL; ++k) av[k] += __shfl_xor(av[k], o, 64);
+            const T di = vde[i];
+            T d[NN], q[NN];
+            const bool last = (a.flags & RF_STORE_REAL) != 0;  // row_fast_vkey stored Q
+#pragma unroll
+            for (int k = 0; k < NN; ++k) q[k] = last ? Aout[(int64_t)k * a.npts + p0 + i] : (T)0;
+            vp_change<T, n>(av, !(bool)__builtin_signbit(di), di, fallback, a.sigma_fb, q, last, d);
+            if (last && lane == 0) {
+#pragma unroll
+                for (int k = 0; k < NN; ++k) Aout[(int64_t)k * a.npts + p0 + i] = q[k];
+            }
+            if (lane == 0) {
+#pragma unroll
+                for (int k = 0; k < NN; ++k) delta[g][k] = d[k];
+                if (NN & 1) delta[g][NN] = (T)0;
+            }
+        }
+        __syncthreads();
+        // spectra of the rows of these points: a thread owns its (plane, mode)
+        // pairs, the points of a row follow each other in the list
+        if (a.flags & RF_FORWARD) {
+            for (int e = tid; e < PL * W; e += NT) {
+                const int p = e / W, w = e - p * W;
+                if (W != L && w > c && w < W - c) continue;  // unused slot: stays zero
+                const int kx = (W == L || w <= c) ? w : L - W + w;
+                int j = 0;
+                while (j < nb) {
+                    const int r = rs[j];
+                    C* z = &Zo[((size_t)p * a.rows + row0 + r) * W + w];
+                    C v = *z;
+                    int j1 = j;
+                    while (j1 < nb && rs[j1] == r) ++j1;
+#pragma unroll 4
+                    for (; j < j1; ++j) {
+                        const C t = twl[(kx * xs[j]) & (L - 1)];
+                        const T dr = delta[j][2 * p], di = delta[j][2 * p + 1];
+                        v.x += dr * t.x - di * t.y;  // (dr + i di) exp(-2 pi i kx x / L)
+                        v.y += dr * t.y + di * t.x;
+                    }
+                    *z = v;
+                }
+            }
+        }
+        __syncthreads();  // delta is free for the next points
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -217,6 +217,17 @@ struct SelArgs {
     uint8_t* mask;           // launch_sel_mark: 1 = selected [batch][npts]
 };
 hipError_t launch_select(int prec, const SelArgs& a, int batch, hipStream_t st);
+// The same selection in three launches, for Delta E values whose cut falls where
+// the values are spread out (along the volume-preserving iteration, near zero):
+// the histogram of the top digit, the points of the digit holding the cut
+// listed (key and index), and one workgroup that ends the search among them.
+struct SelListArgs {
+    SelArgs s;
+    unsigned long long* key;  // [batch][npts] keys of the listed points
+    unsigned* idx;            // [batch][npts] their point indices
+    unsigned* count;          // [batch] listed points, zero between uses
+};
+hipError_t launch_select_list(int prec, const SelListArgs& a, int batch, hipStream_t st);
 hipError_t launch_sel_mark(int prec, const SelArgs& a, int batch, hipStream_t st);
 // out[b] = number of points p with sgn[b][p] > 0 (out is overwritten)
 hipError_t launch_count_pos(const int8_t* sgn, int64_t npts, int batch, long long* out,
@@ -384,6 +395,14 @@ struct FastRowArgs {
     unsigned long long* cnt_part;  // nullable: packed flips | fallbacks << 21 | non-finite << 42
                                    // per workgroup [batch][K][gridDim.x]
     const void* Gin;         // row_fast_vjp: cotangent field [batch][n*n][npts]
+    void* Zout;              // row_fast_vkey: row spectra written (Z is read)
+    void* vde;               // row_fast_vkey: Delta E per point [batch][npts]
+};
+
+// The points that the volume-preserving selection reassigns (volume_fix).
+struct VolFixArgs {
+    FastRowArgs r;           // Z: spectra read by row_fast_vkey, Zout: the spectra it wrote
+    const VpSel* vsel;       // finished selection of each field [batch]
 };
 
 struct FastColArgs {
@@ -438,15 +457,22 @@ hipError_t launch_row_fast_vjp(int prec, int n, int log2L, const FastRowArgs& a,
 hipError_t launch_heat_fast_adj(int prec, int log2L, int mode, const FastColArgs& a, dim3 grid, hipStream_t st,
                                 bool prepare = false);
 int heat_fast_adj_tile(int log2L);
+// The volume-preserving step's passes (2-D): row_fast_vkey projects every point
+// onto the side that its determinant says, writes Delta E and the row spectra;
+// volume_fix moves the points that the selection puts on the other side.
+hipError_t launch_row_fast_vkey(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
+                                bool prepare = false);
+hipError_t launch_volume_fix(int prec, int n, const VolFixArgs& a, dim3 grid, hipStream_t st);
 // the 3-D plane pass (float): one workgroup per (packed plane, stored x mode)
 hipError_t launch_plane_fast(int log2Y, int log2Z, const FastColArgs& a, dim3 grid, hipStream_t st,
                              bool prepare = false, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 int plane_fast_threads(int log2Y, int log2Z);
 size_t plane_fast_lds_bytes(int log2Y, int log2Z);
-// flips / fallbacks / non-finite of every iteration and field from the row
+// flips / fallbacks / non-finite of every iteration from `first` on and field from the row
 // pass's per-workgroup packed counts [batch][K][nwg]
-hipError_t launch_sum_counts(const unsigned long long* part, int nwg, int K, int batch, unsigned long long* flips,
-                             unsigned long long* fallbacks, unsigned long long* nonfinite, hipStream_t st);
+hipError_t launch_sum_counts(const unsigned long long* part, int nwg, int K, int first, int batch,
+                             unsigned long long* flips, unsigned long long* fallbacks,
+                             unsigned long long* nonfinite, hipStream_t st);
 // Layout of the band-limited passes of a 2-D grid N0 x N1 with n x n entries in
 // precision pk (1 float, 0 double) for the diffusion times taus[0..ntau): kept
 // half-width, stored modes per row (every mode when banded is false or nothing

@@ -333,12 +333,13 @@ hipError_t launch_fill_uniform(int prec, void* p, int64_t count, uint64_t seed, 
 
 // One workgroup per (field, iteration): the sums of the unpacked counts of
 // every row-pass workgroup, in a fixed order.
-__global__ void __launch_bounds__(256) sum_counts(const unsigned long long* part, int nwg, int K,
+__global__ void __launch_bounds__(256) sum_counts(const unsigned long long* part, int nwg, int K, int first,
                                                   unsigned long long* flips, unsigned long long* fallbacks,
                                                   unsigned long long* nonfinite)
 {
     __shared__ unsigned long long sh[3][256];
-    const int64_t slot = blockIdx.x;  // b * K + s
+    const int s = first + (int)blockIdx.x % (K - first);
+    const int64_t slot = (int64_t)((int)blockIdx.x / (K - first)) * K + s;  // b * K + s
     const unsigned long long* pp = part + slot * (int64_t)nwg;
     const unsigned long long m21 = (1ull << 21) - 1;
     unsigned long long f = 0, fb = 0, bad = 0;
@@ -364,12 +365,13 @@ __global__ void __launch_bounds__(256) sum_counts(const unsigned long long* part
     }
 }
 
-hipError_t launch_sum_counts(const unsigned long long* part, int nwg, int K, int batch, unsigned long long* flips,
-                             unsigned long long* fallbacks, unsigned long long* nonfinite, hipStream_t st)
+hipError_t launch_sum_counts(const unsigned long long* part, int nwg, int K, int first, int batch,
+                             unsigned long long* flips, unsigned long long* fallbacks,
+                             unsigned long long* nonfinite, hipStream_t st)
 {
-    if (K <= 0) return hipSuccess;
-    hipLaunchKernelGGL(sum_counts, dim3((unsigned)((int64_t)batch * K)), dim3(256), 0, st, part, nwg, K, flips,
-                       fallbacks, nonfinite);
+    if (K <= first) return hipSuccess;
+    hipLaunchKernelGGL(sum_counts, dim3((unsigned)((int64_t)batch * (K - first))), dim3(256), 0, st, part, nwg, K,
+                       first, flips, fallbacks, nonfinite);
     return hipGetLastError();
 }
 

@@ -61,12 +61,24 @@ __global__ void __launch_bounds__(256) sel_hist(const SelArgs a, int shift, int 
         const int64_t x = x0 + (int64_t)k * 256;
         val[k] = x < a.npts ? v[x] : (T)0;
     }
+    // equal digits that follow each other in a thread count once (smooth fields:
+    // most points of a chunk share the digit, and the lanes' atomics on its bin
+    // are done one after another)
+    unsigned bin = 0u, run = 0u;
 #pragma unroll
     for (int k = 0; k < SEL_PER; ++k) {
         const unsigned long long key = vp_key(val[k]);
-        if (x0 + (int64_t)k * 256 < a.npts && (top >= KB || (key >> top) == (pre >> top)))
-            atomicAdd(&h[(key >> shift) & (unsigned)(nb - 1)], 1u);
+        if (x0 + (int64_t)k * 256 < a.npts && (top >= KB || (key >> top) == (pre >> top))) {
+            const unsigned d = (unsigned)(key >> shift) & (unsigned)(nb - 1);
+            if (run && d != bin) {
+                atomicAdd(&h[bin], run);
+                run = 0u;
+            }
+            bin = d;
+            ++run;
+        }
     }
+    if (run) atomicAdd(&h[bin], run);
     __syncthreads();
     unsigned* g = a.hist + (size_t)b * (1 << SEL_BITS);
     for (int i = threadIdx.x; i < nb; i += blockDim.x)
@@ -231,6 +243,221 @@ __global__ void __launch_bounds__(256) sel_tie(const SelArgs a)
     }
 }
 
+// ---------------------------------------------------------------------------
+// The three-launch selection (SelListArgs)
+// ---------------------------------------------------------------------------
+
+// The digit holding the cut, found by every workgroup for itself from the
+// histogram (8 KB; one launch fewer than a pick kernel), then the chunk's points
+// of that digit appended to the field's list, in no particular order.
+template <typename T>
+__global__ void __launch_bounds__(256) sel_list(const SelListArgs la, int shift)
+{
+    const SelArgs& a = la.s;
+    __shared__ long long sh[4];
+    __shared__ long long s_need;
+    __shared__ int s_digit;
+    __shared__ unsigned s_cnt, s_base;
+    const int b = blockIdx.y, tid = threadIdx.x;
+    const long long np = a.nplus[b];
+    VpSel* st = a.st + b;
+    if (np <= 0 || np >= a.npts) {  // uniform
+        if (blockIdx.x == 0 && tid == 0) {
+            st->mode = np <= 0 ? VS_NONE : VS_ALL;
+            st->kstar = 0ull;
+            st->need = 0;
+            st->ties = 0;
+            st->istar = -1;
+        }
+        return;
+    }
+    // every load of the chunk in flight while the histogram is scanned
+    const T* v = reinterpret_cast<const T*>(a.dE) + (size_t)b * a.npts;
+    const int64_t x0 = (int64_t)blockIdx.x * SEL_CHUNK + tid;
+    T val[SEL_PER];
+#pragma unroll
+    for (int k = 0; k < SEL_PER; ++k) {
+        const int64_t x = x0 + (int64_t)k * 256;
+        val[k] = x < a.npts ? v[x] : (T)0;
+    }
+    const unsigned* g = a.hist + (size_t)b * (1 << SEL_BITS);
+    constexpr int per = (1 << SEL_BITS) / 256;
+    const int hi = (1 << SEL_BITS) - 1 - tid * per;
+    unsigned c[per];
+    long long sum = 0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        c[i] = g[hi - i];
+        sum += c[i];
+    }
+    if (tid == 0) s_cnt = 0u;
+    long long total;
+    const long long incl = scan256(sum, sh, total);
+    const long long excl = incl - sum;
+    if (excl < np && np <= incl) {  // exactly one thread
+        long long acc = excl;
+        int d = hi;
+#pragma unroll
+        for (int i = 0; i < per; ++i) {
+            if (acc + (long long)c[i] >= np) {
+                d = hi - i;
+                break;
+            }
+            acc += c[i];
+        }
+        s_digit = d;
+        s_need = np - acc;
+    }
+    __syncthreads();
+    const unsigned long long digit = (unsigned long long)s_digit;
+    if (blockIdx.x == 0 && tid == 0) {
+        st->kstar = digit << shift;
+        st->need = s_need;
+        st->mode = VS_SEARCH;
+        st->istar = -1;
+    }
+    unsigned mine = 0;
+#pragma unroll
+    for (int k = 0; k < SEL_PER; ++k)
+        mine += (x0 + (int64_t)k * 256 < a.npts && (vp_key(val[k]) >> shift) == digit) ? 1u : 0u;
+    unsigned at = mine ? atomicAdd(&s_cnt, mine) : 0u;
+    __syncthreads();
+    if (s_cnt == 0u) return;  // uniform
+    if (tid == 0) s_base = atomicAdd(la.count + b, s_cnt);
+    __syncthreads();
+    at += s_base;
+    unsigned long long* lk = la.key + (size_t)b * a.npts;
+    unsigned* li = la.idx + (size_t)b * a.npts;
+#pragma unroll
+    for (int k = 0; k < SEL_PER; ++k) {
+        const int64_t x = x0 + (int64_t)k * 256;
+        const unsigned long long key = vp_key(val[k]);
+        if (x < a.npts && (key >> shift) == digit) {
+            lk[at] = key;
+            li[at] = (unsigned)x;
+            ++at;
+        }
+    }
+}
+
+// The end of the search among the listed points, one workgroup per field:
+// digits of SEL_BITS bits of the key below the first, then, when only some of
+// the points with the last key are selected, of the index from the lower end.
+// The list is copied to LDS when it fits.  Leaves the histogram and the count at
+// zero.
+constexpr int SEL_LIST_LDS = 8192;
+__global__ void __launch_bounds__(256) sel_finish(const SelListArgs la, int shift0, int index_bits)
+{
+    const SelArgs& a = la.s;
+    __shared__ long long sh[4];
+    __shared__ unsigned h[1 << SEL_BITS];
+    __shared__ unsigned long long lkey[SEL_LIST_LDS];
+    __shared__ unsigned lidx[SEL_LIST_LDS];
+    __shared__ unsigned long long s_pre;
+    __shared__ long long s_need;
+    __shared__ unsigned s_cnt;
+    const int b = blockIdx.x, tid = threadIdx.x;
+    VpSel* st = a.st + b;
+    const long long np = a.nplus[b];
+    unsigned* g = a.hist + (size_t)b * (1 << SEL_BITS);
+    const unsigned M = la.count[b];
+    for (int i = tid; i < (1 << SEL_BITS); i += 256) g[i] = 0u;
+    if (np <= 0 || np >= a.npts) return;  // decided by sel_list, nothing listed
+    const unsigned long long* gk = la.key + (size_t)b * a.npts;
+    const unsigned* gi = la.idx + (size_t)b * a.npts;
+    const bool lds = M <= (unsigned)SEL_LIST_LDS;
+    __syncthreads();  // every wave has read the count, which is cleared below
+    if (lds)
+        for (unsigned i = tid; i < M; i += 256) {
+            lkey[i] = gk[i];
+            lidx[i] = gi[i];
+        }
+    auto key_at = [&](unsigned i) { return lds ? lkey[i] : gk[i]; };
+    auto idx_at = [&](unsigned i) { return lds ? lidx[i] : gi[i]; };
+    if (tid == 0) {
+        s_pre = st->kstar;
+        s_need = st->need;
+        s_cnt = M;
+        la.count[b] = 0u;
+    }
+    __syncthreads();
+    // one digit: histogram of (value >> sh) over the points for which `in`
+    // holds, then the digit at which the running count, from the top (down) or
+    // the bottom, reaches s_need; s_need becomes the rank within it
+    auto digit = [&](auto value, auto in, int shift, int bits, bool down) -> int {
+        __shared__ int s_d;
+        const int nb = 1 << bits;
+        for (int i = tid; i < nb; i += 256) h[i] = 0u;
+        __syncthreads();
+        for (unsigned i = tid; i < M; i += 256)
+            if (in(i)) atomicAdd(&h[(unsigned)(value(i) >> shift) & (unsigned)(nb - 1)], 1u);
+        __syncthreads();
+        const int per = (nb + 255) / 256;
+        long long sum = 0;
+        for (int i = 0; i < per; ++i) {
+            const int o = tid * per + i;
+            if (o < nb) sum += h[down ? nb - 1 - o : o];
+        }
+        long long total;
+        const long long need = s_need;
+        const long long incl = scan256(sum, sh, total);
+        const long long excl = incl - sum;
+        if (excl < need && need <= incl) {
+            long long acc = excl;
+            for (int i = 0; i < per; ++i) {
+                const int o = tid * per + i;
+                const int d = down ? nb - 1 - o : o;
+                if (acc + (long long)h[d] >= need) {
+                    s_d = d;
+                    s_cnt = h[d];
+                    s_need = need - acc;
+                    break;
+                }
+                acc += h[d];
+            }
+        }
+        __syncthreads();
+        return s_d;
+    };
+    int low = shift0;  // key bits below `low` are still open
+    while (low > 0 && s_need != (long long)s_cnt) {
+        const int bits = low < SEL_BITS ? low : SEL_BITS;
+        const int top = low;
+        low -= bits;
+        const unsigned long long pre = s_pre >> top;
+        const int d = digit(key_at, [&](unsigned i) { return (key_at(i) >> top) == pre; }, low, bits, true);
+        if (tid == 0) s_pre |= (unsigned long long)d << low;
+        __syncthreads();
+    }
+    const unsigned long long ks = s_pre;
+    if (s_need == (long long)s_cnt) {
+        // every point of the digits found is selected: the keys from ks up
+        if (tid == 0) {
+            st->kstar = ks;
+            st->mode = VS_TIES_ALL;
+            st->istar = LLONG_MAX;
+        }
+        return;
+    }
+    // the need-th smallest index among the points with key ks
+    unsigned ipre = 0u;
+    int ilow = index_bits;
+    while (ilow > 0) {
+        const int bits = ilow < SEL_BITS ? ilow : SEL_BITS;
+        const int top = ilow;
+        ilow -= bits;
+        const unsigned pre = ipre >> top;
+        const int d = digit(idx_at, [&](unsigned i) { return key_at(i) == ks && (idx_at(i) >> top) == pre; }, ilow,
+                            bits, false);
+        ipre |= (unsigned)d << ilow;
+    }
+    if (tid == 0) {
+        st->kstar = ks;
+        st->mode = VS_TIES_PART;
+        st->istar = (long long)ipre;
+    }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) sel_mark(const SelArgs a)
 {
@@ -281,6 +508,24 @@ hipError_t launch_select(int prec, const SelArgs& a, int batch, hipStream_t st)
 {
     if (a.chunks <= 0 || batch <= 0) return hipErrorInvalidValue;
     return prec == 0 ? select_t<double>(a, batch, st) : select_t<float>(a, batch, st);
+}
+
+hipError_t launch_select_list(int prec, const SelListArgs& a, int batch, hipStream_t st)
+{
+    if (a.s.chunks <= 0 || batch <= 0 || a.s.npts > (1ll << 31)) return hipErrorInvalidValue;
+    const dim3 gc((unsigned)a.s.chunks, (unsigned)batch), bl(256);
+    const int shift = (prec == 0 ? 64 : 32) - SEL_BITS;
+    int ib = 0;
+    while ((1ll << ib) < a.s.npts) ++ib;
+    if (prec == 0) {
+        hipLaunchKernelGGL((sel_hist<double>), gc, bl, 0, st, a.s, shift, SEL_BITS, 0);
+        hipLaunchKernelGGL((sel_list<double>), gc, bl, 0, st, a, shift);
+    } else {
+        hipLaunchKernelGGL((sel_hist<float>), gc, bl, 0, st, a.s, shift, SEL_BITS, 0);
+        hipLaunchKernelGGL((sel_list<float>), gc, bl, 0, st, a, shift);
+    }
+    hipLaunchKernelGGL(sel_finish, dim3((unsigned)batch), bl, 0, st, a, shift, ib);
+    return hipGetLastError();
 }
 
 hipError_t launch_sel_mark(int prec, const SelArgs& a, int batch, hipStream_t st)

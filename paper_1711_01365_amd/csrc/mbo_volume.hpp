@@ -52,6 +52,69 @@ __device__ __forceinline__ bool vp_member(const VpSel& s, unsigned long long key
 //     U D V^t reverses that direction (Lemma 7.1).  The one of Q, Q' with
 //     det +1 is T+, and Delta E = 2 sgn(det Q) sigma_min.
 template <typename T, int n>
+__device__ __forceinline__ T vp_candidates(const T* a_in, T* tp, T* tm);
+
+// The n >= 3 route, in precision T on a matrix and candidates of precision Tio.
+// WARM: V holds orthonormal columns near the right singular vectors on entry
+// (else it is set to the identity); on return V holds the right singular
+// vectors.
+template <typename T, typename Tio, int n, bool WARM>
+__device__ __forceinline__ T vp_candidates_svd(const Tio* a, T (&V)[n][n], Tio* tp, Tio* tm)
+{
+    const int ex = scale_exponent<Tio, n>(a);
+    T W[n][n];
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            if constexpr (WARM) {
+                T v = 0;
+#pragma unroll
+                for (int k = 0; k < n; ++k) v += (T)a[i * n + k] * V[k][j];
+                W[i][j] = ldexp(v, -ex);
+            } else {
+                W[i][j] = ldexp((T)a[i * n + j], -ex);
+                V[i][j] = (i == j) ? (T)1 : (T)0;
+            }
+        }
+    jacobi_sweeps<T, n>(W, V);
+    T sig[n], smin;
+    Tio q[n * n];
+    int ds;
+    jacobi_finish<T, n, Tio>(W, V, ex, q, ds, smin, sig);
+    // W holds U (the zero matrix leaves W = 0 and V = I: then U = I too,
+    // with Q = I); pick the column of the smallest singular value
+    T u[n], v[n];
+    int jm = 0;
+    bool zero = !(sig[0] > (T)0);
+#pragma unroll
+    for (int j = 1; j < n; ++j) {
+        jm = sig[j] < sig[jm] ? j : jm;
+        zero = zero && !(sig[j] > (T)0);
+    }
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        u[i] = zero ? (i == 0 ? (T)1 : (T)0) : W[i][0];
+        v[i] = V[i][0];
+#pragma unroll
+        for (int j = 1; j < n; ++j) {
+            u[i] = (jm == j && !zero) ? W[i][j] : u[i];
+            v[i] = jm == j ? V[i][j] : v[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const Tio qv = q[i * n + k];
+            const Tio r = (Tio)((T)qv - (T)2 * u[i] * v[k]);
+            tp[i * n + k] = ds > 0 ? qv : r;
+            tm[i * n + k] = ds > 0 ? r : qv;
+        }
+    return ds > 0 ? smin + smin : -(smin + smin);
+}
+
+template <typename T, int n>
 __device__ __forceinline__ T vp_candidates(const T* a_in, T* tp, T* tm)
 {
     const T* a = a_in;
@@ -79,48 +142,8 @@ __device__ __forceinline__ T vp_candidates(const T* a_in, T* tp, T* tm)
         const T det = a[0] * a[3] - a[1] * a[2];
         return r > (T)0 ? ldexp((T)4 * det / r, ex) : (T)0;
     } else {
-        const int ex = scale_exponent<T, n>(a);
-        T W[n][n], V[n][n];
-#pragma unroll
-        for (int i = 0; i < n; ++i)
-#pragma unroll
-            for (int j = 0; j < n; ++j) {
-                W[i][j] = ldexp(a[i * n + j], -ex);
-                V[i][j] = (i == j) ? (T)1 : (T)0;
-            }
-        jacobi_sweeps<T, n>(W, V);
-        T q[n * n], sig[n], smin;
-        int ds;
-        jacobi_finish<T, n>(W, V, ex, q, ds, smin, sig);
-        // W holds U (the zero matrix leaves W = 0 and V = I: then U = I too,
-        // with Q = I); pick the column of the smallest singular value
-        T u[n], v[n];
-        int jm = 0;
-        bool zero = !(sig[0] > (T)0);
-#pragma unroll
-        for (int j = 1; j < n; ++j) {
-            jm = sig[j] < sig[jm] ? j : jm;
-            zero = zero && !(sig[j] > (T)0);
-        }
-#pragma unroll
-        for (int i = 0; i < n; ++i) {
-            u[i] = zero ? (i == 0 ? (T)1 : (T)0) : W[i][0];
-            v[i] = V[i][0];
-#pragma unroll
-            for (int j = 1; j < n; ++j) {
-                u[i] = (jm == j && !zero) ? W[i][j] : u[i];
-                v[i] = jm == j ? V[i][j] : v[i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < n; ++i)
-#pragma unroll
-            for (int k = 0; k < n; ++k) {
-                const T r = q[i * n + k] - (T)2 * u[i] * v[k];
-                tp[i * n + k] = ds > 0 ? q[i * n + k] : r;
-                tm[i * n + k] = ds > 0 ? r : q[i * n + k];
-            }
-        return ds > 0 ? smin + smin : -(smin + smin);
+        T V[n][n];
+        return vp_candidates_svd<T, T, n, false>(a, V, tp, tm);
     }
 }
 
@@ -131,24 +154,177 @@ __device__ __forceinline__ T vp_candidates(const T* a_in, T* tp, T* tm)
 template <typename T, int n>
 __device__ __forceinline__ bool vp_point(const T* a, T* tp, T* tm, T& de, bool fallback, double sigma_fb)
 {
-    de = vp_candidates<T, n>(a, tp, tm);
-    if constexpr (sizeof(T) == 4 && n >= 2) {
+    if constexpr (sizeof(T) == 4 && n >= 3) {
+        float V[n][n];
+        de = vp_candidates_svd<float, float, n, false>(a, V, tp, tm);
         const T half = (de < (T)0 ? -de : de) * (T)0.5;
         if (fallback && (double)half < sigma_fb) {
-            double ad[n * n], pd[n * n], md[n * n];
-#pragma unroll
-            for (int k = 0; k < n * n; ++k) ad[k] = (double)a[k];
-            const double dd = vp_candidates<double, n>(ad, pd, md);
-#pragma unroll
-            for (int k = 0; k < n * n; ++k) {
-                tp[k] = (T)pd[k];
-                tm[k] = (T)md[k];
-            }
-            de = (T)dd;
+            // in double, from the float run's V orthonormalised (one or two
+            // sweeps instead of five)
+            double Vd[n][n];
+            orthonormal_columns<n>(V, Vd);
+            de = (T)vp_candidates_svd<double, float, n, true>(a, Vd, tp, tm);
             return true;
+        }
+    } else {
+        de = vp_candidates<T, n>(a, tp, tm);
+        if constexpr (sizeof(T) == 4 && n == 2) {
+            const T half = (de < (T)0 ? -de : de) * (T)0.5;
+            if (fallback && (double)half < sigma_fb) {
+                double ad[n * n], pd[n * n], md[n * n];
+#pragma unroll
+                for (int k = 0; k < n * n; ++k) ad[k] = (double)a[k];
+                const double dd = vp_candidates<double, n>(ad, pd, md);
+#pragma unroll
+                for (int k = 0; k < n * n; ++k) {
+                    tp[k] = (T)pd[k];
+                    tm[k] = (T)md[k];
+                }
+                de = (T)dd;
+                return true;
+            }
         }
     }
     return false;
+}
+
+// The change of a point that moves to the other determinant, d = T' - Q =
+// -2 u v^t with (u, v) the singular pair of sigma_min (Lemma 7.1), n = 3, 4.
+// cof(A) = det(A) A^{-t} has the singular vectors of A, and its largest singular
+// value belongs to that pair: the powers of cof^t cof (squared until they have
+// rank one, at most 60 times: two or three do where sigma_n is small) converge to
+// v v^t, and u = s cof v / |cof v|, s the side (sign of the determinant) that the
+// point leaves.  Where sigma_n = sigma_{n-1} to rounding, every direction between
+// their vectors is a closest choice, and the power's largest column is one.
+// have_q: q is Q as it was formed before; then u = q v, so that T' =
+// q (I - 2 v v^t) is as orthogonal as q.  False, d unset, when the cofactors are
+// no more than rounding (rank <= n - 2): the candidates then come from the SVD.
+template <typename T, typename Tio, int n>
+__device__ __forceinline__ bool vp_flip(const Tio* a_in, bool plus, const Tio* q, bool have_q, Tio* d)
+{
+    const int ex = scale_exponent<Tio, n>(a_in);
+    T a[n * n], C[n * n], M[n * n];
+#pragma unroll
+    for (int k = 0; k < n * n; ++k) a[k] = ldexp((T)a_in[k], -ex);
+    cofactor_n<T, n>(a, C);
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            T m = 0;
+#pragma unroll
+            for (int k = 0; k < n; ++k) m += C[k * n + i] * C[k * n + j];
+            M[i * n + j] = m;
+        }
+#pragma unroll 1
+    for (int it = 0; it < 60; ++it) {
+        T tr = 0;
+#pragma unroll
+        for (int i = 0; i < n; ++i) tr += M[i * n + i];
+        // cofactors below their rounding (the entries of a are below 1), or NaN
+        if (it == 0 && !(tr > (T)(64 * n * n) * num<T>::eps * num<T>::eps)) return false;
+        const T inv = (T)1 / tr;
+        T f2 = 0;
+#pragma unroll
+        for (int k = 0; k < n * n; ++k) {
+            M[k] *= inv;
+            f2 += M[k] * M[k];
+        }
+        if ((T)1 - f2 < (T)8 * num<T>::eps) break;  // 1 - f2 = 0 for rank one
+        T S[n * n];
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+#pragma unroll
+            for (int j = i; j < n; ++j) {
+                T m = 0;
+#pragma unroll
+                for (int k = 0; k < n; ++k) m += M[i * n + k] * M[k * n + j];
+                S[i * n + j] = m;
+                S[j * n + i] = m;
+            }
+#pragma unroll
+        for (int k = 0; k < n * n; ++k) M[k] = S[k];
+    }
+    // v: the column with the largest diagonal entry, refined by one more product
+    // with cof^t cof (its rounding is then that of one product, not of the powers)
+    T v[n];
+    T best = M[0];
+#pragma unroll
+    for (int i = 0; i < n; ++i) v[i] = M[i * n];
+#pragma unroll
+    for (int j = 1; j < n; ++j) {
+        const bool more = M[j * n + j] > best;
+        best = more ? M[j * n + j] : best;
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = more ? M[i * n + j] : v[i];
+    }
+    T u[n], vv = 0, uu = 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        T m = 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) m += C[i * n + k] * v[k];
+        u[i] = m;
+    }
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        T m = 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) m += C[k * n + i] * u[k];
+        v[i] = m;
+        vv += m * m;
+    }
+    if (!(vv > (T)0)) return false;
+    const T iv = num<T>::rsq(vv);
+#pragma unroll
+    for (int i = 0; i < n; ++i) v[i] *= iv;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        T m = 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) m += (have_q ? (T)q[i * n + k] : C[i * n + k]) * v[k];
+        u[i] = m;
+        uu += m * m;
+    }
+    if (!(uu > (T)0)) return false;
+    const T iu = have_q ? (T)-2 : (plus ? (T)-2 : (T)2) * num<T>::rsq(uu);
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int k = 0; k < n; ++k) d[i * n + k] = (Tio)(iu * u[i] * v[k]);
+    return true;
+}
+
+// A point of matrix a that leaves the side `plus` (its Delta E is de): the change
+// d = T' - Q, in the plan's precision T with the double fallback of float plans.
+// have_q: q holds Q on entry; T' on return.
+template <typename T, int n>
+__device__ __forceinline__ void vp_change(const T* a, bool plus, T de, bool fallback, double sigma_fb, T* q,
+                                          bool have_q, T* d)
+{
+    if constexpr (n >= 3) {
+        bool done;
+        if constexpr (sizeof(T) == 4) {
+            const T half = (de < (T)0 ? -de : de) * (T)0.5;
+            done = fallback && (double)half < sigma_fb ? vp_flip<double, T, n>(a, plus, q, have_q, d)
+                                                       : vp_flip<T, T, n>(a, plus, q, have_q, d);
+        } else {
+            done = vp_flip<T, T, n>(a, plus, q, have_q, d);
+        }
+        if (done) {
+#pragma unroll
+            for (int k = 0; k < n * n; ++k) q[k] += d[k];
+            return;
+        }
+    }
+    T tp[n * n], tm[n * n], e;
+    // n >= 3: the polar factor is not unique there, in any precision
+    (void)vp_point<T, n>(a, tp, tm, e, n <= 2 && fallback, sigma_fb);
+#pragma unroll
+    for (int k = 0; k < n * n; ++k) {
+        d[k] = plus ? tm[k] - tp[k] : tp[k] - tm[k];
+        q[k] = plus ? tm[k] : tp[k];
+    }
 }
 
 }  // namespace mbo
