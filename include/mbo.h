@@ -38,8 +38,10 @@
  *             n = 1 is sign thresholding with sgn(0) = +1 (Remark 1.2).
  * Ownership   the caller owns every field buffer; the plan owns its workspace,
  *             tables and graphs and frees them in mbo_plan_destroy.  No call
- *             keeps a caller pointer after it returns (a captured iteration graph
- *             is keyed by the field pointer and re-captured when it changes).
+ *             reads a caller pointer after it returns (a captured band-limited
+ *             iteration takes the field from a device word that each call sets;
+ *             other captured iterations are keyed by the field pointer and
+ *             re-captured when it changes).
  * Streams     all device work is enqueued on the plan's HIP stream.  Calls that
  *             return host values (mbo_energy, the logs of mbo_iterate)
  *             synchronise that stream before returning.  A plan must not be used
@@ -120,7 +122,8 @@ mbo_status mbo_plan(mbo_plan_t* out, int d, const int64_t* N, int n, int64_t bat
 /* Free a plan and everything it owns (NULL is accepted). */
 mbo_status mbo_plan_destroy(mbo_plan_t plan);
 
-/* Change the diffusion time; the heat-symbol tables are rebuilt. */
+/* Change the diffusion time; the heat-symbol tables are rebuilt (nothing is done
+ * when tau is the plan's own already). */
 mbo_status mbo_plan_set_tau(mbo_plan_t plan, double tau);
 
 /* Choose the kernels of mbo_iterate and the calls that share them (see mbo_path; a batched plan applies the

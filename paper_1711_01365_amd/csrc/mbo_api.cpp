@@ -121,7 +121,7 @@ struct mbo_plan_s {
     double* ws_dot = nullptr;
     size_t ws_spec_bytes = 0, ws_dot_bytes = 0;
     bool adj_ready = false;  // their dynamic-LDS limits are set
-    unsigned long long* counters = nullptr;  // project: [0] nonfinite, [1] fallbacks
+    unsigned long long* counters = nullptr;  // project: [0] nonfinite, [1] fallbacks, zero between calls
 
     // per-field diffusion times (fields of a batched plan): tables per field
     bool per_field_tau = false;
@@ -148,8 +148,14 @@ struct mbo_plan_s {
     std::vector<int> f_member, f_index;
     std::vector<int64_t> f_off;
 
-    // logs of mbo_iterate, capacity log_K
+    // logs of a call of K iterations (ensure_logs): one device allocation of
+    // capacity log_K; the counters, energies and stop marks lie side by side in
+    // the order below (log_words(K) words from log_block) and the last kernel of
+    // the call copies them to log_host (pinned)
     int log_K = -1;
+    void* log_block = nullptr;
+    unsigned long long* log_host = nullptr;
+    size_t log_host_words = 0;
     double* epart = nullptr;
     double* energy = nullptr;
     unsigned long long* flips = nullptr;
@@ -180,9 +186,14 @@ struct mbo_plan_s {
     // counts of the last mbo_project: double re-projections, non-finite inputs
     int64_t last_fb = 0, last_bad = 0;  // row-pass counts per workgroup [batch][log_K][workgroups]
 
+    // the band-limited iterations read the caller's field pointer from this
+    // device word (slot_A: its content), so that their graphs outlive a buffer
+    void** slot = nullptr;
+    void* slot_A = nullptr;
+
     // cached iteration graph
     hipGraphExec_t gexec = nullptr;
-    void* g_A = nullptr;
+    const void* g_A = nullptr;  // the field, nullptr where it is read through slot
     int g_K = -1;
     int g_key = -1;
     double g_tol = 0.0;
@@ -210,7 +221,7 @@ struct mbo_plan_s {
     double* pen = nullptr;       // [batch][ceil(npts / 256)]
     double* pen_sum = nullptr;   // [batch]
     hipGraphExec_t vexec = nullptr;  // cached graph of mbo_iterate_volume
-    void* vg_A = nullptr;
+    const void* vg_A = nullptr;  // the field, nullptr where it is read through slot
     int vg_K = -1;
     int vg_key = -1;
 
@@ -297,13 +308,10 @@ void destroy(mbo_plan_t p)
     free_dev(p->taus_dev);
     free_dev(p->foff_dev);
     free_dev(p->counters);
-    free_dev(p->epart);
-    free_dev(p->energy);
-    free_dev(p->flips);
-    free_dev(p->fallbacks);
-    free_dev(p->nonfinite);
-    free_dev(p->delta_bits);
-    free_dev(p->stop_iter);
+    free_dev(p->log_block);
+    if (p->log_host) (void)hipHostFree(p->log_host);
+    p->log_host = nullptr;
+    free_dev(p->slot);
     free_dev(p->vde);
     free_dev(p->vsel);
     free_dev(p->vhist);
@@ -831,37 +839,82 @@ int fast_energy_partials(mbo_plan_t p)
 void drop_logs(mbo_plan_t p)
 {
     drop_graph(p);
-    free_dev(p->epart);
-    free_dev(p->energy);
-    free_dev(p->flips);
-    free_dev(p->fallbacks);
-    free_dev(p->nonfinite);
-    free_dev(p->delta_bits);
-    free_dev(p->stop_iter);
-    free_dev(p->cnt_part);
+    free_dev(p->log_block);
     p->log_K = -1;
 }
 
+size_t log_counters(mbo_plan_t p, int K) { return (size_t)p->batch * (size_t)(K > 0 ? K : 1); }
+
+// Words of the logs of K iterations: four counters per field and iteration,
+// K + 1 energies and one stop mark (an int) per field.
+size_t log_words(mbo_plan_t p, int K)
+{
+    return 4 * log_counters(p, K) + (size_t)p->batch * (size_t)(K + 1) + ((size_t)p->batch + 1) / 2;
+}
+
+// Logs of a call of K iterations: grown when needed, and laid out for K (a
+// captured graph of K iterations finds them at the same addresses).
 mbo_status ensure_logs(mbo_plan_t p, int K)
 {
-    if (K <= p->log_K) return MBO_OK;
-    drop_logs(p);
-    const size_t slots = (size_t)p->batch * (size_t)(K + 1);
-    // room for the partials of either heat pass (the band-limited one when
-    // mbo_iterate runs it, the generic one for the other calls)
-    const int nwg = std::max(energy_partials(p), fast_energy_partials(p));
-    HIP_TRY(p, hipMalloc((void**)&p->epart, slots * (size_t)nwg * sizeof(double)));
-    HIP_TRY(p, hipMalloc((void**)&p->energy, slots * sizeof(double)));
-    const size_t cslots = (size_t)p->batch * (size_t)(K > 0 ? K : 1);
-    HIP_TRY(p, hipMalloc((void**)&p->flips, cslots * sizeof(unsigned long long)));
-    HIP_TRY(p, hipMalloc((void**)&p->fallbacks, cslots * sizeof(unsigned long long)));
-    HIP_TRY(p, hipMalloc((void**)&p->nonfinite, cslots * sizeof(unsigned long long)));
-    HIP_TRY(p, hipMalloc((void**)&p->delta_bits, cslots * sizeof(unsigned long long)));
-    HIP_TRY(p, hipMalloc((void**)&p->stop_iter, (size_t)p->batch * sizeof(int)));
-    if (p->fast)
-        HIP_TRY(p, hipMalloc((void**)&p->cnt_part, cslots * (size_t)fast_row_groups(p) * sizeof(unsigned long long)));
-    p->log_K = K;
+    if (K > p->log_K) {
+        drop_logs(p);
+        const size_t slots = (size_t)p->batch * (size_t)(K + 1);
+        // room for the partials of either heat pass (the band-limited one when
+        // mbo_iterate runs it, the generic one for the other calls)
+        const int nwg = std::max(energy_partials(p), fast_energy_partials(p));
+        const size_t words = log_words(p, K), ep = slots * (size_t)nwg;
+        const size_t cp = p->fast ? log_counters(p, K) * (size_t)fast_row_groups(p) : 0;
+        // one more word per field: the volume-preserving step's counts
+        const size_t hw = words + (size_t)p->batch;
+        if (p->log_host_words < hw) {
+            if (p->log_host) (void)hipHostFree(p->log_host);
+            p->log_host = nullptr;
+            p->log_host_words = 0;
+            HIP_TRY(p, hipHostMalloc((void**)&p->log_host, hw * 8, hipHostMallocDefault));
+            p->log_host_words = hw;
+        }
+        HIP_TRY(p, hipMalloc(&p->log_block, (words + ep + cp) * 8));
+        p->epart = static_cast<double*>(p->log_block) + words;
+        p->cnt_part = cp ? reinterpret_cast<unsigned long long*>(p->epart + ep) : nullptr;
+        p->log_K = K;
+    }
+    const size_t cs = log_counters(p, K);
+    p->flips = static_cast<unsigned long long*>(p->log_block);
+    p->fallbacks = p->flips + cs;
+    p->nonfinite = p->fallbacks + cs;
+    p->delta_bits = p->nonfinite + cs;
+    p->energy = reinterpret_cast<double*>(p->delta_bits + cs);
+    p->stop_iter = reinterpret_cast<int*>(p->energy + (size_t)p->batch * (size_t)(K + 1));
     return MBO_OK;
+}
+
+hipError_t enqueue_init_logs(mbo_plan_t p, int K, hipStream_t st)
+{
+    return launch_init_logs(p->flips, (int64_t)(4 * log_counters(p, K)), p->stop_iter, (int)p->batch, K, st);
+}
+
+// The call's logs to the pinned buffer (and after them vnplus), by a kernel of the
+// call's own graph: a copy command per log cost about 20 us each, 110 to 130 us of
+// every call that ends in one.
+hipError_t enqueue_export_logs(mbo_plan_t p, int K, bool volume, hipStream_t st)
+{
+    return launch_export(p->log_host, p->flips, (int64_t)log_words(p, K),
+                         volume ? reinterpret_cast<const unsigned long long*>(p->vnplus) : nullptr, p->batch, false,
+                         st);
+}
+
+// The field's pointer into its device word, when it is not there already.
+hipError_t set_slot_field(mbo_plan_t p, void* A, hipStream_t st)
+{
+    if (!p->slot) {
+        const hipError_t e = hipMalloc((void**)&p->slot, sizeof(void*));
+        if (e != hipSuccess) return e;
+        p->slot_A = nullptr;
+    }
+    if (p->slot_A == A) return hipSuccess;
+    const hipError_t e = launch_set_slot(p->slot, A, st);
+    if (e == hipSuccess) p->slot_A = A;
+    return e;
 }
 
 // Forward transforms of a real field into Z: rows, then (3-D, with_mid) the
@@ -972,19 +1025,14 @@ hipError_t run_heat_fast(mbo_plan_t p, const FastColArgs& a, hipStream_t st, hip
 // mbo_iterate through the band-limited passes: the row pass of A_0 (forward
 // row FFT, det signs), then per iteration the heat pass over the stored columns
 // and the row pass (inverse row FFT, projection, forward row FFT).
-hipError_t enqueue_iterate_fast(mbo_plan_t p, void* A, int K, double tol, bool want_energy, hipStream_t st)
+hipError_t enqueue_iterate_fast(mbo_plan_t p, int K, double tol, bool want_energy, hipStream_t st)
 {
     const bool track = tol > 0.0;
     const bool fallback = p->prec == MBO_F32_F64FALLBACK;
-    const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
     hipError_t e;
-    if ((e = launch_fill_u64(p->flips, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->fallbacks, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->nonfinite, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->delta_bits, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_i32(p->stop_iter, p->batch, K, st)) != hipSuccess) return e;
+    if ((e = enqueue_init_logs(p, K, st)) != hipSuccess) return e;
     FastRowArgs r0 = fast_row_args(p);
-    r0.Ain = A;
+    r0.slot = p->slot;
     r0.flags = RF_LOAD_REAL | RF_FORWARD | RF_SIGN_INIT;
     if ((e = run_row_fast(p, r0, st)) != hipSuccess) return e;
     for (int s = 1; s <= K; ++s) {
@@ -1000,7 +1048,7 @@ hipError_t enqueue_iterate_fast(mbo_plan_t p, void* A, int K, double tol, bool w
         hipEvent_t he = p->timing ? p->ev[4 * (s - 1) + 3] : nullptr;
         if ((e = run_heat_fast(p, h, st, hs, he)) != hipSuccess) return e;
         FastRowArgs r = fast_row_args(p);
-        r.Aout = A;
+        r.slot = p->slot;
         r.iter = s;
         r.K = K;
         r.delta_bits = p->delta_bits;
@@ -1045,19 +1093,13 @@ hipError_t enqueue_iterate_fast(mbo_plan_t p, void* A, int K, double tol, bool w
     return launch_reduce(ra, st);
 }
 
-// Enqueue the whole of mbo_iterate on stream st (captured into a graph by the caller).
-hipError_t enqueue_iterate(mbo_plan_t p, void* A, int K, double tol, bool want_energy, hipStream_t st)
+// mbo_iterate through the general passes.
+hipError_t enqueue_iterate_general(mbo_plan_t p, void* A, int K, double tol, bool want_energy, hipStream_t st)
 {
-    if (p->fast) return enqueue_iterate_fast(p, A, K, tol, want_energy, st);
     const bool track = tol > 0.0;
     const bool fallback = p->prec == MBO_F32_F64FALLBACK;
-    const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
     hipError_t e;
-    if ((e = launch_fill_u64(p->flips, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->fallbacks, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->nonfinite, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->delta_bits, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_i32(p->stop_iter, p->batch, K, st)) != hipSuccess) return e;
+    if ((e = enqueue_init_logs(p, K, st)) != hipSuccess) return e;
 
     // A_0: forward row FFT (and det signs for the flip count of iteration 1);
     // in 3-D each iteration starts with the middle-axis forward pass itself.
@@ -1114,6 +1156,15 @@ hipError_t enqueue_iterate(mbo_plan_t p, void* A, int K, double tol, bool want_e
     }
     if (want_energy) return enqueue_final_energy(p, K, st);
     return hipSuccess;
+}
+
+// Enqueue the whole of mbo_iterate on stream st (captured into a graph by the
+// caller); the band-limited passes find the field through p->slot.
+hipError_t enqueue_iterate(mbo_plan_t p, void* A, int K, double tol, bool want_energy, hipStream_t st)
+{
+    const hipError_t e = p->fast ? enqueue_iterate_fast(p, K, tol, want_energy, st)
+                                 : enqueue_iterate_general(p, A, K, tol, want_energy, st);
+    return e == hipSuccess ? enqueue_export_logs(p, K, false, st) : e;
 }
 
 // ---- volume-preserving step (Section 7) -----------------------------------
@@ -1230,15 +1281,11 @@ mbo_status ensure_volume_fast(mbo_plan_t p)
 // diffused field; from then on the field holds that volume.
 hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy, hipStream_t st)
 {
-    const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
     hipError_t e;
-    if ((e = launch_fill_u64(p->flips, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->fallbacks, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->nonfinite, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_i32(p->stop_iter, p->batch, K, st)) != hipSuccess) return e;
+    if ((e = enqueue_init_logs(p, K, st)) != hipSuccess) return e;
     const int fb = p->prec == MBO_F32_F64FALLBACK ? RF_FALLBACK : 0;
     FastRowArgs r0 = fast_row_args(p);
-    r0.Ain = A;
+    r0.slot = p->slot;
     r0.flags = RF_LOAD_REAL | RF_FORWARD | RF_SIGN_INIT;
     if ((e = run_row_fast(p, r0, st)) != hipSuccess) return e;
     if (from_a0 && (e = launch_count_pos(p->sgn, p->npts, (int)p->batch, p->vnplus, st)) != hipSuccess)
@@ -1257,7 +1304,7 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
     if (!from_a0 && K > 0) {
         if ((e = heat(p->Z, 0, 1)) != hipSuccess) return e;
         FastRowArgs r1 = fast_row_args(p);
-        r1.Aout = A;
+        r1.slot = p->slot;
         r1.flags = RF_INVERSE | RF_STORE_REAL;
         if ((e = run_row_fast(p, r1, st)) != hipSuccess) return e;
         RowArgs r = row_args(p);
@@ -1285,7 +1332,7 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
         FastRowArgs r = fast_row_args(p);
         r.Z = Zin;
         r.Zout = Zout;
-        r.Aout = A;
+        r.slot = p->slot;
         r.vde = p->vde;
         r.iter = s;
         r.K = K;
@@ -1322,15 +1369,11 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
 
 // Enqueue the whole of mbo_iterate_volume on stream st.  from_a0: the points to
 // select are the points of A_0 with det >= 0 (else vnplus holds them).
-hipError_t enqueue_iterate_volume(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy, hipStream_t st)
+hipError_t enqueue_iterate_volume_general(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy,
+                                          hipStream_t st)
 {
-    if (p->fast && p->d == 2) return enqueue_iterate_volume_fast(p, A, K, from_a0, want_energy, st);
-    const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
     hipError_t e;
-    if ((e = launch_fill_u64(p->flips, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->fallbacks, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->nonfinite, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_i32(p->stop_iter, p->batch, K, st)) != hipSuccess) return e;
+    if ((e = enqueue_init_logs(p, K, st)) != hipSuccess) return e;
     if ((e = enqueue_forward(p, A, RF_SIGN_INIT, false, st)) != hipSuccess) return e;
     if (from_a0 && (e = launch_count_pos(p->sgn, p->npts, (int)p->batch, p->vnplus, st)) != hipSuccess)
         return e;
@@ -1366,6 +1409,13 @@ hipError_t enqueue_iterate_volume(mbo_plan_t p, void* A, int K, bool from_a0, bo
     return hipSuccess;
 }
 
+hipError_t enqueue_iterate_volume(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy, hipStream_t st)
+{
+    const hipError_t e = p->fast && p->d == 2 ? enqueue_iterate_volume_fast(p, A, K, from_a0, want_energy, st)
+                                              : enqueue_iterate_volume_general(p, A, K, from_a0, want_energy, st);
+    return e == hipSuccess ? enqueue_export_logs(p, K, true, st) : e;
+}
+
 // ---- relaxed gradient flows (GD-1, GD-3) -------------------------------------
 
 hipError_t run_row_relax(mbo_plan_t p, const RowArgs& a, hipStream_t st)
@@ -1376,11 +1426,9 @@ hipError_t run_row_relax(mbo_plan_t p, const RowArgs& a, hipStream_t st)
 // K steps of B = (I - dt Delta)^{-1} A, A = B - c N(B) in place on A.
 hipError_t enqueue_relaxed_flow(mbo_plan_t p, void* A, int K, int kind, double c, double dt, hipStream_t st)
 {
-    const int64_t cs = (int64_t)p->batch * (K > 0 ? K : 1);
     hipError_t e;
-    if ((e = launch_fill_u64(p->fallbacks, cs, 0ull, st)) != hipSuccess) return e;
-    if ((e = launch_fill_u64(p->nonfinite, cs, 0ull, st)) != hipSuccess) return e;
-    if (K == 0) return hipSuccess;
+    if ((e = enqueue_init_logs(p, K, st)) != hipSuccess) return e;
+    if (K == 0) return enqueue_export_logs(p, K, false, st);
     if ((e = enqueue_forward(p, A, 0, false, st)) != hipSuccess) return e;
     const int fb = p->prec == MBO_F32_F64FALLBACK ? RF_FALLBACK : 0;
     for (int s = 1; s <= K; ++s) {
@@ -1407,7 +1455,7 @@ hipError_t enqueue_relaxed_flow(mbo_plan_t p, void* A, int K, int kind, double c
         r.flags = RF_INVERSE | RF_RELAX | fb | (s < K ? RF_FORWARD : 0) | (s == K ? RF_STORE_REAL : 0);
         if ((e = run_row_relax(p, r, st)) != hipSuccess) return e;
     }
-    return hipSuccess;
+    return enqueue_export_logs(p, K, false, st);
 }
 
 mbo_status check_relax_args(mbo_plan_t p, int kind, double eps)
@@ -1474,6 +1522,8 @@ mbo_status plan_init(mbo_plan_t p, const int64_t* foff_host)
     HIP_TRY(p, hipMalloc(&p->Z, zbytes));
     HIP_TRY(p, hipMalloc((void**)&p->sgn, (size_t)batch * (size_t)p->npts));
     HIP_TRY(p, hipMalloc((void**)&p->counters, 4 * sizeof(unsigned long long)));
+    const unsigned long long zero[4] = {0, 0, 0, 0};
+    HIP_TRY(p, hipMemcpy(p->counters, zero, sizeof zero, hipMemcpyHostToDevice));
     for (int a = 0; a < p->d; ++a) {
         for (int b = 0; b < a; ++b)
             if (p->N[b] == p->N[a]) p->tw[a] = p->tw[b];
@@ -1508,26 +1558,20 @@ mbo_status plan_init(mbo_plan_t p, const int64_t* foff_host)
     return MBO_OK;
 }
 
-// Copy the iteration logs of plan p back (on stream st, synchronising) and
-// store them for field row map[b] (or b) of the caller's arrays; counts the
+// Wait for the iteration logs of plan p (stream st) and store them for field row
+// map[b] (or b) of the caller's arrays; counts the
 // projections that met NaN/Inf into *bad.  Also evaluates kernel timing.
 mbo_status read_logs(mbo_plan_t p, int K, double tol, hipStream_t st, int* iters_done, double* energy,
                      int64_t* flips, double* delta, int64_t* fallbacks, const std::vector<int>* map,
                      unsigned long long* bad)
 {
     const size_t B = (size_t)p->batch;
-    const size_t cs = B * (size_t)(K > 0 ? K : 1);
-    std::vector<int> stp(B);
-    std::vector<unsigned long long> hf(cs), hfb(cs), hbad(cs), hd(cs);
-    std::vector<double> he(B * (size_t)(K + 1));
-    HIP_TRY(p, hipMemcpyAsync(stp.data(), p->stop_iter, B * sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(p, hipMemcpyAsync(hf.data(), p->flips, cs * 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(p, hipMemcpyAsync(hfb.data(), p->fallbacks, cs * 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(p, hipMemcpyAsync(hbad.data(), p->nonfinite, cs * 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(p, hipMemcpyAsync(hd.data(), p->delta_bits, cs * 8, hipMemcpyDeviceToHost, st));
-    if (energy)
-        HIP_TRY(p, hipMemcpyAsync(he.data(), p->energy, he.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+    const size_t cs = log_counters(p, K);
     HIP_TRY(p, hipStreamSynchronize(st));
+    // the layout of ensure_logs
+    const unsigned long long *hf = p->log_host, *hfb = hf + cs, *hbad = hfb + cs, *hd = hbad + cs;
+    const double* he = reinterpret_cast<const double*>(hd + cs);
+    const int* stp = reinterpret_cast<const int*>(he + B * (size_t)(K + 1));
 
     if (p->timing && K > 0) {
         // average over the iterations every field ran (stopped fields skip kernels)
@@ -1589,6 +1633,7 @@ mbo_status time_iterations(mbo_plan_t p, void* A, int reps, hipEvent_t e0, hipEv
 {
     const int64_t count = p->batch * (int64_t)p->n * p->n * p->npts;
     HIP_TRY(p, launch_fill_uniform(p->pk, A, count, 0x5eedull, p->stream));
+    if (p->fast) HIP_TRY(p, set_slot_field(p, A, p->stream));
     HIP_TRY(p, enqueue_iterate(p, A, 1, 0.0, false, p->stream));  // warm-up
     double best = 0.0;
     for (int run = 0; run < 3; ++run) {
@@ -1768,13 +1813,11 @@ mbo_status energy_into(mbo_plan_t p, const void* A, double* E, const std::vector
     ra.tau = p->tau;
     ra.taus = p->taus_dev;
     ra.stop_iter = nullptr;
-    ra.energy = p->energy;
+    double* h_e = reinterpret_cast<double*>(p->log_host);  // pinned: the kernel writes it
+    ra.energy = h_e;
     HIP_TRY(p, launch_reduce(ra, p->stream));
-    std::vector<double> h_e((size_t)p->batch);
-    HIP_TRY(p, hipMemcpyAsync(h_e.data(), p->energy, (size_t)p->batch * sizeof(double), hipMemcpyDeviceToHost,
-                              p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
-    for (size_t b = 0; b < h_e.size(); ++b) E[map ? (size_t)(*map)[b] : b] = h_e[b];
+    for (size_t b = 0; b < (size_t)p->batch; ++b) E[map ? (size_t)(*map)[b] : b] = h_e[b];
     return MBO_OK;
 }
 
@@ -1950,7 +1993,7 @@ mbo_status step_vjp_fast(mbo_plan_t p, const void* A_prev, void* G, double* dtau
         v.A = p->ws_a;
         v.G = G;
         v.GA = p->ws_g;
-        v.nonfinite = p->counters;
+        v.nonfinite = p->counters + 3;  // not read: the step is asynchronous
         v.fallback = fb != 0;
         v.sigma_fb = p->sigma_fb;
         HIP_TRY(p, launch_vjp(p->pk, p->n, v, (int)p->batch, st));
@@ -2693,6 +2736,7 @@ mbo_status mbo_plan_set_tau(mbo_plan_t p, double tau)
     if (!p) return MBO_ERR_INVALID_ARG;
     if (p->group) return fail(p, MBO_ERR_UNSUPPORTED, "the fields of a batched plan keep their own tau");
     if (!(tau > 0.0) || !std::isfinite(tau)) return fail(p, MBO_ERR_INVALID_ARG, "tau must be finite and > 0");
+    if (tau == p->tau) return MBO_OK;  // tables, kept band and graphs stay (an adjoint sets its tau twice a step)
     HIP_TRY(p, hipSetDevice(p->device));
     HIP_TRY(p, hipStreamSynchronize(p->stream));  // tables may be in use by queued work
     p->tau = tau;
@@ -2797,7 +2841,8 @@ mbo_status mbo_project(mbo_plan_t p, const void* A_in, void* A_out, int8_t* det_
         }
         return MBO_OK;
     }
-    HIP_TRY(p, launch_fill_u64(p->counters, 4, 0ull, p->stream));
+    mbo_status s = ensure_logs(p, 0);
+    if (s != MBO_OK) return s;
     ProjArgs a;
     a.npts = p->npts;
     a.A = A_in;
@@ -2809,8 +2854,9 @@ mbo_status mbo_project(mbo_plan_t p, const void* A_in, void* A_out, int8_t* det_
     a.sigma_fb = p->sigma_fb;
     a.foff = p->foff_dev;
     HIP_TRY(p, launch_project(p->pk, p->n, a, (int)p->batch, p->stream));
-    unsigned long long h[4];
-    HIP_TRY(p, hipMemcpyAsync(h, p->counters, sizeof h, hipMemcpyDeviceToHost, p->stream));
+    // to pinned memory, leaving the counters at zero
+    const unsigned long long* h = p->log_host;
+    HIP_TRY(p, launch_export(p->log_host, p->counters, 2, nullptr, 0, true, p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
     p->last_fb = (int64_t)h[1];
     p->last_bad = (int64_t)h[0];
@@ -2874,7 +2920,8 @@ mbo_status mbo_project_vjp(mbo_plan_t p, const void* A_tilde, const void* G_Q, v
     if (p->group) return fail(p, MBO_ERR_UNSUPPORTED, "not available for a batched plan");
     if (!A_tilde || !G_Q || !G_A) return fail(p, MBO_ERR_INVALID_ARG, "A_tilde / G_Q / G_A is NULL");
     HIP_TRY(p, hipSetDevice(p->device));
-    HIP_TRY(p, launch_fill_u64(p->counters, 4, 0ull, p->stream));
+    mbo_status s = ensure_logs(p, 0);
+    if (s != MBO_OK) return s;
     VjpArgs a;
     a.npts = p->npts;
     a.A = A_tilde;
@@ -2884,8 +2931,8 @@ mbo_status mbo_project_vjp(mbo_plan_t p, const void* A_tilde, const void* G_Q, v
     a.fallback = p->prec == MBO_F32_F64FALLBACK;
     a.sigma_fb = p->sigma_fb;
     HIP_TRY(p, launch_vjp(p->pk, p->n, a, (int)p->batch, p->stream));
-    unsigned long long h[4];
-    HIP_TRY(p, hipMemcpyAsync(h, p->counters, sizeof h, hipMemcpyDeviceToHost, p->stream));
+    const unsigned long long* h = p->log_host;
+    HIP_TRY(p, launch_export(p->log_host, p->counters, 2, nullptr, 0, true, p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
     if (h[0]) return fail(p, MBO_ERR_NONFINITE, "%llu points with NaN/Inf input", h[0]);
     return MBO_OK;
@@ -2948,7 +2995,7 @@ mbo_status mbo_step_vjp(mbo_plan_t p, const void* A_prev, void* G, double* dtau)
     v.A = p->ws_a;
     v.G = G;
     v.GA = p->ws_g;
-    v.nonfinite = p->counters;
+    v.nonfinite = p->counters + 3;  // not read: the step is asynchronous
     v.fallback = p->prec == MBO_F32_F64FALLBACK;
     v.sigma_fb = p->sigma_fb;
     HIP_TRY(p, launch_vjp(p->pk, p->n, v, (int)p->batch, st));
@@ -3004,7 +3051,8 @@ mbo_status mbo_iterate(mbo_plan_t p, void* A, int max_iter, double tol, int* ite
     // the iteration of plan q captured into its own graph (re-captured when the
     // field pointer, K, tol or the logs asked for change)
     auto ensure_graph = [&](mbo_plan_t q) -> mbo_status {
-        if (q->gexec && q->g_A == A && q->g_K == K && q->g_key == key && q->g_tol == tol) return MBO_OK;
+        const void* field = q->fast ? nullptr : A;
+        if (q->gexec && q->g_A == field && q->g_K == K && q->g_key == key && q->g_tol == tol) return MBO_OK;
         drop_graph(q);
         hipGraph_t g = nullptr;
         HIP_TRY(q, hipStreamBeginCapture(q->cap, hipStreamCaptureModeThreadLocal));
@@ -3020,12 +3068,18 @@ mbo_status mbo_iterate(mbo_plan_t p, void* A, int max_iter, double tol, int* ite
             q->gexec = nullptr;
             return fail(q, MBO_ERR_HIP, "hipGraphInstantiate failed: %s", hipGetErrorString(e3));
         }
-        q->g_A = A;
+        q->g_A = field;
         q->g_K = K;
         q->g_key = key;
         q->g_tol = tol;
         return MBO_OK;
     };
+    if (p->group) {
+        for (mbo_plan_t m : p->members)
+            if (m->fast) HIP_TRY(p, set_slot_field(m, A, p->stream));
+    } else if (p->fast) {
+        HIP_TRY(p, set_slot_field(p, A, p->stream));
+    }
     if (use_graphs() && !p->timing) {
         if (!p->group) {
             if ((s = ensure_graph(p)) != MBO_OK) return s;
@@ -3113,12 +3167,10 @@ mbo_status mbo_relaxed_flow(mbo_plan_t p, void* A, int steps, int kind, double e
     } else {
         HIP_TRY(p, enqueue_relaxed_flow(p, A, steps, kind, c, dt, p->stream));
     }
-    const size_t cs = (size_t)p->batch * (size_t)(steps > 0 ? steps : 1);
-    std::vector<unsigned long long> h(cs);
-    HIP_TRY(p, hipMemcpyAsync(h.data(), p->nonfinite, cs * 8, hipMemcpyDeviceToHost, p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
+    const size_t cs = log_counters(p, steps);
     unsigned long long bad = 0;
-    for (unsigned long long v : h) bad += v;
+    for (size_t i = 0; i < cs; ++i) bad += p->log_host[2 * cs + i];
     if (bad) return fail(p, MBO_ERR_NONFINITE, "%llu points met NaN/Inf", bad);
     return MBO_OK;
 }
@@ -3204,8 +3256,7 @@ mbo_status mbo_project_volume(mbo_plan_t p, const void* A_in, void* A_out, const
     if ((s = ensure_logs(p, 1)) != MBO_OK) return s;
     if ((s = ensure_volume(p)) != MBO_OK) return s;
     if ((s = upload_nplus(p, n_plus)) != MBO_OK) return s;
-    HIP_TRY(p, launch_fill_u64(p->nonfinite, p->batch, 0ull, p->stream));
-    HIP_TRY(p, launch_fill_u64(p->fallbacks, p->batch, 0ull, p->stream));
+    HIP_TRY(p, enqueue_init_logs(p, 1, p->stream));
     RowArgs r = row_args(p);
     r.Aout = A_out;
     r.iter = 1;
@@ -3214,11 +3265,11 @@ mbo_status mbo_project_volume(mbo_plan_t p, const void* A_in, void* A_out, const
     r.fallbacks = p->fallbacks;
     r.flags = RF_STORE_REAL;
     HIP_TRY(p, enqueue_volume_step(p, RF_LOAD_REAL, A_in, dE ? dE : p->vde, r, p->stream));
-    std::vector<unsigned long long> h((size_t)p->batch);
-    HIP_TRY(p, hipMemcpyAsync(h.data(), p->nonfinite, h.size() * 8, hipMemcpyDeviceToHost, p->stream));
+    HIP_TRY(p, enqueue_export_logs(p, 1, false, p->stream));
     HIP_TRY(p, hipStreamSynchronize(p->stream));
+    const size_t cs = log_counters(p, 1);
     unsigned long long bad = 0;
-    for (unsigned long long v : h) bad += v;
+    for (size_t i = 0; i < cs; ++i) bad += p->log_host[2 * cs + i];
     if (bad) return fail(p, MBO_ERR_NONFINITE, "%llu points with NaN/Inf input", bad);
     return MBO_OK;
 }
@@ -3240,8 +3291,11 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
     if (p->fast && p->d == 2 && (s = ensure_volume_fast(p)) != MBO_OK) return s;
     if (!from_a0 && (s = upload_nplus(p, n_plus)) != MBO_OK) return s;
     const int key = (want_energy ? 1 : 0) | (from_a0 ? 2 : 0);
+    const bool fast = p->fast && p->d == 2;
+    if (fast) HIP_TRY(p, set_slot_field(p, A, p->stream));
+    const void* field = fast && from_a0 ? nullptr : A;
     if (use_graphs()) {
-        if (!(p->vexec && p->vg_A == A && p->vg_K == K && p->vg_key == key)) {
+        if (!(p->vexec && p->vg_A == field && p->vg_K == K && p->vg_key == key)) {
             if (p->vexec) (void)hipGraphExecDestroy(p->vexec);
             p->vexec = nullptr;
             hipGraph_t g = nullptr;
@@ -3259,7 +3313,7 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
                 p->vexec = nullptr;
                 return fail(p, MBO_ERR_HIP, "hipGraphInstantiate failed: %s", hipGetErrorString(e3));
             }
-            p->vg_A = A;
+            p->vg_A = field;
             p->vg_K = K;
             p->vg_key = key;
         }
@@ -3267,14 +3321,11 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
     } else {
         HIP_TRY(p, enqueue_iterate_volume(p, A, K, from_a0, want_energy, p->stream));
     }
-    std::vector<long long> used((size_t)p->batch);
-    HIP_TRY(p, hipMemcpyAsync(used.data(), p->vnplus, used.size() * sizeof(long long), hipMemcpyDeviceToHost,
-                              p->stream));
     unsigned long long bad = 0;
     if ((s = read_logs(p, K, 0.0, p->stream, nullptr, energy, flips, nullptr, fallbacks, nullptr, &bad)) != MBO_OK)
         return s;
     if (n_plus_used)
-        for (int64_t b = 0; b < p->batch; ++b) n_plus_used[b] = (int64_t)used[(size_t)b];
+        for (int64_t b = 0; b < p->batch; ++b) n_plus_used[b] = (int64_t)p->log_host[log_words(p, K) + (size_t)b];
     if (bad) return fail(p, MBO_ERR_NONFINITE, "%llu projections met NaN/Inf input", bad);
     return MBO_OK;
 }

@@ -313,7 +313,9 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     if (stop < a.iter) return;
 
     // ---- phase 2: PPT points per projection thread
-    T* Aout = reinterpret_cast<T*>(a.Aout) + field_base(a.foff, b, NN * npts);
+    // the field's pointer from its device word where there is one (a captured
+    // iteration then serves any field buffer)
+    T* Aout = reinterpret_cast<T*>(a.slot ? *a.slot : a.Aout) + field_base(a.foff, b, NN * npts);
     unsigned long long nflip = 0, nfb = 0, nbad = 0;
     double dmax = 0.0;
     const bool fallback = (flags & RF_FALLBACK) != 0;
@@ -356,7 +358,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
 
     if (flags & RF_LOAD_REAL) {
         // forward transform of a real field: the points' entries from A
-        const T* A = reinterpret_cast<const T*>(a.Ain) + field_base(a.foff, b, NN * npts);
+        const T* A = (a.slot ? Aout : reinterpret_cast<const T*>(a.Ain) + field_base(a.foff, b, NN * npts));
 #pragma unroll 1
         for (int pp = 0; pp < PPT; ++pp) {
             int64_t xp;
@@ -892,7 +894,7 @@ __global__ void __launch_bounds__((VolumeFixShape<T, n>::NT), (VolumeFixShape<T,
     const C* tw = reinterpret_cast<const C*>(a.tw);
     const C* Zi = reinterpret_cast<const C*>(a.Z) + (size_t)b * PL * a.rows * W;
     C* Zo = reinterpret_cast<C*>(a.Zout) + (size_t)b * PL * a.rows * W;
-    T* Aout = reinterpret_cast<T*>(a.Aout) + field_base(a.foff, b, NN * a.npts);
+    T* Aout = reinterpret_cast<T*>(a.slot ? *a.slot : a.Aout) + field_base(a.foff, b, NN * a.npts);
     const int lane = tid & 15, g = tid >> 4;
     const bool fallback = (a.flags & RF_FALLBACK) != 0;
     for (int j0 = 0; j0 < m; j0 += NB) {

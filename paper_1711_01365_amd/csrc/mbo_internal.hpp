@@ -188,6 +188,15 @@ hipError_t launch_fill_u64(unsigned long long* p, int64_t count, unsigned long l
                            hipStream_t st);
 hipError_t launch_fill_i32(int* p, int64_t count, int v, hipStream_t st);
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st);
+// count words of p to zero and stop[0..batch) to K: the logs of a call, in one
+// launch
+hipError_t launch_init_logs(unsigned long long* p, int64_t count, int* stop, int batch, int K, hipStream_t st);
+// dst[0..n) = src[0..n), then dst[n..n + n2) = src2[0..n2) (nullable); dst may be
+// pinned host memory.  clear: src is left zero.
+hipError_t launch_export(unsigned long long* dst, unsigned long long* src, int64_t n, const unsigned long long* src2,
+                         int64_t n2, bool clear, hipStream_t st);
+// *slot = p, for kernels that read a field's pointer from device memory
+hipError_t launch_set_slot(void** slot, void* p, hipStream_t st);
 hipError_t launch_vjp(int prec, int n, const VjpArgs& a, int batch, hipStream_t st);
 // count values uniform in [-1, 1) from a counter-based hash of (seed, index)
 hipError_t launch_fill_uniform(int prec, void* p, int64_t count, uint64_t seed, hipStream_t st);
@@ -386,6 +395,7 @@ struct FastRowArgs {
     int plane_major;         // 3-D: spectra stored plane by plane for the plane pass
     const void* Ain;         // RF_LOAD_REAL: real field [batch][n*n][npts]
     void* Aout;              // RF_STORE_REAL / RF_TRACK: real field
+    void* const* slot;       // nullable: device word holding the field's pointer, in place of Ain and Aout
     int8_t* sgn;             // det signs [batch][npts]
     unsigned long long* delta_bits;  // [batch][K] max |A_s - A_{s-1}| (double bits)
     int* stop_iter;          // [batch]

@@ -179,6 +179,27 @@ __global__ void fill_i32(int* p, int64_t count, int v)
     if (i < count) p[i] = v;
 }
 
+__global__ void init_logs(unsigned long long* p, int64_t count, int* stop, int batch, int K)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) p[i] = 0ull;
+    if (i < batch) stop[i] = K;
+}
+
+__global__ void export_words(unsigned long long* dst, unsigned long long* src, int64_t n,
+                             const unsigned long long* src2, int64_t n2, int clear)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) {
+        dst[i] = src[i];
+        if (clear) src[i] = 0ull;
+    } else if (i < n + n2) {
+        dst[i] = src2[i - n];
+    }
+}
+
+__global__ void set_slot(void** slot, void* p) { *slot = p; }
+
 // E(A_s) = (1/tau) (n - (1/npts) sum_wg partial), the partials being
 // sum_m symbol(m)/npts |Z(m)|^2 over each workgroup's modes.
 // One workgroup per (field, iterate) slot; the partials are summed in a fixed
@@ -312,6 +333,29 @@ hipError_t launch_fill_u64(unsigned long long* p, int64_t count, unsigned long l
 {
     if (count <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_u64, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, p, count, v);
+    return hipGetLastError();
+}
+
+hipError_t launch_init_logs(unsigned long long* p, int64_t count, int* stop, int batch, int K, hipStream_t st)
+{
+    const int64_t n = count > batch ? count : batch;
+    hipLaunchKernelGGL(init_logs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, count, stop, batch, K);
+    return hipGetLastError();
+}
+
+hipError_t launch_export(unsigned long long* dst, unsigned long long* src, int64_t n, const unsigned long long* src2,
+                         int64_t n2, bool clear, hipStream_t st)
+{
+    if (!src2) n2 = 0;
+    if (n + n2 <= 0) return hipSuccess;
+    hipLaunchKernelGGL(export_words, dim3((unsigned)((n + n2 + 255) / 256)), dim3(256), 0, st, dst, src, n, src2, n2,
+                       clear ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_set_slot(void** slot, void* p, hipStream_t st)
+{
+    hipLaunchKernelGGL(set_slot, dim3(1), dim3(1), 0, st, slot, p);
     return hipGetLastError();
 }
 
