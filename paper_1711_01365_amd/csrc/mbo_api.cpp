@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <array>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -2262,9 +2263,17 @@ struct mbo_surface_s {
     void* tiles = nullptr;
     int* binmap = nullptr;
     int tile_edge = 0;
+    // separable spreading (sep.t1 set: used in place of the cell kernels and their
+    // tiles), its tables in one allocation; interpolation groups by stencil start
+    SurfSepArgs sep = {};
+    void* sep_block = nullptr;
+    SurfGroup* groups = nullptr;
+    int ngroups = 0;
     void* tmp = nullptr;        // [n*n][m]
     int8_t* sgn = nullptr;      // [m]
     unsigned long long* counters = nullptr;
+    unsigned long long* flips = nullptr;  // [flips_K] flips of each step (lazy)
+    int flips_K = 0;
     // volume-preserving step: integer volume weights (host and device), their
     // total, Delta E, the selection state, digit histogram and tie chunk sums
     std::vector<int64_t> Wh;
@@ -2305,6 +2314,8 @@ void surface_free(mbo_surface_t s)
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     free_dev(s->nodes);
     free_dev(s->nwts);
+    free_dev(s->sep_block);
+    free_dev(s->groups);
     free_dev(s->tiles);
     free_dev(s->binmap);
     free_dev(s->Wd);
@@ -2322,6 +2333,7 @@ void surface_free(mbo_surface_t s)
     free_dev(s->tmp);
     free_dev(s->sgn);
     free_dev(s->counters);
+    free_dev(s->flips);
     if (s->grid) destroy(s->grid);
     delete s;
 }
@@ -2396,6 +2408,32 @@ mbo_status build_bins_t(mbo_surface_t s, const std::vector<double>& pts, const s
     start.push_back(m);
     B.nbins = (int)(start.size() - 1);
     mbo_status st;
+    // groups of at most 64 targets with one stencil start, unless a stencil wraps
+    if (&B == &s->interp) {
+        std::vector<SurfGroup> gr;
+        bool inside = true;
+        for (int64_t i = 0; i < m && inside;) {
+            const int64_t id = sub[(size_t)key[(size_t)i].second], row = s->Ng + 64;
+            int64_t e = i + 1;
+            while (e < m && e - i < 64 && key[(size_t)e].first == key[(size_t)i].first &&
+                   sub[(size_t)key[(size_t)e].second] == id)
+                ++e;
+            SurfGroup g;
+            g.first = i;
+            g.count = (int)(e - i);
+            g.i0 = (int)(id / (row * row)) - 32;
+            g.j0 = (int)((id / row) % row) - 32;
+            g.k0 = (int)(id % row) - 32;
+            for (const int c : {g.i0, g.j0, g.k0}) inside = inside && c >= 0 && c + s->w <= s->Ng;
+            gr.push_back(g);
+            i = e;
+        }
+        if (inside && gr.size() < (size_t)1 << 30) {
+            SHIP(s, hipMalloc((void**)&s->groups, gr.size() * sizeof(SurfGroup)));
+            SHIP(s, hipMemcpy(s->groups, gr.data(), gr.size() * sizeof(SurfGroup), hipMemcpyHostToDevice));
+            s->ngroups = (int)gr.size();
+        }
+    }
     if ((st = upload_as(s, &B.pos, pos)) != MBO_OK) return st;
     if (wts && (st = upload_as(s, &B.wts, w)) != MBO_OK) return st;
     SHIP(s, hipMalloc((void**)&B.perm, (size_t)m * 8 + 8));
@@ -2486,6 +2524,151 @@ SurfArgs surf_args(mbo_surface_t s, const mbo_surface_s::Bins& B)
 }
 
 // Device state of the volume-preserving step, allocated on first use.
+hipError_t grow_flips(mbo_surface_t s, int K)
+{
+    if (s->flips_K >= K) return hipSuccess;
+    free_dev(s->flips);
+    s->flips_K = 0;
+    const hipError_t e = hipMalloc((void**)&s->flips, (size_t)K * 8);
+    if (e == hipSuccess) s->flips_K = K;
+    return e;
+}
+
+// Tables and workspace of the separable spreading (launch_surface_sep) for the
+// cells of lattice corners corner[c] = dx (i, j, k), in canonical order.  Leaves
+// s->sep.t1 null, and the cell kernels in use, when the lattice's lines do not fit
+// in LDS or its two intermediate fields (zeros outside the band included) would be
+// more than 512 MiB and more than eight times the field: thin bands of wide
+// lattices.  Their traffic is what bounds the passes, and the cell kernels' work
+// does not depend on the lattice.
+mbo_status build_sep(mbo_surface_t s, const std::vector<std::array<double, 3>>& corners, const double* nx,
+                     const double* nw)
+{
+    const int p = s->p, Ng = s->Ng, w = s->w;
+    const int64_t nc = s->cells;
+    const double dx = s->dx;
+    std::vector<int> lat((size_t)(3 * nc));
+    int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {INT_MIN, INT_MIN, INT_MIN};
+    for (int64_t c = 0; c < nc; ++c)
+        for (int d = 0; d < 3; ++d) {
+            const int v = (int)std::llround(corners[(size_t)c][(size_t)d] / dx);
+            lat[(size_t)(3 * c + d)] = v;
+            lo[d] = std::min(lo[d], v);
+            hi[d] = std::max(hi[d], v);
+        }
+    SurfSepArgs a = {};
+    a.m = s->m;
+    a.nn = s->n * s->n;
+    a.p = p;
+    a.Ng = Ng;
+    for (int d = 0; d < 3; ++d) a.len[d] = (hi[d] - lo[d] + 1) * p;
+    std::vector<int64_t> col_start;
+    std::vector<int> col_j, cell_k((size_t)nc), slice((size_t)(a.len[0] / p) + 1, 0);
+    for (int64_t c = 0; c < nc; ++c) {
+        const int* l = &lat[(size_t)(3 * c)];
+        if (c == 0 || l[0] != l[-3] || l[1] != l[-2]) {
+            col_start.push_back(c);
+            col_j.push_back(l[1] - lo[1]);
+            slice[(size_t)(l[0] - lo[0]) + 1] = (int)col_start.size();
+        }
+        cell_k[(size_t)c] = l[2] - lo[2];
+    }
+    a.ncols = (int)col_start.size();
+    col_start.push_back(nc);
+    for (size_t i = 1; i < slice.size(); ++i) slice[i] = std::max(slice[i], slice[i - 1]);  // empty slices
+    const size_t lds = s->grid->lds_max;
+    a.zt = sep_tile(a.len[0], a.len[1], s->esz, lds);
+    if (!a.zt || sep_z_lds(p, a.len[2], Ng, s->esz) > lds) return MBO_OK;
+    const size_t t1 = (size_t)a.nn * a.ncols * p * p * Ng * s->esz, t2 = (size_t)a.nn * a.len[0] * Ng * Ng * s->esz;
+    if (t1 + t2 > std::max((size_t)512 << 20, (size_t)8 * a.nn * (size_t)s->m * s->esz)) return MBO_OK;
+
+    // runs and weights per axis: node t = i p + a sits at u grid steps and touches
+    // the w points from ceil(u - w / 2) on, each by its weight factor times psi
+    std::vector<SepRun> run((size_t)(3 * Ng));
+    std::vector<double> wt[3];
+    for (int d = 0; d < 3; ++d) {
+        std::vector<std::vector<std::pair<int, double>>> at((size_t)Ng);
+        for (int t = 0; t < a.len[d]; ++t) {
+            const double u = (dx * (double)(lo[d] + t / p) + dx * nx[t % p] - s->y0) / s->h;
+            if (!(u >= 1.0 && u < (double)(Ng - 1)))
+                return sfail(s, MBO_ERR_INVALID_ARG, "lattice node %d of axis %d lies outside the grid", t, d);
+            const int i0 = (int)std::ceil(u - 0.5 * w);
+            for (int k = 0; k < w; ++k) {
+                const double r = ((double)(i0 + k) - u) / (0.5 * w), q = 1.0 - r * r;
+                const double v = q > 0.0 ? std::exp(s->beta * (std::sqrt(q) - 1.0)) : 0.0;
+                at[(size_t)(((i0 + k) % Ng + Ng) % Ng)].push_back({t, dx * nw[t % p] * v});
+            }
+        }
+        // runs, then the table, x and y with a grid point's weights side by side
+        constexpr int pad = SURF_SEP_PAD;
+        int most = pad;
+        for (int g = 0; g < Ng; ++g) {
+            const auto& v = at[(size_t)g];
+            SepRun r = {0, 0, 0, 0};
+            for (size_t k = 0; k < v.size(); ++k) {
+                if (k == 0) r.n0 = v[k].first;
+                if (r.len1 == 0 && v[k].first == r.n0 + r.len0) ++r.len0;
+                else if (r.len1 == 0) { r.n1 = v[k].first; r.len1 = 1; }
+                else if (v[k].first == r.n1 + r.len1) ++r.len1;
+                else return MBO_OK;  // three runs: a box no wider than a stencil
+            }
+            run[(size_t)(d * Ng + g)] = r;
+            most = std::max(most, (r.len0 + pad - 1) / pad * pad + (r.len1 + pad - 1) / pad * pad);
+        }
+        a.wlen[d] = most;
+        wt[d].assign((size_t)most * (size_t)Ng, 0.0);
+        for (int g = 0; g < Ng; ++g) {
+            const SepRun& r = run[(size_t)(d * Ng + g)];
+            const auto& v = at[(size_t)g];
+            for (size_t k = 0; k < v.size(); ++k) {
+                const int o = (int)k < r.len0 ? (int)k : (r.len0 + pad - 1) / pad * pad + (int)k - r.len0;
+                wt[d][d == 2 ? (size_t)o * Ng + (size_t)g : (size_t)g * most + (size_t)o] = v[k].second;
+            }
+        }
+    }
+    // one allocation, each part on a 256-byte boundary
+    auto up = [](size_t b) { return (b + 255) / 256 * 256; };
+    size_t off = 0, o_wt[3];
+    const size_t o_t1 = off;
+    off += up(t1);
+    const size_t o_t2 = off;
+    off += up(t2);
+    const size_t o_run = off;
+    off += up(run.size() * sizeof(SepRun));
+    const size_t o_cs = off;
+    off += up(col_start.size() * 8);
+    const size_t o_cj = off;
+    off += up(col_j.size() * 4);
+    const size_t o_sl = off;
+    off += up(slice.size() * 4);
+    const size_t o_ck = off;
+    off += up(cell_k.size() * 4);
+    for (int d = 0; d < 3; ++d) {
+        o_wt[d] = off;
+        off += up(wt[d].size() * s->esz);
+    }
+    SHIP(s, hipMalloc(&s->sep_block, off));
+    char* base = static_cast<char*>(s->sep_block);
+    SHIP(s, hipMemcpy(base + o_run, run.data(), run.size() * sizeof(SepRun), hipMemcpyHostToDevice));
+    SHIP(s, hipMemcpy(base + o_cs, col_start.data(), col_start.size() * 8, hipMemcpyHostToDevice));
+    SHIP(s, hipMemcpy(base + o_cj, col_j.data(), col_j.size() * 4, hipMemcpyHostToDevice));
+    SHIP(s, hipMemcpy(base + o_sl, slice.data(), slice.size() * 4, hipMemcpyHostToDevice));
+    SHIP(s, hipMemcpy(base + o_ck, cell_k.data(), cell_k.size() * 4, hipMemcpyHostToDevice));
+    for (int d = 0; d < 3; ++d) {
+        if (upload(s->grid, base + o_wt[d], wt[d]) != MBO_OK) return sfail(s, MBO_ERR_HIP, "%s", s->grid->err.c_str());
+        a.w[d] = base + o_wt[d];
+        a.run[d] = reinterpret_cast<const SepRun*>(base + o_run) + d * Ng;
+    }
+    a.col_start = reinterpret_cast<const int64_t*>(base + o_cs);
+    a.col_j = reinterpret_cast<const int*>(base + o_cj);
+    a.slice = reinterpret_cast<const int*>(base + o_sl);
+    a.cell_k = reinterpret_cast<const int*>(base + o_ck);
+    a.t1 = base + o_t1;
+    a.t2 = base + o_t2;
+    s->sep = a;
+    return MBO_OK;
+}
+
 mbo_status ensure_surface_volume(mbo_surface_t s)
 {
     if (s->wsel) return MBO_OK;
@@ -2532,7 +2715,12 @@ hipError_t enqueue_surface_diffuse(mbo_surface_t s, const void* in, void* out, h
     a.pl1 = PL;
     a.tiles = s->tiles;
     a.binmap = s->binmap;
-    if (cells) {
+    if (s->sep.t1) {
+        SurfSepArgs sa = s->sep;
+        sa.A = in;
+        sa.Z = g->Z;
+        if ((e = launch_surface_sep(s->pk, sa, st)) != hipSuccess) return e;
+    } else if (cells) {
         a.p = s->p;
         a.U = s->U;
         a.TE = SURF_BIN + s->U;
@@ -2544,7 +2732,7 @@ hipError_t enqueue_surface_diffuse(mbo_surface_t s, const void* in, void* out, h
     } else if ((e = launch_surface_spread(s->pk, a, st)) != hipSuccess) {
         return e;
     }
-    if ((e = launch_surface_gather(s->pk, a, s->tile_edge, st)) != hipSuccess) return e;
+    if (!s->sep.t1 && (e = launch_surface_gather(s->pk, a, s->tile_edge, st)) != hipSuccess) return e;
     RowArgs r = row_args(g);
     r.flags = RF_FORWARD;
     if ((e = run_row_relax(g, r, st)) != hipSuccess) return e;
@@ -2559,8 +2747,8 @@ hipError_t enqueue_surface_diffuse(mbo_surface_t s, const void* in, void* out, h
     ia.out = out;
     ia.pl0 = 0;
     ia.pl1 = PL;
-    if ((e = launch_surface_interp(s->pk, ia, st)) != hipSuccess) return e;
-    return hipSuccess;
+    return s->groups ? launch_surface_interp_groups(s->pk, ia, s->groups, s->ngroups, st)
+                     : launch_surface_interp(s->pk, ia, st);
 }
 
 }  // namespace
@@ -2844,6 +3032,7 @@ mbo_status mbo_project(mbo_plan_t p, const void* A_in, void* A_out, int8_t* det_
     mbo_status s = ensure_logs(p, 0);
     if (s != MBO_OK) return s;
     ProjArgs a;
+    std::memset(&a, 0, sizeof a);
     a.npts = p->npts;
     a.A = A_in;
     a.Q = A_out;
@@ -3512,7 +3701,9 @@ mbo_status surface_create(mbo_surface_t* out, int kind, double radius, double dx
     }
     (void)launch_row_relax(g->pk, n, ilog2(Ng), row_args(g), g->row_grid, g->row_block, g->lds_max, nullptr, true);
     (void)hipGetLastError();
-    // spreading: whole cells when the cell kernel's LDS (tile plus per-wave
+    // spreading: by one pass per axis of the lattice where that serves the band ...
+    if ((st = build_sep(s, corners, nx, nw)) != MBO_OK) return bail(st);
+    // ... else whole cells when the cell kernel's LDS (tile plus per-wave
     // scratch) fits with at least one wave, else sample by sample
     s->U = s->w + (int)std::ceil(dx * (nx[p - 1] - nx[0]) / s->h * (1.0 + 1e-4) + 1e-4);
     // the line-owner variant (no LDS atomics) when its tile fits in the
@@ -3530,7 +3721,9 @@ mbo_status surface_create(mbo_surface_t* out, int kind, double radius, double dx
             s->cell_chunk = (int)std::min<size_t>(ch, 64);
         }
     }
-    if (s->cell_waves || s->cell_lines) {
+    if (s->sep.t1) {
+        // no cell lists, tiles or bins
+    } else if (s->cell_waves || s->cell_lines) {
         std::vector<double> cflat((size_t)(3 * s->cells)), nd((size_t)p), nwv((size_t)p);
         for (int64_t c = 0; c < s->cells; ++c)
             for (int a = 0; a < 3; ++a) cflat[(size_t)(a * s->cells + c)] = corners[(size_t)c][(size_t)a];
@@ -3546,7 +3739,7 @@ mbo_status surface_create(mbo_surface_t* out, int kind, double radius, double dx
         return bail(st);
     }
     if ((st = build_bins(s, s->xc, nullptr, s->interp)) != MBO_OK) return bail(st);
-    {
+    if (!s->sep.t1) {
         // spreading tiles and the map from bin to listed index (the gather's lookup)
         const bool cells = s->cell_waves || s->cell_lines;
         const mbo_surface_s::Bins& sb = cells ? s->cellbins : s->spread;
@@ -3713,8 +3906,11 @@ mbo_status mbo_surface_iterate(mbo_surface_t s, void* A, int K, int64_t* flips)
     if (!A) return sfail(s, MBO_ERR_INVALID_ARG, "A is NULL");
     if (K < 0) return sfail(s, MBO_ERR_INVALID_ARG, "K < 0");
     SHIP(s, hipSetDevice(s->grid->device));
-    std::vector<int8_t> prev, cur;
+    unsigned long long* fl = nullptr;  // flips of each step, counted by the projection
     if (flips && K > 0) {
+        SHIP(s, grow_flips(s, K));
+        fl = s->flips;
+        SHIP(s, launch_fill_u64(fl, K, 0ull, s->stream));
         ProjArgs a0;
         std::memset(&a0, 0, sizeof a0);
         a0.npts = s->m;
@@ -3724,9 +3920,6 @@ mbo_status mbo_surface_iterate(mbo_surface_t s, void* A, int K, int64_t* flips)
         a0.nonfinite = s->counters;
         a0.fallbacks = s->counters + 1;
         SHIP(s, launch_project(s->pk, s->n, a0, 1, s->stream));  // det signs of A_0 (projection discarded)
-        prev.resize((size_t)s->m);
-        SHIP(s, hipMemcpyAsync(prev.data(), s->sgn, (size_t)s->m, hipMemcpyDeviceToHost, s->stream));
-        SHIP(s, hipStreamSynchronize(s->stream));
     }
     SHIP(s, launch_fill_u64(s->counters, 4, 0ull, s->stream));
     for (int it = 0; it < K; ++it) {
@@ -3737,21 +3930,14 @@ mbo_status mbo_surface_iterate(mbo_surface_t s, void* A, int K, int64_t* flips)
         a.A = s->tmp;
         a.Q = A;
         a.dsign = flips ? s->sgn : nullptr;
+        a.flips = fl ? fl + it : nullptr;
         a.nonfinite = s->counters;
         a.fallbacks = s->counters + 1;
         a.fallback = s->prec == MBO_F32_F64FALLBACK;
         a.sigma_fb = 1e-3;
         SHIP(s, launch_project(s->pk, s->n, a, 1, s->stream));
-        if (flips) {
-            cur.resize((size_t)s->m);
-            SHIP(s, hipMemcpyAsync(cur.data(), s->sgn, (size_t)s->m, hipMemcpyDeviceToHost, s->stream));
-            SHIP(s, hipStreamSynchronize(s->stream));
-            int64_t f = 0;
-            for (int64_t i = 0; i < s->m; ++i) f += cur[(size_t)i] != prev[(size_t)i];
-            flips[it] = f;
-            prev.swap(cur);
-        }
     }
+    if (fl) SHIP(s, hipMemcpyAsync(flips, fl, (size_t)K * 8, hipMemcpyDeviceToHost, s->stream));
     unsigned long long h[4];
     SHIP(s, hipMemcpyAsync(h, s->counters, sizeof h, hipMemcpyDeviceToHost, s->stream));
     SHIP(s, hipStreamSynchronize(s->stream));

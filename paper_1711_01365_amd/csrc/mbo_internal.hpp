@@ -147,6 +147,7 @@ struct ProjArgs {
     int fallback;
     double sigma_fb;
     const int64_t* foff;     // nullable: element offset of field b in A and Q
+    unsigned long long* flips;  // nullable: += points whose sign differs from the one in dsign
 };
 
 // Vector-Jacobian product of the projection, one point per thread.
@@ -283,6 +284,46 @@ struct SurfArgs {
     void* tiles;             // spreading: [bins][PL][TE^3] complex, each workgroup's tile
     const int* binmap;       // [(Ng / SURF_BIN)^3] listed index of each bin, -1 when empty
 };
+// Spreading of all band cells by one pass per axis (mbo_surfsep.hip).  The lattice
+// nodes along axis d are p nodes in each of the len[d] / p lattice cells that the
+// band spans; columns are the cells of equal (i, j), in canonical order.
+// The nodes that a grid point sees along an axis: n0 .. n0 + len0 - 1, and a second
+// run where stencils wrap around the periodic box.
+struct SepRun {
+    int n0, len0, n1, len1;
+};
+constexpr int SURF_SEP_PAD = 8;  // weights of a run are padded with zeros to a multiple of this
+struct SurfSepArgs {
+    int64_t m;               // samples
+    int nn, p, Ng;           // entries, nodes per cell and axis, grid points per axis
+    int ncols, zt;           // columns; z points per workgroup of the y and x passes
+    int len[3];              // lattice nodes per axis
+    const int64_t* col_start;  // [ncols + 1] first cell of each column
+    const int* col_j;        // [ncols] lattice cell j of each column
+    const int* slice;        // [len[0] / p + 1] first column of each lattice cell i
+    const int* cell_k;       // [cells] lattice cell k of each cell
+    const SepRun* run[3];    // [Ng] node runs of each grid point, per axis
+    // their weights (plan precision), the second run's after the padded first's:
+    // x and y [Ng][wlen], z [wlen][Ng]
+    const void* w[3];
+    int wlen[3];
+    const void* A;           // field [n*n][m]
+    void* t1;                // [n*n][ncols][p^2][Ng]
+    void* t2;                // [n*n][len[0]][Ng][Ng]
+    void* Z;                 // grid [PL][Ng^3] complex
+};
+hipError_t launch_surface_sep(int prec, const SurfSepArgs& a, hipStream_t st);
+int sep_tile(int len_x, int len_y, size_t esz, size_t lds_max);  // 0: the lines do not fit
+size_t sep_z_lds(int p, int len_z, int Ng, size_t esz);
+
+// Interpolation targets first .. first + count - 1 (sorted order, at most 64) whose
+// stencils start at grid point (i0, j0, k0) and do not wrap.
+struct SurfGroup {
+    int64_t first;
+    int count, i0, j0, k0;
+};
+hipError_t launch_surface_interp_groups(int prec, const SurfArgs& a, const SurfGroup* groups, int ngroups,
+                                        hipStream_t st);
 hipError_t launch_surface_spread(int prec, const SurfArgs& a, hipStream_t st);
 // waves = 0: the line-owner variant without atomics (p <= 4, TE <= 22), else
 // the cell-per-wave variant with that many waves per workgroup

@@ -16,7 +16,7 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjArgs a)
     const int b = blockIdx.y;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     __shared__ unsigned long long red_u[64];
-    unsigned long long bad = 0, fb = 0;
+    unsigned long long bad = 0, fb = 0, fl = 0;
     if (p < a.npts) {
         const T* A = reinterpret_cast<const T*>(a.A) + field_base(a.foff, b, NN * a.npts);
         T* Q = reinterpret_cast<T*>(a.Q) + field_base(a.foff, b, NN * a.npts);
@@ -28,7 +28,15 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjArgs a)
         fb = project_point_fb<T, n>(av, qv, ds, a.fallback != 0, a.sigma_fb) ? 1ull : 0ull;
 #pragma unroll
         for (int k = 0; k < NN; ++k) Q[(int64_t)k * a.npts + p] = qv[k];
-        if (a.dsign) a.dsign[(size_t)b * a.npts + p] = (int8_t)ds;
+        if (a.dsign) {
+            int8_t* d = a.dsign + (size_t)b * a.npts + p;
+            if (a.flips) fl = *d != (int8_t)ds ? 1ull : 0ull;
+            *d = (int8_t)ds;
+        }
+    }
+    if (a.flips) {  // uniform
+        fl = block_reduce<OpSum>(fl, red_u);
+        if (threadIdx.x == 0 && fl) atomicAdd(a.flips, fl);
     }
     bad = block_reduce<OpSum>(bad, red_u);
     if (threadIdx.x == 0 && bad) atomicAdd(a.nonfinite, bad);
