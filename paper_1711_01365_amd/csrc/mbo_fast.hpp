@@ -20,8 +20,8 @@
 //              planes load their kept modes straight into the FFT register
 //              layout (lane t holds x[t + e L/8]), inverse-FFT (inside one wave
 //              for L <= 512, with workgroup exchanges and in rounds of lines
-//              beyond) and leave the lines in LDS; 512 threads, one to four
-//              points each, project (Lemma 1.1) with the det-sign,
+//              beyond) and leave the lines in LDS; 512 threads or more, one to
+//              four points each, project (Lemma 1.1) with the det-sign,
 //              fallback, non-finite and change diagnostics; the line groups
 //              forward-FFT and store the kept modes.  Float plans with n = 3
 //              run the Newton polar iteration on every point that is certainly
@@ -113,7 +113,7 @@ __device__ __forceinline__ void newton3_run(Newton3& s, float* q, int& dsign)
 // ---------------------------------------------------------------------------
 
 // Shape of a row-pass workgroup: 512 points (512/L rows) for L <= 512, one row
-// of L points otherwise; 512 projection threads (PPT points each); the line
+// of L points otherwise; NP projection threads (PPT points each); the line
 // groups of L/8 threads run in ROUNDS rounds of G lines over NT threads.
 template <typename T, int n, int LOG2L>
 struct RowFastShape {
@@ -123,7 +123,6 @@ struct RowFastShape {
     static constexpr int PL = (NN + 1) / 2;
     static constexpr int RPW = L >= 512 ? 1 : 512 / L;
     static constexpr int P = RPW * L;
-    static constexpr int PPT = P / 512;
     static constexpr int LINES = RPW * PL;
     static constexpr bool WAVE_LINE = LOG2L <= 9;
     static constexpr bool HELPER = sizeof(T) == 4 && n == 3;
@@ -138,6 +137,14 @@ struct RowFastShape {
     static constexpr int G = NT / Tn;  // lines per round
     static constexpr int ROUNDS = (LINES + G - 1) / G;
     static constexpr int THREADS = NT;
+    // projection threads: 512, or every thread of a long row's workgroup where
+    // that leaves each fewer points (1024 points over 1024 threads at n = 4, 2048
+    // over 768 at n = 3); where it does not (1024 over 640) the waves beyond the
+    // 512 threads stay free for the queued points.  Four iterations of
+    // 2048 x 2048 3 x 3 fields take 1129 us with 768 projecting threads, 1152 with
+    // 512; ten of twelve fields of up to 1024 x 1024, n = 2..4, 4314 us and 4416.
+    static constexpr int NP = (P + THREADS - 1) / THREADS < P / 512 ? THREADS : 512;
+    static constexpr int PPT = (P + NP - 1) / NP;
     static constexpr int LP = L + L / 8;  // padded LDS line
     static constexpr size_t LDS_LINES = (size_t)LINES * LP * 2 * sizeof(T);
     // the twiddle table staged in LDS, where it fits beside the lines and the
@@ -166,7 +173,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
 {
     typedef RowFastShape<T, n, LOG2L> S;
     constexpr int NN = S::NN, PL = S::PL, L = S::L, Tn = S::Tn, RPW = S::RPW, LP = S::LP;
-    constexpr int G = S::G, ROUNDS = S::ROUNDS, NT = S::NT, PPT = S::PPT;
+    constexpr int G = S::G, ROUNDS = S::ROUNDS, NT = S::NT, PPT = S::PPT, NP = S::NP;
     constexpr bool HELPER = S::HELPER;
     typedef typename cx<T>::type C;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -263,8 +270,8 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     unsigned s_old = 0;
 #pragma unroll
     for (int pp = 0; pp < PPT; ++pp) {
-        const int idx = pp * 512 + tid;
-        const bool live = tid < 512 && row0 + (idx >> LOG2L) < a.rows;
+        const int idx = pp * NP + tid;
+        const bool live = tid < NP && idx < S::P && row0 + (idx >> LOG2L) < a.rows;
         const int8_t so = (live && (flags & RF_SIGN)) ? sgn[(row0 + (idx >> LOG2L)) * L + (idx & (L - 1))] : (int8_t)0;
         s_old |= (unsigned)(uint8_t)so << (8 * pp);
     }
@@ -324,7 +331,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         xp = (row0 + rq) * L + xq;
         lrq = lr + (size_t)rq * PL * LP + lds_pad(xq);
         liq = li + (size_t)rq * PL * LP + lds_pad(xq);
-        return row0 + rq < a.rows;
+        return idx < S::P && row0 + rq < a.rows;
     };
 
     // diagnostics and write-back of a projected point (LDS slot at lrq/liq)
@@ -363,7 +370,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         for (int pp = 0; pp < PPT; ++pp) {
             int64_t xp;
             T *lrq, *liq;
-            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+            if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
                 T av[NN];
 #pragma unroll
                 for (int k = 0; k < NN; ++k) av[k] = A[(int64_t)k * npts + xp];
@@ -396,7 +403,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         for (int pp = 0; pp < PPT; ++pp) {
             int64_t xp;
             T *lrq, *liq;
-            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+            if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
                 T av[NN], gv[NN], ov[NN];
 #pragma unroll
                 for (int k = 0; k < NN; ++k) gv[k] = G[(int64_t)k * npts + xp];
@@ -408,7 +415,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                     if (polar_vjp_newton3<T, 3>(av, gv, ov, a.sigma_fb)) {
                         put(lrq, liq, ov);
                     } else {
-                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * 512 + tid);
+                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * NP + tid);
                     }
                 }
             }
@@ -447,7 +454,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         for (int pp = 0; pp < PPT; ++pp) {
             int64_t xp;
             T *lrq, *liq;
-            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+            if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
                 T av[NN], qv[NN];
                 load_point(lrq, liq, av);
                 nbad += all_finite<T, NN>(av) ? 0ull : 1ull;
@@ -466,7 +473,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                     T smin;
                     polar_jacobi<T, n>(av, qv, ds, smin);
                     if (QUEUE && fallback && (double)smin < a.sigma_fb)
-                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * 512 + tid);
+                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * NP + tid);
                     else
                         key_out(xp, lrq, liq, qv, ds, smin);
                 }
@@ -508,7 +515,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
             for (int pp = 0; pp < PPT; ++pp) {
                 int64_t xp;
                 T *lrq, *liq;
-                if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+                if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
                     T av[NN];
                     load_point(lrq, liq, av);
                     nbad += all_finite<T, NN>(av) ? 0ull : 1ull;
@@ -518,9 +525,9 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                         // det sign, for the other waves to take over when it
                         // becomes the queue's wave
                         if (SPLIT && tid >= 512 - 64)
-                            hq[atomicAdd(&hq_n, 1)] = (pp * 512 + tid) | ((int)(uint8_t)(s_old >> (8 * pp)) << 16);
+                            hq[atomicAdd(&hq_n, 1)] = (pp * NP + tid) | ((int)(uint8_t)(s_old >> (8 * pp)) << 16);
                     } else {
-                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * 512 + tid);
+                        fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * NP + tid);
                     }
                 }
             }
@@ -561,13 +568,13 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
             // other waves' Newton iterations instead of following them.
             const bool split = SPLIT && fq_n > 0;
             const bool qwave = split && tid >= 512 - 64;
-            if (tid < 512 && !qwave) {
+            if (tid < NP && !qwave) {
 #pragma unroll 1
                 for (int pp = 0; pp < PPT; ++pp) {
                     if (!(ok >> pp & 1u)) continue;
                     int64_t xp;
                     T *lrq, *liq;
-                    (void)point_of(pp * 512 + tid, xp, lrq, liq);
+                    (void)point_of(pp * NP + tid, xp, lrq, liq);
                     if constexpr (PPT > 1) {
                         T av[NN];
                         load_point(lrq, liq, av);
@@ -605,8 +612,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                 }
             } else {
                 // The queued points go to the first wave done with its own
-                // points (threads beyond the 512 projection threads, for long
-                // rows, have none).  A wave of its own would cost the registers
+                // points (threads beyond the projection threads have none).  A wave of its own would cost the registers
                 // that let two workgroups share a CU.
                 int claim = 0;
                 if ((tid & 63) == 0) claim = atomicAdd(&fq_claim, 1);
@@ -618,7 +624,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
             for (int pp = 0; pp < PPT; ++pp) {
                 int64_t xp;
                 T *lrq, *liq;
-                if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+                if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
                     T av[NN], qv[NN];
                     load_point(lrq, liq, av);
                     nbad += all_finite<T, NN>(av) ? 0ull : 1ull;
@@ -629,7 +635,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                         } else if (fallback) {
                             float V[n][n];
                             if (polar_jacobi_f32_fb<n>(av, qv, ds, V, a.sigma_fb)) {
-                                fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * 512 + tid);
+                                fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * NP + tid);
                                 continue;
                             }
                         } else {
@@ -672,7 +678,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         for (int pp = 0; pp < PPT; ++pp) {
             int64_t xp;
             T *lrq, *liq;
-            if (tid < 512 && point_of(pp * 512 + tid, xp, lrq, liq)) {
+            if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
 #pragma unroll
                 for (int k = 0; k < NN; ++k)
                     Aout[(int64_t)k * npts + xp] = (k & 1) ? liq[(k >> 1) * LP] : lrq[(k >> 1) * LP];
