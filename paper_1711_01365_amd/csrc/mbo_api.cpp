@@ -182,7 +182,7 @@ struct mbo_plan_s {
     int band_c = 0, band_W = 0;
     int fast_tx = 0, tune_fast_tx = 0;
     void* lam_col = nullptr;
-    void* lam_y = nullptr;      // 3-D band-limited plane pass: axis-1 factor [N1] (per field with own tau)
+    void* lam_y = nullptr;      // 3-D band-limited plane pass: axis-1 factor [N1] (per field with own tau), behind lam_col
     unsigned long long* cnt_part = nullptr;
     // counts of the last mbo_project: double re-projections, non-finite inputs
     int64_t last_fb = 0, last_bad = 0;  // row-pass counts per workgroup [batch][log_K][workgroups]
@@ -297,7 +297,6 @@ void destroy(mbo_plan_t p)
     free_dev(p->lam_row);
     free_dev(p->lam_inner);
     free_dev(p->lam_col);
-    free_dev(p->lam_y);
     free_dev(p->mu_row);
     free_dev(p->mu_inner);
     free_dev(p->dpart);
@@ -497,17 +496,21 @@ bool fast_layout(int64_t N0, int64_t N1, int n, int pk, const double* taus, int6
 
 namespace {
 
-// 3-D band-limited path (float plans): the row pass over the x rows and one
-// plane pass per (packed plane, stored x mode) holding the whole y-z plane in
-// LDS, so y and z planes of 64 or 128 points.  The kept x half-width bounds the
-// dropped symbol mass by eta with the y and z axes' summed factors.
+// 3-D band-limited path: the row pass over the x rows and a plane pass per
+// (packed plane, stored x mode) holding the whole y-z plane in LDS, so y and z
+// sides of 8 to 128 points whose plane fits it (all of them in float; in double
+// at most 8192 points).  Two launches per iteration and two passes over kept
+// modes, against four and every mode of the general passes: 32 x 64 x 128 with
+// n = 2 in double, ten iterations, 267 us against 565; 32^3, n = 2 in float, five,
+// 106 against 210; 16^3, n = 3 in double 157 against 243; 128 x 64 x 64, n = 4 in
+// double, four, 675 against 866.  The kept x half-width bounds the dropped symbol
+// mass by eta with the y and z axes' summed factors.
 void config_fast3(mbo_plan_t p)
 {
     const int64_t N0 = p->N[0], N1 = p->N[1], N2 = p->N[2];
-    if (p->pk != 1) return;
-    if ((N0 != 64 && N0 != 128) || (N1 != 64 && N1 != 128) || N2 < 8 || N2 > 2048) return;
+    if (N0 < 8 || N0 > 128 || N1 < 8 || N1 > 128 || N2 < 8 || N2 > 2048) return;
     if (row_fast_lds_bytes(p->pk, p->n, ilog2((int)N2)) + 12288 > p->lds_max) return;
-    if (plane_fast_lds_bytes(ilog2((int)N1), ilog2((int)N0)) > p->lds_max) return;
+    if (plane_fast_lds_bytes(p->pk, ilog2((int)N1), ilog2((int)N0)) > p->lds_max) return;
     int c = (int)(N2 / 2), W = (int)N2;
     if (p->path == MBO_PATH_BANDED) {
         const double* taus = p->per_field_tau ? p->taus.data() : &p->tau;
@@ -515,7 +518,7 @@ void config_fast3(mbo_plan_t p)
         int cmax = 0;
         for (int64_t i = 0; i < ntau; ++i) {
             const double sy = axis_weight(N0, taus[i]) * axis_weight(N1, taus[i]);
-            const int ci = band_halfwidth_w(sy, N2, taus[i], 1e-12);
+            const int ci = band_halfwidth_w(sy, N2, taus[i], p->pk == 1 ? 1e-12 : 1e-20);
             cmax = ci > cmax ? ci : cmax;
         }
         // the plane-major layout needs no alignment of W: a plane pass per
@@ -563,7 +566,7 @@ void config_fast(mbo_plan_t p)
 mbo_status build_fast_tables(mbo_plan_t p)
 {
     free_dev(p->lam_col);
-    free_dev(p->lam_y);
+    p->lam_y = nullptr;
     if (!p->fast) return MBO_OK;
     const int W = p->band_W, c = p->band_c;
     const int64_t N1 = p->N[p->d - 1];
@@ -585,17 +588,15 @@ mbo_status build_fast_tables(mbo_plan_t p)
             v.push_back(std::exp(-4.0 * pi * pi * tau * k * k) / (double)N1);
         }
     }
-    HIP_TRY(p, hipMalloc(&p->lam_col, v.size() * p->esz));
-    const mbo_status s = upload(p, p->lam_col, v);
-    if (s != MBO_OK || p->d != 3) return s;
-    // 3-D: the y factor, exp(-4 pi^2 tau ky^2) / N1 of the plane pass
-    std::vector<double> y;
-    for (int64_t b = 0; b < nt; ++b) {
-        std::vector<double> f = axis_symbol(p->N[1], p->per_field_tau ? p->taus[(size_t)b] : p->tau);
-        y.insert(y.end(), f.begin(), f.end());
+    // 3-D: behind it the y factor, exp(-4 pi^2 tau ky^2) / N1 of the plane pass
+    const size_t ncol = v.size();
+    for (int64_t b = 0; b < nt && p->d == 3; ++b) {
+        const std::vector<double> f = axis_symbol(p->N[1], p->per_field_tau ? p->taus[(size_t)b] : p->tau);
+        v.insert(v.end(), f.begin(), f.end());
     }
-    HIP_TRY(p, hipMalloc(&p->lam_y, y.size() * p->esz));
-    return upload(p, p->lam_y, y);
+    HIP_TRY(p, hipMalloc(&p->lam_col, v.size() * p->esz));
+    if (p->d == 3) p->lam_y = static_cast<char*>(p->lam_col) + ncol * p->esz;
+    return upload(p, p->lam_col, v);
 }
 
 // Twiddles exp(-2 pi i m / L), m < L, interleaved (re, im).
@@ -791,11 +792,12 @@ void prepare_fast_kernels(mbo_plan_t p)
     if (!p->fast) return;
     FastRowArgs r;
     std::memset(&r, 0, sizeof r);
+    r.plane_major = p->d == 3;
     (void)launch_row_fast(p->pk, p->n, ilog2((int)p->N[p->d - 1]), r, dim3(1), nullptr, true);
     FastColArgs h;
     std::memset(&h, 0, sizeof h);
     if (p->d == 3) {
-        (void)launch_plane_fast(ilog2((int)p->N[1]), ilog2((int)p->N[0]), h, dim3(1), nullptr, true);
+        (void)launch_plane_fast(p->pk, ilog2((int)p->N[1]), ilog2((int)p->N[0]), h, dim3(1), nullptr, true);
     } else {
         for (int tx = 1; tx <= 16; tx *= 2)
             (void)launch_heat_fast(p->pk, ilog2((int)p->N[0]), tx, h, dim3(1), nullptr, true);
@@ -824,6 +826,10 @@ int fast_row_groups(mbo_plan_t p)
 // iterate (one per wave).
 dim3 fast_heat_grid(mbo_plan_t p)
 {
+    if (p->d == 3) {
+        const int g = plane_fast_group(ilog2((int)p->N[1]), ilog2((int)p->N[0]));
+        return dim3((unsigned)(((int64_t)p->PL * p->band_W + g - 1) / g), (unsigned)p->batch);
+    }
     return dim3((unsigned)((int64_t)p->PL * (p->band_W / p->fast_tx)), (unsigned)p->batch);
 }
 
@@ -1019,7 +1025,8 @@ hipError_t run_heat_fast(mbo_plan_t p, const FastColArgs& a, hipStream_t st, hip
                          hipEvent_t ev1 = nullptr)
 {
     if (p->d == 3)
-        return launch_plane_fast(ilog2((int)p->N[1]), ilog2((int)p->N[0]), a, fast_heat_grid(p), st, false, ev0, ev1);
+        return launch_plane_fast(p->pk, ilog2((int)p->N[1]), ilog2((int)p->N[0]), a, fast_heat_grid(p), st, false,
+                                 ev0, ev1);
     return launch_heat_fast(p->pk, ilog2((int)p->N[0]), p->fast_tx, a, fast_heat_grid(p), st, false, ev0, ev1);
 }
 

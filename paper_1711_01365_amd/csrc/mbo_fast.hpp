@@ -1137,27 +1137,33 @@ __global__ void __launch_bounds__(TX * (1 << LOG2L) / 8) heat_fast_adj(const Fas
 }
 
 // ---------------------------------------------------------------------------
-// Plane pass of the 3-D iteration (float): the heat step along y and z
+// Plane pass of the 3-D iteration: the heat step along y and z
 // ---------------------------------------------------------------------------
 
-// One workgroup per (field, packed plane, stored x mode w): the N0 x N1 plane of
-// that mode, contiguous in Z[plane][w][z][y] as the row pass stores it for
-// 3-D, is loaded once, transformed along y and then z in LDS, its Lyapunov
-// partial taken, multiplied by lambda_z(kz) lambda_y(ky) lambda_x(w),
-// transformed back along z and y, and stored in place: the whole diffusion
-// between two row passes in one read and one write of the spectra.  Each
-// thread holds two lines of eight values.  The plane sits in LDS as complex
-// pairs (real and imaginary part side by side: one address per element) in
-// rows of odd pitch, so that the z lines spread over the banks; the exchanges
-// inside a line use the XOR-permuted positions of line_index<LIX_XOR>.
+// The N0 x N1 plane of one packed plane and stored x mode w, contiguous in
+// Z[plane][w][z][y] as the row pass stores it for 3-D, is loaded once,
+// transformed along y and then z in LDS, its Lyapunov partial taken, multiplied
+// by lambda_z(kz) lambda_y(ky) lambda_x(w), transformed back along z and y, and
+// stored in place: the whole diffusion between two row passes in one read and
+// one write of the spectra.  Each thread holds two lines of eight values.  The
+// plane sits in LDS as complex pairs (real and imaginary part side by side: one
+// address per element) in rows of odd pitch, so that the z lines spread over the
+// banks; the exchanges inside a line use the XOR-permuted positions of
+// line_index<LIX_XOR>.  One workgroup per plane, or as many planes as fill a
+// wave where a plane has fewer than 1024 points (a wider workgroup of small
+// planes would leave CUs idle: 16 x 16 x 128 has a few hundred planes).
+// Bound by memory where the spectra are large (128^3 in float, n = 3: 53 us,
+// 2.8 TB/s), by the latency of its chain of transforms where they are not.
 template <typename T, int LOG2Y, int LOG2Z>
 struct PlaneFastShape {
     static constexpr int NY = 1 << LOG2Y, NZ = 1 << LOG2Z;
     static constexpr int TY = NY / 8, TZ = NZ / 8;
-    static constexpr int THREADS = NY * NZ / 16;
+    static constexpr int PT = NY * NZ / 16;         // threads of one plane
+    static constexpr int G = PT < 64 ? 64 / PT : 1; // planes per workgroup
+    static constexpr int THREADS = G * PT;
     static constexpr int PZ = NY + 1;  // row pitch in complex elements
-    // the plane, then the y and z twiddle tables
-    static constexpr size_t LDS = ((size_t)NZ * PZ + NY + NZ) * 2 * sizeof(T);
+    // the planes, then the y and z twiddle tables
+    static constexpr size_t LDS = ((size_t)G * NZ * PZ + NY + NZ) * 2 * sizeof(T);
 };
 
 template <typename T, int LOG2Y, int LOG2Z>
@@ -1167,11 +1173,17 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
     typedef typename cx<T>::type C;
     constexpr int NY = S::NY, NZ = S::NZ, TY = S::TY, TZ = S::TZ, PZ = S::PZ;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    T* lc = reinterpret_cast<T*>(smem_raw);  // element o: lc[2 o] (real), lc[2 o + 1] (imaginary)
 
     const int b = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int64_t wg = blockIdx.x;  // packed plane * W + stored mode
+    const int tid = threadIdx.x % S::PT;
+    const int pw = threadIdx.x / S::PT;  // this plane among the workgroup's
+    // element o of the plane: lc[2 o] (real), lc[2 o + 1] (imaginary)
+    T* lc = reinterpret_cast<T*>(smem_raw) + (S::G > 1 ? 2 * pw * NZ * PZ : 0);
+    // packed plane * W + stored mode; the last workgroup's planes beyond the
+    // field's read its last one and store nothing
+    const int64_t nplanes = a.field_elems / (NZ * NY);
+    const bool live = S::G == 1 || (int64_t)blockIdx.x * S::G + pw < nplanes;
+    const int64_t wg = live ? (int64_t)blockIdx.x * S::G + pw : nplanes - 1;
     const int w = (int)(wg % a.W);
     C* Zp = reinterpret_cast<C*>(a.Z) + (size_t)b * a.field_elems + (size_t)wg * NZ * NY;
     // y lines: group gy takes z = gy and gy + NZ/2, lane ty elements y = ty + e TY
@@ -1194,8 +1206,8 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
     // copies of global reads would be merged across the kernel and kept in
     // registers, more than the 1024-thread instance's 128 hold), and the symbol
     // where it is used
-    C* twl = reinterpret_cast<C*>(lc + 2 * (size_t)NZ * PZ);
-    for (int m = tid; m < NY + NZ; m += S::THREADS)
+    C* twl = reinterpret_cast<C*>(smem_raw) + (size_t)S::G * NZ * PZ;
+    for (int m = threadIdx.x; m < NY + NZ; m += S::THREADS)
         twl[m] = m < NY ? reinterpret_cast<const C*>(a.tw_y)[m] : reinterpret_cast<const C*>(a.tw)[m - NY];
     __syncthreads();
     const TwiddleTable<T, LOG2Y> twy{twl};
@@ -1208,7 +1220,7 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
         if (stop < a.iter) return;  // uniform per workgroup
         // the first pass of iteration s stops field b when s-1 changed it by <= tol
         if (check_tol && __longlong_as_double((long long)dbits) <= a.tol) {
-            if (blockIdx.x == 0 && tid == 0) atomicMin(a.stop_iter + b, a.iter - 1);
+            if (blockIdx.x == 0 && threadIdx.x == 0) atomicMin(a.stop_iter + b, a.iter - 1);
             return;
         }
     }
@@ -1251,16 +1263,17 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
 #pragma unroll
     for (int h = 0; h < 2; ++h) lyv[h] = ly[gz + h * (NY / 2)];
     if (a.epart) {
-        // this thread's terms in float, the wave's sum in double
+        // this thread's terms in the plan's precision, the wave's sum in double
         T acc = 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc += (lzv[e] * lyv[h]) * (r[h][e] * r[h][e] + im[h][e] * im[h][e]);
-        const double sum = wave_sum((double)acc);
+        const double sum = wave_sum(live ? (double)acc : 0.0);
         const int slot = a.slot >= 0 ? a.slot : a.stop_iter[b];
-        if ((tid & 63) == 0)
-            a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + wg * (blockDim.x >> 6) + (tid >> 6)] = sum;
+        if ((threadIdx.x & 63) == 0)
+            a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + (int64_t)blockIdx.x * (S::THREADS >> 6) +
+                    (threadIdx.x >> 6)] = sum;
     }
     if (!a.apply) return;
 #pragma unroll
@@ -1292,6 +1305,7 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
             im[h][e] = lc[o + 1];
         }
     fft_lines<T, +1, 2, LOG2Y, LIX_XOR>(r, im, lc, lc + 1, yp, 2, yl, fresh(ty), twy);
+    if (!live) return;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll

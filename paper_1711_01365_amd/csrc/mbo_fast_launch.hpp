@@ -23,22 +23,12 @@ static hipError_t row_fast_go(const FastRowArgs& a, dim3 g, hipStream_t st, bool
     return hipGetLastError();
 }
 
-// The row-major instance, and for float the plane-major one of the 3-D layout
-// (both prepared together).
+// The row-major instance or the plane-major one of the 3-D layout.
 template <typename T, int n, int LG>
 static hipError_t row_fast_pm(const FastRowArgs& a, dim3 g, hipStream_t st, bool prepare, hipEvent_t ev0,
                               hipEvent_t ev1)
 {
-    if constexpr (sizeof(T) == 4) {
-        if (prepare) {
-            const hipError_t e = row_fast_go<T, n, LG, true>(a, g, st, true, ev0, ev1);
-            if (e != hipSuccess) return e;
-        } else if (a.plane_major) {
-            return row_fast_go<T, n, LG, true>(a, g, st, false, ev0, ev1);
-        }
-    } else {
-        if (a.plane_major && !prepare) return hipErrorInvalidValue;  // float-only layout
-    }
+    if (a.plane_major) return row_fast_go<T, n, LG, true>(a, g, st, prepare, ev0, ev1);
     return row_fast_go<T, n, LG, false>(a, g, st, prepare, ev0, ev1);
 }
 
@@ -117,18 +107,6 @@ static hipError_t heat_fast_t(int log2L, int TX, const FastColArgs& a, dim3 g, h
     case 11: return heat_fast_l<T, 11>(TX, a, g, st, prepare, ev0, ev1);
     }
     return hipErrorInvalidValue;
-}
-
-template <typename T, int LY, int LZ>
-static hipError_t plane_fast_go(const FastColArgs& a, dim3 g, hipStream_t st, bool prepare, hipEvent_t ev0,
-                                hipEvent_t ev1)
-{
-    typedef PlaneFastShape<T, LY, LZ> S;
-    const void* f = reinterpret_cast<const void*>(&plane_fast<T, LY, LZ>);
-    if (prepare) return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
-    if (ev0) hipExtLaunchKernelGGL((plane_fast<T, LY, LZ>), g, dim3(S::THREADS), S::LDS, st, ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((plane_fast<T, LY, LZ>), g, dim3(S::THREADS), S::LDS, st, a);
-    return hipGetLastError();
 }
 
 }  // namespace mbo

@@ -514,11 +514,13 @@ int heat_fast_adj_tile(int log2L);
 hipError_t launch_row_fast_vkey(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
                                 bool prepare = false);
 hipError_t launch_volume_fix(int prec, int n, const VolFixArgs& a, dim3 grid, hipStream_t st);
-// the 3-D plane pass (float): one workgroup per (packed plane, stored x mode)
-hipError_t launch_plane_fast(int log2Y, int log2Z, const FastColArgs& a, dim3 grid, hipStream_t st,
+// the 3-D plane pass: workgroups of plane_fast_group planes (a packed plane and
+// stored x mode each)
+hipError_t launch_plane_fast(int prec, int log2Y, int log2Z, const FastColArgs& a, dim3 grid, hipStream_t st,
                              bool prepare = false, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+int plane_fast_group(int log2Y, int log2Z);
 int plane_fast_threads(int log2Y, int log2Z);
-size_t plane_fast_lds_bytes(int log2Y, int log2Z);
+size_t plane_fast_lds_bytes(int prec, int log2Y, int log2Z);
 // flips / fallbacks / non-finite of every iteration from `first` on and field from the row
 // pass's per-workgroup packed counts [batch][K][nwg]
 hipError_t launch_sum_counts(const unsigned long long* part, int nwg, int K, int first, int batch,
