@@ -158,8 +158,12 @@ struct RowFastShape {
     // workgroup.  The register budget this leaves (128) holds the queued
     // points' double Jacobi without spilling: any scratch use would delay the
     // launch of the workgroups, and a ninth wave per workgroup would leave
-    // room for only one of them per CU at that budget.
-    static constexpr int WAVES = WAVE_LINE ? 4 : (THREADS + 255) / 256;
+    // room for only one of them per CU at that budget.  Double n = 4 does not fit it (520 bytes of
+    // scratch): rows of 512 points run one workgroup per CU with 252 registers
+    // instead (512^2, six steps: 482 us, with scratch 506; 1024 x 512 875 and 947);
+    // shorter rows, whose workgroups end at more uneven times, keep two (1024 x
+    // 256: 662 us, alone 688; 64^3, four steps: 525 and 548).
+    static constexpr int WAVES = WAVE_LINE ? (sizeof(T) == 8 && n == 4 && LOG2L == 9 ? 2 : 4) : (THREADS + 255) / 256;
 };
 
 // What the points of a row pass go through between the two line transforms:
