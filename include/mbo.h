@@ -99,10 +99,12 @@ typedef enum {
  * tau and grid leave nothing to drop runs the same kernels with every mode kept.
  * MBO_PATH_FULL runs the same kernels with every mode kept; MBO_PATH_GENERIC the
  * general kernels (any d, any row length).  mbo_diffuse, mbo_step, mbo_energy
- * and, for d = 2, mbo_step_vjp and mbo_diffuse_dtau run the kernels that
- * mbo_iterate runs; the other calls always use the general ones.
+ * and, for d = 2, mbo_step_vjp, mbo_diffuse_dtau, mbo_iterate_volume and (n <= 3,
+ * every mode kept) mbo_relaxed_flow run the kernels that mbo_iterate runs; the
+ * other calls always use the general ones.
  * The band-limited kernels serve d = 2 with a first axis of at least 64 points
- * (every last axis a plan accepts); other shapes run the general kernels. */
+ * (every last axis a plan accepts) and d = 3 with first axes of at most 128 points
+ * whose product is at most 8192 in double; other shapes run the general kernels. */
 typedef enum {
     MBO_PATH_GENERIC = 0,
     MBO_PATH_FULL = 1,

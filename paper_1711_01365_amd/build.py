@@ -23,9 +23,9 @@ SOURCES = ["mbo_row_f32.hip", "mbo_row_f64.hip", "mbo_col_f32.hip", "mbo_col_f64
            "mbo_relaxrow_f64.hip", "mbo_misc.hip", "mbo_fast_f32.hip", "mbo_fast_f64.hip",
            "mbo_plane_f32.hip", "mbo_plane_f64.hip", "mbo_surface.hip", "mbo_surfvol.hip", "mbo_surfsep.hip",
            "mbo_static.hip", "mbo_fastadj_f32.hip", "mbo_fastadj_f64.hip",
-           "mbo_fastvol_f32.hip", "mbo_fastvol_f64.hip", "mbo_api.cpp"]
+           "mbo_fastvol_f32.hip", "mbo_fastvol_f64.hip", "mbo_fastrelax_f32.hip", "mbo_fastrelax_f64.hip", "mbo_api.cpp"]
 HEADERS = ["mbo_device.hpp", "mbo_kernels.hpp", "mbo_internal.hpp", "mbo_volume.hpp", "mbo_fast.hpp",
-           "mbo_fast_launch.hpp", "mbo_plane_launch.hpp", "mbo_fastadj_launch.hpp", "mbo_fastvol_launch.hpp"]
+           "mbo_fast_launch.hpp", "mbo_plane_launch.hpp", "mbo_fastadj_launch.hpp", "mbo_fastvol_launch.hpp", "mbo_fastrelax_launch.hpp"]
 
 
 def hipcc() -> str:

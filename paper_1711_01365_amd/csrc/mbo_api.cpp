@@ -1431,12 +1431,62 @@ hipError_t run_row_relax(mbo_plan_t p, const RowArgs& a, hipStream_t st)
     return launch_row_relax(p->pk, p->n, a.log2L, a, p->row_grid, p->row_block, p->row_lds, st);
 }
 
+// Whether the flow runs on the two passes of mbo_iterate, with every mode kept (the
+// resolvent falls off as |k|^-2: no band to leave out): 2-D plans that have them, n <= 3.
+// GD-1 with n = 3 in float, 20 steps of 512^2: 593 us against 648 by the general passes;
+// ten of 1024^2 925 against 1329, of 64^2 140 against 151; GD-3 in double, ten of 128 x
+// 1024, 383 against 467; n = 2, 256 x 16, 133 against 150.  With n = 4 the two-pass row
+// pass gains only on rows of 512 points (446 against 520) and loses on others (256^2 in
+// float 340 against 271, 1024^2 in double 2995 against 2483).
+bool relax_fast(mbo_plan_t p) { return p->fast && p->d == 2 && p->n <= 3; }
+
+hipError_t enqueue_relaxed_flow_fast(mbo_plan_t p, void* A, int K, int kind, double c, double dt, hipStream_t st)
+{
+    hipError_t e;
+    const int log2Y = ilog2((int)p->N[0]), log2X = ilog2((int)p->N[1]);
+    const int tx = resolvent_fast_tile(log2Y);
+    const dim3 gc((unsigned)((int64_t)p->PL * (p->N[1] / tx)), (unsigned)p->batch);
+    const dim3 gr((unsigned)fast_row_groups(p), (unsigned)p->batch);
+    FastRowArgs r = fast_row_args(p);
+    r.band = (int)(p->N[1] / 2);
+    r.W = (int)p->N[1];
+    r.Ain = A;
+    r.Aout = A;
+    r.flags = RF_LOAD_REAL | RF_FORWARD;
+    if ((e = launch_row_fast(p->pk, p->n, log2X, r, gr, st)) != hipSuccess) return e;
+    FastColArgs h = fast_col_args(p);
+    h.W = (int)p->N[1];
+    h.tiles = h.W / tx;
+    h.field_elems = (int64_t)p->PL * p->npts;
+    h.lam_row = p->mu_row;
+    h.lam_col = p->mu_inner;
+    h.lam_row_stride = h.lam_col_stride = 0;
+    h.rdt = dt;
+    h.rnorm = 1.0 / (double)p->npts;
+    r.K = K;
+    r.cnt_part = p->cnt_part;
+    r.relax_kind = kind;
+    r.relax_c = c;
+    const int fb = p->prec == MBO_F32_F64FALLBACK ? RF_FALLBACK : 0;
+    for (int s = 1; s <= K; ++s) {
+        if ((e = launch_resolvent_fast(p->pk, log2Y, h, gc, st)) != hipSuccess) return e;
+        r.iter = s;
+        r.flags = RF_INVERSE | fb | (s < K ? RF_FORWARD : RF_STORE_REAL);
+        if ((e = launch_row_fast_relax(p->pk, p->n, log2X, r, gr, st)) != hipSuccess) return e;
+    }
+    return launch_sum_counts(p->cnt_part, (int)gr.x, K, 0, (int)p->batch, p->flips, p->fallbacks, p->nonfinite, st);
+}
+
 // K steps of B = (I - dt Delta)^{-1} A, A = B - c N(B) in place on A.
 hipError_t enqueue_relaxed_flow(mbo_plan_t p, void* A, int K, int kind, double c, double dt, hipStream_t st)
 {
     hipError_t e;
     if ((e = enqueue_init_logs(p, K, st)) != hipSuccess) return e;
     if (K == 0) return enqueue_export_logs(p, K, false, st);
+    if (relax_fast(p)) {
+        if ((e = enqueue_relaxed_flow_fast(p, A, K, kind, c, dt, st)) != hipSuccess) return e;
+        return enqueue_export_logs(p, K, false, st);
+    }
     if ((e = enqueue_forward(p, A, 0, false, st)) != hipSuccess) return e;
     const int fb = p->prec == MBO_F32_F64FALLBACK ? RF_FALLBACK : 0;
     for (int s = 1; s <= K; ++s) {
@@ -3330,8 +3380,13 @@ mbo_status mbo_relaxed_flow(mbo_plan_t p, void* A, int steps, int kind, double e
     if (!(dt > 0.0) || !std::isfinite(dt)) return fail(p, MBO_ERR_INVALID_ARG, "dt must be finite and > 0");
     HIP_TRY(p, hipSetDevice(p->device));
     if ((s = ensure_logs(p, steps)) != MBO_OK) return s;
-    (void)launch_row_relax(p->pk, p->n, ilog2((int)p->N[p->d - 1]), row_args(p), p->row_grid, p->row_block,
-                           p->lds_max, nullptr, true);
+    if (relax_fast(p)) {
+        (void)launch_row_fast_relax(p->pk, p->n, ilog2((int)p->N[1]), fast_row_args(p), dim3(1), nullptr, true);
+        (void)launch_resolvent_fast(p->pk, ilog2((int)p->N[0]), fast_col_args(p), dim3(1), nullptr, true);
+    } else {
+        (void)launch_row_relax(p->pk, p->n, ilog2((int)p->N[p->d - 1]), row_args(p), p->row_grid, p->row_block,
+                               p->lds_max, nullptr, true);
+    }
     (void)hipGetLastError();
     const double c = std::isinf(eps) ? 0.0 : dt / (eps * eps);
     if (use_graphs()) {

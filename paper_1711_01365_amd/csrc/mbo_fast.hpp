@@ -158,8 +158,8 @@ struct RowFastShape {
     // workgroup.  The register budget this leaves (128) holds the queued
     // points' double Jacobi without spilling: any scratch use would delay the
     // launch of the workgroups, and a ninth wave per workgroup would leave
-    // room for only one of them per CU at that budget.  Double n = 4 does not fit it (520 bytes of
-    // scratch): rows of 512 points run one workgroup per CU with 252 registers
+    // room for only one of them per CU at that budget.  Double n = 4 does not
+    // fit it (520 bytes of scratch): rows of 512 points run one workgroup per CU with 252 registers
     // instead (512^2, six steps: 482 us, with scratch 506; 1024 x 512 875 and 947);
     // shorter rows, whose workgroups end at more uneven times, keep two (1024 x
     // 256: 662 us, alone 688; 64^3, four steps: 525 and 548).
@@ -169,8 +169,9 @@ struct RowFastShape {
 // What the points of a row pass go through between the two line transforms:
 // FM_ITER the steps that the flags name (projection, load, store), FM_VJP the
 // projection's vector-Jacobian product with the cotangent field a.Gin, FM_VKEY
-// the projection with Delta E of the volume-preserving step into a.vde.
-enum { FM_ITER = 0, FM_VJP = 1, FM_VKEY = 2 };
+// the projection with Delta E of the volume-preserving step into a.vde, FM_RELAX
+// the reaction step of the relaxed flows (GD-1 by the projection of FM_ITER).
+enum { FM_ITER = 0, FM_VJP = 1, FM_VKEY = 2, FM_RELAX = 3 };
 
 template <typename T, int n, int LOG2L, bool PM, int MODE>
 __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
@@ -183,7 +184,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T* lr = reinterpret_cast<T*>(smem_raw);
     T* li = lr + (size_t)S::LINES * LP;
-    __shared__ unsigned short fq[(HELPER || S::DEFER4 || (MODE != FM_ITER && n == 3)) ? S::P : 1];
+    __shared__ unsigned short fq[(HELPER || S::DEFER4 || ((MODE == FM_VJP || MODE == FM_VKEY) && n == 3)) ? S::P : 1];
     __shared__ int fq_n, fq_claim;
     // rows of at most 512 points (every wave holds points): the last wave's
     // Newton points, handed to the other waves when it runs the queue
@@ -339,7 +340,16 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     };
 
     // diagnostics and write-back of a projected point (LDS slot at lrq/liq)
-    auto finish = [&](int64_t xp, T* lrq, T* liq, const T (&qv)[NN], int ds, int8_t so) {
+    auto finish = [&](int64_t xp, T* lrq, T* liq, T (&qv)[NN], int ds, int8_t so) {
+        if constexpr (MODE == FM_RELAX) {
+            // GD-1: N(A) = U (Sigma - I) V^t = A - U V^t, the point is still in LDS
+            const T rc = (T)a.relax_c;
+#pragma unroll
+            for (int k = 0; k < NN; ++k) {
+                const T av = (k & 1) ? liq[(k >> 1) * LP] : lrq[(k >> 1) * LP];
+                qv[k] = av - rc * (av - qv[k]);
+            }
+        }
         if (flags & RF_SIGN) {
             nflip += (so != (int8_t)ds) ? 1ull : 0ull;
             sgn[xp] = (int8_t)ds;
@@ -449,7 +459,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         // of det Q (also where sigma_min is 0: volume_fix reads the side there).
         // Float points below sigma_fb are queued and done in double afterwards.
         T* vde = reinterpret_cast<T*>(a.vde) + (size_t)b * npts;
-        auto key_out = [&](int64_t xp, T* lrq, T* liq, const T (&qv)[NN], int ds, T smin) {
+        auto key_out = [&](int64_t xp, T* lrq, T* liq, T (&qv)[NN], int ds, T smin) {
             vde[xp] = ds > 0 ? smin + smin : -(smin + smin);
             finish(xp, lrq, liq, qv, ds, (int8_t)0);
         };
@@ -509,7 +519,43 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
             }
         }
         __syncthreads();
-    } else if (flags & RF_PROJECT) {
+    } else if (MODE == FM_RELAX && a.relax_kind == 3) {
+        // GD-3: N(A) = A (A^t A - I)
+#pragma unroll 1
+        for (int pp = 0; pp < PPT; ++pp) {
+            int64_t xp;
+            T *lrq, *liq;
+            if (tid < NP && point_of(pp * NP + tid, xp, lrq, liq)) {
+                T av[NN], m[NN];
+                load_point(lrq, liq, av);
+                nbad += all_finite<T, NN>(av) ? 0ull : 1ull;
+#pragma unroll
+                for (int i = 0; i < n; ++i)
+#pragma unroll
+                    for (int j = 0; j < n; ++j) {
+                        T v = 0;
+#pragma unroll
+                        for (int k = 0; k < n; ++k) v += av[k * n + i] * av[k * n + j];
+                        m[i * n + j] = v - (i == j ? (T)1 : (T)0);
+                    }
+                const T rc = (T)a.relax_c;
+#pragma unroll
+                for (int i = 0; i < n; ++i)
+#pragma unroll
+                    for (int j = 0; j < n; ++j) {
+                        T v = 0;
+#pragma unroll
+                        for (int k = 0; k < n; ++k) v += av[i * n + k] * m[k * n + j];
+                        v = av[i * n + j] - rc * v;
+                        const int e = i * n + j;
+                        if (e & 1) liq[(e >> 1) * LP] = v;
+                        else lrq[(e >> 1) * LP] = v;
+                        if (flags & RF_STORE_REAL) Aout[(int64_t)e * npts + xp] = v;
+                    }
+            }
+        }
+        __syncthreads();
+    } else if (MODE == FM_RELAX || (flags & RF_PROJECT)) {
         if constexpr (HELPER) {
             // which points are certainly well conditioned: the Newton
             // iteration; the others are queued
@@ -749,7 +795,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         }
     }
 
-    if (MODE == FM_VKEY || (flags & (RF_PROJECT | RF_TRACK))) {
+    if (MODE == FM_VKEY || MODE == FM_RELAX || (flags & (RF_PROJECT | RF_TRACK))) {
         // counts of the workgroup: packed 21 bits each (at most 2048 per workgroup)
         unsigned long long packed = wave_sum(nflip | (nfb << 21) | (nbad << 42));
         unsigned long long dbits = (unsigned long long)__double_as_longlong(dmax);
@@ -787,6 +833,13 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFast
     row_fast_vjp(const FastRowArgs a)
 {
     row_fast_body<T, n, LOG2L, false, FM_VJP>(a);
+}
+
+template <typename T, int n, int LOG2L>
+__global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
+    row_fast_relax(const FastRowArgs a)
+{
+    row_fast_body<T, n, LOG2L, false, FM_RELAX>(a);
 }
 
 // n = 4: the Jacobi of every point with its singular values takes more than 128
@@ -1066,7 +1119,10 @@ __device__ __forceinline__ void heat_fast_body(const FastColArgs& a)
         }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) lam[e] *= lcol;
+    for (int e = 0; e < 8; ++e) {
+        if constexpr (MODE == HF_RESOLVENT) lam[e] = (T)a.rnorm / ((T)1 - (T)a.rdt * (lam[e] + lcol));
+        else lam[e] *= lcol;
+    }
     fft_lines<T, -1, 1, LOG2L>(r, im, lr, li, 0, TX, cc, t, tw);
     if (a.epart) {
         // this thread's eight terms in the plan's precision, the wave's sum in double
@@ -1078,7 +1134,7 @@ __device__ __forceinline__ void heat_fast_body(const FastColArgs& a)
         if ((tid & 63) == 0)
             a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + wg * (blockDim.x >> 6) + (tid >> 6)] = s;
     }
-    if constexpr (MODE != HF_PLAIN) {
+    if constexpr (MODE == HF_SAVE || MODE == HF_DOT || MODE == HF_DTAU) {
         // a thread's eight values side by side: the two passes run the same
         // launch shape, so the layout of a.spec is their own
         C* S = reinterpret_cast<C*>(a.spec) + ((size_t)b * gridDim.x + wg) * (size_t)(TX * L) + tid;

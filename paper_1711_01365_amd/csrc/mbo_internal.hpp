@@ -448,6 +448,8 @@ struct FastRowArgs {
     const void* Gin;         // row_fast_vjp: cotangent field [batch][n*n][npts]
     void* Zout;              // row_fast_vkey: row spectra written (Z is read)
     void* vde;               // row_fast_vkey: Delta E per point [batch][npts]
+    int relax_kind;          // row_fast_relax: 1 = GD-1, 3 = GD-3
+    double relax_c;          // row_fast_relax: dt / eps^2
 };
 
 // The points that the volume-preserving selection reassigns (volume_fix).
@@ -486,6 +488,8 @@ struct FastColArgs {
     int N1, band;            // last axis length and kept half-width
     void* spec;              // transformed columns [batch][gridDim.x][8][threads] complex
     double* dpart;           // [batch][nwg]
+    // HF_RESOLVENT: the step dt and the inverse transforms' scale 1 / (N0 N1)
+    double rdt, rnorm;
 };
 
 // What a column pass does with the transformed columns besides the heat step
@@ -493,7 +497,9 @@ struct FastColArgs {
 // Re(conj(column) a.spec) (-4 pi^2 |k|^2) symbol, one double per wave, in
 // a.dpart [batch][nwg]; HF_DTAU multiplies by -4 pi^2 |k|^2 symbol in place of
 // the symbol, and stores the columns as HF_SAVE does when a.spec is set.
-enum { HF_PLAIN = 0, HF_SAVE = 1, HF_DOT = 2, HF_DTAU = 3 };
+// HF_RESOLVENT takes a.lam_row + a.lam_col as -4 pi^2 |k|^2 and multiplies by
+// rnorm / (1 + 4 pi^2 rdt |k|^2), the implicit diffusion step of the relaxed flows.
+enum { HF_PLAIN = 0, HF_SAVE = 1, HF_DOT = 2, HF_DTAU = 3, HF_RESOLVENT = 4 };
 
 hipError_t launch_row_fast(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
                            bool prepare = false, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
@@ -514,6 +520,14 @@ int heat_fast_adj_tile(int log2L);
 hipError_t launch_row_fast_vkey(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
                                 bool prepare = false);
 hipError_t launch_volume_fix(int prec, int n, const VolFixArgs& a, dim3 grid, hipStream_t st);
+// The relaxed flows' passes (2-D, every mode kept): row_fast_relax steps the points
+// by the reaction term, the column pass in mode HF_RESOLVENT (tiles of
+// resolvent_fast_tile columns).
+hipError_t launch_row_fast_relax(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
+                                 bool prepare = false);
+hipError_t launch_resolvent_fast(int prec, int log2L, const FastColArgs& a, dim3 grid, hipStream_t st,
+                                 bool prepare = false);
+int resolvent_fast_tile(int log2L);
 // the 3-D plane pass: workgroups of plane_fast_group planes (a packed plane and
 // stored x mode each)
 hipError_t launch_plane_fast(int prec, int log2Y, int log2Z, const FastColArgs& a, dim3 grid, hipStream_t st,
