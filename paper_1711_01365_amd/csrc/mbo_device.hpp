@@ -179,6 +179,26 @@ __device__ __forceinline__ void twiddle(T& r, T& i, const typename cx<T>::type w
     i = ni;
 }
 
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// twiddle with its fused multiplications written out.  IMF: which of the two
+// products of a forward imaginary part is fused, i w.x or else r w.y.
+template <typename T, int S, bool IMF>
+__device__ __forceinline__ void twiddle_fma(T& r, T& i, const typename cx<T>::type w)
+{
+    T nr, ni;
+    if constexpr (S < 0) {
+        nr = fma_t(r, w.x, -(i * w.y));
+        ni = IMF ? fma_t(i, w.x, r * w.y) : fma_t(r, w.y, i * w.x);
+    } else {
+        nr = fma_t(r, w.x, i * w.y);
+        ni = fma_t(i, w.x, -(r * w.y));
+    }
+    r = nr;
+    i = ni;
+}
+
 // LDS index with one pad slot per eight elements (spreads the strided stage
 // writes over all banks).
 __device__ __forceinline__ int lds_pad(int j) { return j + (j >> 3); }
@@ -389,23 +409,39 @@ enum { FFT_FULL = 0, FFT_IN07 = 1, FFT_OUT07 = 2 };
 // The same transform for a line whose L/8 threads lie inside one wave
 // (L <= 512): exchanges need no workgroup barrier.  LDS element j of the line is
 // at lr/li[lds_pad(j)].  Threads with act = false touch no LDS.
-template <typename T, int S, int LOG2L, int STAGE = 0, int PR = FFT_FULL>
+// With the twiddles of a longer line (LOG2F > LOG2L = 9) it is part q of that line's
+// transform of R * 512 points, R = 2 or 4, after its radix-R first stage: the
+// later stages only combine elements of equal index mod R, so that elements
+// R m + q form a 512-point transform of their own whose stages all have twiddles,
+// those of thread R t + q of the long line (its values bit for bit).
+template <typename T, int S, int LOG2L, int STAGE = 0, int PR = FFT_FULL, int LOG2F = LOG2L, bool IMF = false>
 __device__ __forceinline__ void fft_wave(T (&r)[8], T (&im)[8], T* lr, T* li, int t,
-                                         const Twiddles<T, LOG2L>& tw, bool act)
+                                         const Twiddles<T, LOG2F>& tw, bool act)
 {
+    constexpr int TS = LOG2F > LOG2L ? STAGE : STAGE - 1;  // this stage's twiddles
+    static_assert(LOG2F == LOG2L || (LOG2L == 9 && FftShape<LOG2F>::NTW == 3), "a part has 512 points");
     typedef FftShape<LOG2L> F;
     static_assert(LOG2L <= 9, "a line must fit in one wave");
     static_assert(!(PR & FFT_IN07) || F::radix(0) == 8, "input pruning needs a radix-8 first stage");
     if constexpr (STAGE < F::NST) {
         constexpr int R = F::radix(STAGE);
         constexpr int p = 1 << F::log2span(STAGE);
-        if constexpr (STAGE == 0 && (PR & FFT_IN07)) dft8_in07<T, S>(r, im);
-        else if constexpr (STAGE == 0) stage_span1<T, R, S>(r, im);
+        if constexpr (STAGE == 0 && (PR & FFT_IN07)) {
+            if constexpr (TS >= 0) twiddle_fma<T, S, IMF>(r[7], im[7], tw.w[0][6]);
+            dft8_in07<T, S>(r, im);
+        } else if constexpr (STAGE == 0 && TS < 0) stage_span1<T, R, S>(r, im);
         else if constexpr (STAGE == F::NST - 1 && (PR & FFT_OUT07)) {
 #pragma unroll
-            for (int j = 1; j < 8; ++j) twiddle<T, S>(r[j], im[j], tw.w[STAGE - 1][j - 1]);
+            for (int j = 1; j < 8; ++j) {
+                if constexpr (LOG2F > LOG2L) twiddle_fma<T, S, IMF>(r[j], im[j], tw.w[TS][j - 1]);
+                else twiddle<T, S>(r[j], im[j], tw.w[TS][j - 1]);
+            }
             dft8_out07<T, S>(r, im);
-        } else stage_tw8<T, S>(r, im, tw.w[STAGE - 1]);
+        } else if constexpr (LOG2F > LOG2L) {
+#pragma unroll
+            for (int j = 1; j < 8; ++j) twiddle_fma<T, S, IMF>(r[j], im[j], tw.w[TS][j - 1]);
+            dft8<T, S>(r, im);
+        } else stage_tw8<T, S>(r, im, tw.w[TS]);
         if constexpr (STAGE != F::NST - 1) {
             wave_lds_sync();  // earlier reads of the line are done
             if (act) {
@@ -444,7 +480,7 @@ __device__ __forceinline__ void fft_wave(T (&r)[8], T (&im)[8], T* lr, T* li, in
                     im[e] = li[a];
                 }
             }
-            fft_wave<T, S, LOG2L, STAGE + 1, PR>(r, im, lr, li, t, tw, act);
+            fft_wave<T, S, LOG2L, STAGE + 1, PR, LOG2F, IMF>(r, im, lr, li, t, tw, act);
         }
     }
 }

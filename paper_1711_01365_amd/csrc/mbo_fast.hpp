@@ -19,8 +19,7 @@
 //              1024 and 2048 points, one row: the line groups of its packed
 //              planes load their kept modes straight into the FFT register
 //              layout (lane t holds x[t + e L/8]), inverse-FFT (inside one wave
-//              for L <= 512, with workgroup exchanges and in rounds of lines
-//              beyond) and leave the lines in LDS; 512 threads or more, one to
+//              for L <= 512, in L/512 waves or with workgroup exchanges beyond) and leave the lines in LDS; 512 threads or more, one to
 //              four points each, project (Lemma 1.1) with the det-sign,
 //              fallback, non-finite and change diagnostics; the line groups
 //              forward-FFT and store the kept modes.  Float plans with n = 3
@@ -112,13 +111,51 @@ __device__ __forceinline__ void newton3_run(Newton3& s, float* q, int& dsign)
 // Row pass
 // ---------------------------------------------------------------------------
 
+// (x, y) times i^p
+template <typename T>
+__device__ __forceinline__ void turn(T& x, T& y, int p)
+{
+    if (p & 1) {
+        const T v = x;
+        x = -y;
+        y = v;
+    }
+    if (p & 2) {
+        x = -x;
+        y = -y;
+    }
+}
+
+// Adds ((ax, ay) + (-1)^q (bx, by)) i^p to (x, y): output q of dft2 or, in two
+// steps, of dft4, with its operations.
+template <typename T>
+__device__ __forceinline__ void first_stage(T& x, T& y, T ax, T ay, T bx, T by, int q, int p)
+{
+    T vx = (q & 1) ? ax - bx : ax + bx, vy = (q & 1) ? ay - by : ay + by;
+    turn(vx, vy, p);
+    x += vx;
+    y += vy;
+}
+
 // Shape of a row-pass workgroup: 512 points (512/L rows) for L <= 512, one row
 // of L points otherwise; NP projection threads (PPT points each); the line
-// groups of L/8 threads run in ROUNDS rounds of G lines over NT threads.
+// groups of Tn threads run in ROUNDS rounds of G transforms over NT threads.  A
+// line of up to 512 points is one transform of L/8 threads inside a wave.  A longer
+// one is, with PARTS, the R = L/512 parts of fft_wave, a wave each, after the
+// radix-R first stage that each wave takes from the whole line: no exchange crosses
+// a wave, one workgroup barrier per round and direction in place of two per stage,
+// the same values; otherwise one transform of L/8 threads with workgroup barriers.
+// Row pass, whole -> parts: 512 x 2048, n = 3 in float 49 -> 45 us; 1024 x 1024,
+// n = 4 84 -> 74; 256 x 1024, n = 3 in double 26.6 -> 24.8.  The other instances gain
+// less (n = 2 24 -> 22, n = 3 1024 x 1024 57 -> 51) and would round their transforms in
+// another order, which changes the det sign of a tied point now and then.
 template <typename T, int n, int LOG2L>
 struct RowFastShape {
     static constexpr int L = 1 << LOG2L;
-    static constexpr int Tn = L / 8;
+    static constexpr bool PARTS =
+        LOG2L >= 10 && (n == 4 || (n >= 2 && sizeof(T) == 8) || (n == 3 && LOG2L == 11));
+    static constexpr int R = PARTS ? L / 512 : 1;
+    static constexpr int Tn = L / R / 8;
     static constexpr int NN = n * n;
     static constexpr int PL = (NN + 1) / 2;
     static constexpr int RPW = L >= 512 ? 1 : 512 / L;
@@ -132,10 +169,12 @@ struct RowFastShape {
     // long rows: at most 768 threads for float n = 3 (twelve waves, a budget of
     // 168 registers for the queued points' double Jacobi), else 1024
     static constexpr int NTMAX = HELPER ? 768 : 1024;
-    static constexpr int NT_LINES = LINES * Tn < NTMAX / Tn * Tn ? LINES * Tn : NTMAX / Tn * Tn;
+    static constexpr int NT_LINES = LINES * R * Tn < NTMAX / (R * Tn) * (R * Tn) ? LINES * R * Tn
+                                                                                  : NTMAX / (R * Tn) * (R * Tn);
     static constexpr int NT = WAVE_LINE ? 512 : (NT_LINES > 512 ? NT_LINES : 512);
-    static constexpr int G = NT / Tn;  // lines per round
-    static constexpr int ROUNDS = (LINES + G - 1) / G;
+    static constexpr int G = NT / Tn;  // transforms per round: whole lines (R divides G)
+    static constexpr int ROUNDS = (LINES * R + G - 1) / G;
+    static_assert(G % R == 0, "a round transforms whole lines");
     static constexpr int THREADS = NT;
     // projection threads: 512, or every thread of a long row's workgroup where
     // that leaves each fewer points (1024 points over 1024 threads at n = 4, 2048
@@ -225,10 +264,13 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     const int g = tid / Tn, t = tid - (tid / Tn) * Tn;
     const int pt = lds_pad(t);
     const bool fft_thread = tid < NT;
+    constexpr int R = S::R, LOG2S = S::PARTS ? 9 : LOG2L;  // log2 of a transform's points
+    constexpr bool IMF = n < 4;  // the order in which the whole-line transform of the instance is compiled
+    const int q = g & (R - 1);                                 // its part of the line (R divides G)
     Twiddles<T, LOG2L> tw;
     T r[1][8], im[1][8];
-    // Line j of a round is row rl, packed plane pl of the workgroup (LDS line
-    // rl*PL + pl).  Spectra are stored row by row (Z[plane][row][w]) or, for
+    // Transform j is part q of line j / R; line j is row rl, packed plane
+    // pl of the workgroup (LDS line rl*PL + pl).  Spectra are stored row by row (Z[plane][row][w]) or, for
     // the 3-D plane pass, plane by plane (Z[plane][w][row]): there the lines
     // of one plane go to neighbouring groups, so that a wave's stores of one
     // mode cover consecutive rows.
@@ -246,17 +288,61 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     };
     auto load_line = [&](int j) {
         int rl, pl;
-        line_of(j, rl, pl);
-        const bool live = j < S::LINES && row0 + rl < a.rows;
+        line_of(j / R, rl, pl);
+        const bool live = j < S::LINES * R && row0 + rl < a.rows;
         const int64_t row = live ? row0 + rl : 0;
+        if (!S::PARTS || c < 256) {
+            // the one kept mode of those at distance 512
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int w = band_slot(t + e * Tn, L, c, W);
-            C v;
-            if (live && w >= 0) v = Zb[zat(pl, row, w)];
-            else { v.x = 0; v.y = 0; }
-            r[0][e] = v.x;
-            im[0][e] = v.y;
+            for (int e = 0; e < 8; ++e) {
+                const int kx = t + e * Tn;
+                const int w = band_slot(!S::PARTS || kx <= c ? kx : kx + 512 * (R - 1), L, c, W);
+                C v;
+                if (live && w >= 0) v = Zb[zat(pl, row, w)];
+                else { v.x = 0; v.y = 0; }
+                r[0][e] = v.x;
+                im[0][e] = v.y;
+            }
+        } else if (R == 4 && n < 4 && c < 512) {
+            // the modes of the lowest and of the highest quarter
+            C hv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int kx = t + e * Tn, kh = kx + 512 * (R - 1);
+                const int w = kx <= c ? kx : -1, wh = kh >= L - c ? W - (L - kh) : -1;
+                C v;
+                if (live && w >= 0) v = Zb[zat(pl, row, w)];
+                else { v.x = 0; v.y = 0; }
+                if (live && wh >= 0) hv[e] = Zb[zat(pl, row, wh)];
+                else { hv[e].x = 0; hv[e].y = 0; }
+                r[0][e] = v.x;
+                im[0][e] = v.y;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                turn(hv[e].x, hv[e].y, 3 * q);
+                r[0][e] += hv[e].x;
+                im[0][e] += hv[e].y;
+            }
+        } else {
+            // every other case: the first stage (output q of dft2 or dft4) at the loads
+            C hv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) r[0][e] = im[0][e] = 0;
+#pragma unroll 1
+            for (int m = 0; m < R / 2; ++m) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int kx = t + e * Tn + 512 * m;
+                    const int w = band_slot(kx, L, c, W), wh = band_slot(kx + 512 * (R / 2), L, c, W);
+                    C v;
+                    if (live && w >= 0) v = Zb[zat(pl, row, w)];
+                    else { v.x = 0; v.y = 0; }
+                    if (live && wh >= 0) hv[e] = Zb[zat(pl, row, wh)];
+                    else { hv[e].x = 0; hv[e].y = 0; }
+                    first_stage(r[0][e], im[0][e], v.x, v.y, hv[e].x, hv[e].y, q, q * m);
+                }
+            }
         }
     };
     if ((flags & RF_INVERSE) && fft_thread) load_line(g);
@@ -268,7 +354,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
             __syncthreads();
         }
     }
-    if (fft_thread && (flags & RF_INVERSE)) load_twiddles<T, LOG2L>(tw, S::TW_LDS ? twl : twg, t);
+    if (fft_thread && (flags & RF_INVERSE)) load_twiddles<T, LOG2L>(tw, S::TW_LDS ? twl : twg, R * t + q);
     int8_t* sgn = a.sgn + (size_t)b * npts;
     // previous det signs of the thread's points, a byte each (a register, not
     // an array: the projection loops index it at run time)
@@ -287,35 +373,44 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
 #pragma unroll 1
         for (int rd = 0; rd < ROUNDS; ++rd) {
             const int j = rd * G + g;
-            const bool act = fft_thread && j < S::LINES;
+            const bool act = fft_thread && j < S::LINES * R;
             if (rd > 0 && fft_thread) load_line(j);
             int rl, pl;
-            line_of(j, rl, pl);
+            line_of(j / R, rl, pl);
             const int lj = act ? rl * PL + pl : 0;
             T* lrj = lr + (size_t)lj * LP;
             T* lij = li + (size_t)lj * LP;
-            if constexpr (S::WAVE_LINE) {
+            const int part = q * (LP / R);  // the exchanges of part q
+            if constexpr (S::WAVE_LINE || S::PARTS) {
                 if (act) {
-                    // with c < L/8 only the loads e = 0, 7 hold kept modes (float, n <= 3:
+                    if (S::PARTS && c < 256) {
+                        // output q of the first stage, of one nonzero input
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (t + e * Tn > c) turn(r[0][e], im[0][e], (4 / R) * q * (R - 1));
+                    }
+                    // with c < Tn only the loads e = 0, 7 hold kept modes (float, n <= 3:
                     // the double and n = 4 instances have no registers to spare for a
                     // second copy of the transform)
-                    if constexpr (sizeof(T) == 4 && n <= 3 && FftShape<LOG2L>::R0 == 1 && FftShape<LOG2L>::NST > 1) {
-                        if (c < Tn) fft_wave<T, +1, LOG2L, 0, FFT_IN07>(r[0], im[0], lrj, lij, t, tw, true);
-                        else fft_wave<T, +1, LOG2L>(r[0], im[0], lrj, lij, t, tw, true);
+                    if constexpr (sizeof(T) == 4 && n <= 3 && FftShape<LOG2S>::R0 == 1 && FftShape<LOG2S>::NST > 1) {
+                        if (c < Tn) fft_wave<T, +1, LOG2S, 0, FFT_IN07, LOG2L>(r[0], im[0], lrj + part, lij + part, t, tw, true);
+                        else fft_wave<T, +1, LOG2S, 0, FFT_FULL, LOG2L>(r[0], im[0], lrj + part, lij + part, t, tw, true);
                     } else {
-                        fft_wave<T, +1, LOG2L>(r[0], im[0], lrj, lij, t, tw, true);
+                        fft_wave<T, +1, LOG2S, 0, FFT_FULL, LOG2L>(r[0], im[0], lrj + part, lij + part, t, tw, true);
                     }
-                    wave_lds_sync();  // the line's last exchange has been read
+                    wave_lds_sync();  // the transform's last exchange has been read
                 }
+                if constexpr (S::PARTS) __syncthreads();  // by every wave of the line
             } else {
                 fft_lines<T, +1, 1, LOG2L>(r, im, lrj, lij, 0, 1, 0, t, tw, act);
                 __syncthreads();  // the line's last exchange has been read
             }
             if (act) {
+                const int o = R * t + q, po = lds_pad(o);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    lrj[lds_pad_at<Tn>(t, pt, e)] = r[0][e];
-                    lij[lds_pad_at<Tn>(t, pt, e)] = im[0][e];
+                    lrj[lds_pad_at<R * Tn>(o, po, e)] = r[0][e];
+                    lij[lds_pad_at<R * Tn>(o, po, e)] = im[0][e];
                 }
             }
         }
@@ -742,33 +837,47 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         // values of phase 1 kept alive across the projection would raise its
         // register peak above what the kernel's occupancy allows
         Twiddles<T, LOG2L> tw3;
-        if (fft_thread) load_twiddles<T, LOG2L>(tw3, S::TW_LDS ? twl : twg, t);
+        if (fft_thread) load_twiddles<T, LOG2L>(tw3, S::TW_LDS ? twl : twg, R * t + q);
 #pragma unroll 1
         for (int rd = 0; rd < ROUNDS; ++rd) {
             const int j = rd * G + g;
-            const bool act = fft_thread && j < S::LINES;
+            const bool act = fft_thread && j < S::LINES * R;
             int rl, pl;
-            line_of(j, rl, pl);
+            line_of(j / R, rl, pl);
             const int lj = act ? rl * PL + pl : 0;
             T* lrj = lr + (size_t)lj * LP;
             T* lij = li + (size_t)lj * LP;
+            const int part = q * (LP / R);
             T r3[1][8], im3[1][8];  // fresh, as tw3
             if (act) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    r3[0][e] = lrj[lds_pad_at<Tn>(t, pt, e)];
-                    im3[0][e] = lij[lds_pad_at<Tn>(t, pt, e)];
+                    const int o = lds_pad_at<Tn>(t, pt, e);
+                    r3[0][e] = lrj[o];
+                    im3[0][e] = lij[o];
+                    if constexpr (R > 1) {
+                        constexpr int H = LP / 2;
+                        T xr = r3[0][e], xi = im3[0][e];
+                        r3[0][e] = im3[0][e] = 0;
+                        first_stage(r3[0][e], im3[0][e], xr, xi, lrj[o + H], lij[o + H], q, 0);
+                        if constexpr (R == 4)
+                            first_stage(r3[0][e], im3[0][e], lrj[o + H / 2], lij[o + H / 2], lrj[o + 3 * H / 2],
+                                        lij[o + 3 * H / 2], q, -q);
+                    }
                 }
             }
-            if constexpr (S::WAVE_LINE) {
+            if constexpr (S::WAVE_LINE || S::PARTS) {
+                // every lane (of a line in parts, every wave) has read its elements
+                // before the exchanges
+                if constexpr (S::PARTS) __syncthreads();
                 if (act) {
-                    wave_lds_sync();  // every lane has read its elements before the exchanges
-                    // with c < L/8 only the modes e = 0, 7 are stored
-                    if constexpr (sizeof(T) == 4 && n <= 3 && FftShape<LOG2L>::NST > 1) {
-                        if (c < Tn) fft_wave<T, -1, LOG2L, 0, FFT_OUT07>(r3[0], im3[0], lrj, lij, t, tw3, true);
-                        else fft_wave<T, -1, LOG2L>(r3[0], im3[0], lrj, lij, t, tw3, true);
+                    if constexpr (S::WAVE_LINE) wave_lds_sync();
+                    // with c < R Tn only the modes e = 0, 7 are stored
+                    if constexpr (sizeof(T) == 4 && n <= 3 && FftShape<LOG2S>::NST > 1) {
+                        if (c < R * Tn) fft_wave<T, -1, LOG2S, 0, FFT_OUT07, LOG2L, IMF>(r3[0], im3[0], lrj + part, lij + part, t, tw3, true);
+                        else fft_wave<T, -1, LOG2S, 0, FFT_FULL, LOG2L, IMF>(r3[0], im3[0], lrj + part, lij + part, t, tw3, true);
                     } else {
-                        fft_wave<T, -1, LOG2L>(r3[0], im3[0], lrj, lij, t, tw3, true);
+                        fft_wave<T, -1, LOG2S, 0, FFT_FULL, LOG2L, IMF>(r3[0], im3[0], lrj + part, lij + part, t, tw3, true);
                     }
                 }
             } else {
@@ -780,7 +889,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                 // take mode L - W + w
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const int kx = t + e * Tn;
+                    const int kx = R * (t + e * Tn) + q;
                     C v;
                     v.x = r3[0][e];
                     v.y = im3[0][e];
