@@ -1234,11 +1234,21 @@ __device__ __forceinline__ void heat_fast_body(const FastColArgs& a)
     }
     fft_lines<T, -1, 1, LOG2L>(r, im, lr, li, 0, TX, cc, t, tw);
     if (a.epart) {
-        // this thread's eight terms in the plan's precision, the wave's sum in double
-        T acc = 0;
+        // this thread's eight terms in the plan's precision (a.wide: in double), the
+        // wave's sum in double
+        double part;
+        if (sizeof(T) == 4 && a.wide) {
+            part = 0.0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc += lam[e] * (r[0][e] * r[0][e] + im[0][e] * im[0][e]);
-        const double s = wave_sum((double)acc);
+            for (int e = 0; e < 8; ++e)
+                part += (double)lam[e] * ((double)r[0][e] * (double)r[0][e] + (double)im[0][e] * (double)im[0][e]);
+        } else {
+            T acc = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc += lam[e] * (r[0][e] * r[0][e] + im[0][e] * im[0][e]);
+            part = (double)acc;
+        }
+        const double s = wave_sum(part);
         const int slot = a.slot >= 0 ? a.slot : a.stop_iter[b];
         if ((tid & 63) == 0)
             a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + wg * (blockDim.x >> 6) + (tid >> 6)] = s;
@@ -1432,13 +1442,14 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
 #pragma unroll
     for (int h = 0; h < 2; ++h) lyv[h] = ly[gz + h * (NY / 2)];
     if (a.epart) {
-        // this thread's terms in the plan's precision, the wave's sum in double
-        T acc = 0;
+        double acc = 0.0;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc += (lzv[e] * lyv[h]) * (r[h][e] * r[h][e] + im[h][e] * im[h][e]);
-        const double sum = wave_sum(live ? (double)acc : 0.0);
+            for (int e = 0; e < 8; ++e)
+                acc += (double)(lzv[e] * lyv[h]) *
+                       ((double)r[h][e] * (double)r[h][e] + (double)im[h][e] * (double)im[h][e]);
+        const double sum = wave_sum(live ? acc : 0.0);
         const int slot = a.slot >= 0 ? a.slot : a.stop_iter[b];
         if ((threadIdx.x & 63) == 0)
             a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + (int64_t)blockIdx.x * (S::THREADS >> 6) +

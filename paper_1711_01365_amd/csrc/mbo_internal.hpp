@@ -478,6 +478,7 @@ struct FastColArgs {
     const unsigned long long* delta_bits;  // nullable
     double tol;
     int apply;               // 1: multiply and transform back (heat step); 0: energy only
+    int wide;                // 2-D float: the energy's terms in double (the calls whose general passes sum so)
     // the 3-D plane pass (L = N0 is the z axis): the y axis, its twiddles and
     // heat factor [Ny] exp(-4 pi^2 tau ky^2) / Ny
     int Ny;
