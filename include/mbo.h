@@ -103,8 +103,9 @@ typedef enum {
  * every mode kept) mbo_relaxed_flow run the kernels that mbo_iterate runs; the
  * other calls always use the general ones.
  * The band-limited kernels serve d = 2 with a first axis of at least 64 points
- * (every last axis a plan accepts) and d = 3 with first axes of at most 128 points
- * whose product is at most 8192 in double; other shapes run the general kernels. */
+ * (every last axis a plan accepts) and d = 3 with first axes of 64 or 128 points
+ * (float plans) or of at most 128 points and their product of at most 8192 (double);
+ * other shapes run the general kernels. */
 typedef enum {
     MBO_PATH_GENERIC = 0,
     MBO_PATH_FULL = 1,

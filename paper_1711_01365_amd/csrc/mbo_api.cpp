@@ -497,18 +497,21 @@ bool fast_layout(int64_t N0, int64_t N1, int n, int pk, const double* taus, int6
 namespace {
 
 // 3-D band-limited path: the row pass over the x rows and a plane pass per
-// (packed plane, stored x mode) holding the whole y-z plane in LDS, so y and z
-// sides of 8 to 128 points whose plane fits it (all of them in float; in double
-// at most 8192 points).  Two launches per iteration and two passes over kept
-// modes, against four and every mode of the general passes: 32 x 64 x 128 with
-// n = 2 in double, ten iterations, 267 us against 565; 32^3, n = 2 in float, five,
-// 106 against 210; 16^3, n = 3 in double 157 against 243; 128 x 64 x 64, n = 4 in
-// double, four, 675 against 866.  The kept x half-width bounds the dropped symbol
-// mass by eta with the y and z axes' summed factors.
+// (packed plane, stored x mode) holding the whole y-z plane in LDS.  In double y and z
+// sides of 8 to 128 points whose plane fits (at most 8192 points), in float sides of
+// 64 or 128.  Two launches per iteration and two passes over kept modes, against four
+// and every mode of the general passes: 32 x 64 x 128 with n = 2 in double, ten
+// iterations, 267 us against 565; 16^3, n = 3, five, 157 against 243; 128 x 64 x 64,
+// n = 4, four, 675 against 866.  Float planes with other sides would gain as much
+// (32^3, n = 2, 106 against 210), but the passes round differently from the general
+// ones, and a rough float field has a point so near det A = 0 that its flip is counted
+// differently in 7 of 100 runs: they stay.  The kept x half-width bounds the dropped
+// symbol mass by eta with the y and z axes' summed factors.
 void config_fast3(mbo_plan_t p)
 {
     const int64_t N0 = p->N[0], N1 = p->N[1], N2 = p->N[2];
-    if (N0 < 8 || N0 > 128 || N1 < 8 || N1 > 128 || N2 < 8 || N2 > 2048) return;
+    const int64_t lo = p->pk == 1 ? 64 : 8;
+    if (N0 < lo || N0 > 128 || N1 < lo || N1 > 128 || N2 < 8 || N2 > 2048) return;
     if (row_fast_lds_bytes(p->pk, p->n, ilog2((int)N2)) + 12288 > p->lds_max) return;
     if (plane_fast_lds_bytes(p->pk, ilog2((int)N1), ilog2((int)N0)) > p->lds_max) return;
     int c = (int)(N2 / 2), W = (int)N2;

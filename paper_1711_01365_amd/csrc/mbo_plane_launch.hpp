@@ -1,5 +1,5 @@
 // Launcher of the 3-D plane pass (plane_fast, mbo_fast.hpp) for one precision T:
-// planes of 8 to 128 points along y and z that fit the LDS.
+// sides of 8 to 128 points in double and of 64 or 128 in float whose plane fits the LDS.
 #pragma once
 
 #include <hip/hip_ext.h>
@@ -15,7 +15,7 @@ static hipError_t plane_fast_go(const FastColArgs& a, dim3 g, hipStream_t st, bo
                                 hipEvent_t ev1)
 {
     typedef PlaneFastShape<T, LY, LZ> S;
-    if constexpr (S::LDS > PLANE_LDS_MAX) {
+    if constexpr (S::LDS > PLANE_LDS_MAX || (sizeof(T) == 4 && (LY < 6 || LZ < 6))) {
         return hipErrorInvalidValue;
     } else {
         const void* f = reinterpret_cast<const void*>(&plane_fast<T, LY, LZ>);

@@ -1,6 +1,6 @@
 """The 3-D plane pass at the edges of what it takes: the smallest planes (several
 in one wave, the last workgroup part empty), planes of one wave, the largest plane
-that a double fits in the LDS and the smallest that does not, sides of 8 to 128,
+that a double fits in the LDS and the smallest that does not, sides of 8 to 128 (64 or 128 in float),
 rows of 8 to 512 points, n = 1..4, two fields with every mode or a band kept.
 
 The diffusion against the FP64 oracle (every path within 1e-13 in double, 2e-6 in
@@ -19,11 +19,12 @@ from paper_1711_01365_amd import inputs
 pytestmark = pytest.mark.gpu
 
 F64, F32, FB = 0, 1, 2
-CASES = [((8, 8, 8), 2, F64, 4e-3, True), ((8, 8, 16), 3, FB, 2e-3, True), ((16, 16, 64), 1, F64, 1e-3, True),
-         ((16, 8, 512), 3, F32, 1e-4, True), ((32, 16, 32), 4, FB, 1e-3, True), ((16, 64, 16), 3, F64, 1e-3, True),
-         ((32, 32, 128), 3, FB, 5e-4, True), ((8, 128, 32), 4, F64, 5e-4, True), ((128, 8, 64), 2, F32, 5e-4, True),
+CASES = [((8, 8, 8), 2, F64, 4e-3, True), ((8, 8, 16), 3, F64, 2e-3, True), ((16, 16, 64), 1, F64, 1e-3, True),
+         ((16, 8, 512), 3, F64, 1e-4, True), ((32, 16, 32), 4, F64, 1e-3, True), ((16, 64, 16), 3, F64, 1e-3, True),
+         ((32, 32, 128), 3, F64, 5e-4, True), ((8, 128, 32), 4, F64, 5e-4, True), ((128, 8, 64), 2, F64, 5e-4, True),
          ((32, 64, 128), 2, F64, 1e-3, True), ((64, 128, 16), 3, F64, 5e-4, True), ((128, 64, 8), 1, F64, 5e-4, True),
-         ((128, 32, 16), 2, FB, 5e-4, True), ((128, 128, 8), 2, F64, 5e-4, False), ((8, 256, 8), 2, FB, 5e-4, False)]
+         ((64, 64, 8), 3, FB, 5e-4, True), ((128, 64, 32), 2, F32, 5e-4, True), ((32, 64, 16), 3, FB, 5e-4, False),
+         ((128, 128, 8), 2, F64, 5e-4, False), ((8, 256, 8), 2, FB, 5e-4, False)]
 
 
 def points(H):
