@@ -1442,14 +1442,13 @@ __global__ void __launch_bounds__((PlaneFastShape<T, LOG2Y, LOG2Z>::THREADS)) pl
 #pragma unroll
     for (int h = 0; h < 2; ++h) lyv[h] = ly[gz + h * (NY / 2)];
     if (a.epart) {
-        double acc = 0.0;
+        // this thread's terms in the plan's precision, the wave's sum in double
+        T acc = 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                acc += (double)(lzv[e] * lyv[h]) *
-                       ((double)r[h][e] * (double)r[h][e] + (double)im[h][e] * (double)im[h][e]);
-        const double sum = wave_sum(live ? acc : 0.0);
+            for (int e = 0; e < 8; ++e) acc += (lzv[e] * lyv[h]) * (r[h][e] * r[h][e] + im[h][e] * im[h][e]);
+        const double sum = wave_sum(live ? (double)acc : 0.0);
         const int slot = a.slot >= 0 ? a.slot : a.stop_iter[b];
         if ((threadIdx.x & 63) == 0)
             a.epart[((int64_t)b * (a.K + 1) + slot) * a.nwg + (int64_t)blockIdx.x * (S::THREADS >> 6) +
