@@ -1349,9 +1349,9 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
         r.iter = s;
         r.K = K;
         r.cnt_part = p->cnt_part;
-        r.flags = RF_INVERSE | fb;
+        // Q goes to the field at every step: volume_fix turns the moved points from it
+        r.flags = RF_INVERSE | RF_STORE_REAL | fb;
         if (s < K || want_energy) r.flags |= RF_FORWARD;
-        if (s == K) r.flags |= RF_STORE_REAL;
         if ((e = launch_row_fast_vkey(p->pk, p->n, ilog2((int)p->N[1]), r, rg, st)) != hipSuccess) return e;
         if ((e = launch_select_list(p->pk, sa, (int)p->batch, st)) != hipSuccess) return e;
         VolFixArgs f;

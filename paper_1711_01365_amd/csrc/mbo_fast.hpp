@@ -972,9 +972,9 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS),
 // the candidate of the other determinant, T = Q - 2 u v^t (Lemma 7.1).  Few do:
 // the selection moves the cut only as far as the volume drifted in one step.
 // Each of them is read back from the kept row modes by a direct sum (16 lanes
-// per point), the change T - Q is formed by vp_change and added to
-// the row spectra that row_fast_vkey wrote, again by direct sums over the kept
-// modes.  Rows without such points end after reading Delta E and the det signs.
+// per point), the change T - Q is formed by vp_change from Q as row_fast_vkey left
+// it in the field, and added to the row spectra that row_fast_vkey wrote, again by
+// direct sums over the kept modes.  Rows without such points end after reading Delta E and the det signs.
 // Bound by its chain of memory round trips (flags, spectra, projection, spectra),
 // not by the 300 to 660 points in 140 to 230 rows that it treats: 13 us at 512^2,
 // n = 3 in float, where transforming every row again took 27.
@@ -1110,11 +1110,10 @@ __global__ void __launch_bounds__((VolumeFixShape<T, n>::NT), (VolumeFixShape<T,
                 for (int k = 0; k < 2 * PL; ++k) av[k] += __shfl_xor(av[k], o, 64);
             const T di = vde[i];
             T d[NN], q[NN];
-            const bool last = (a.flags & RF_STORE_REAL) != 0;  // row_fast_vkey stored Q
 #pragma unroll
-            for (int k = 0; k < NN; ++k) q[k] = last ? Aout[(int64_t)k * a.npts + p0 + i] : (T)0;
-            vp_change<T, n>(av, !(bool)__builtin_signbit(di), di, fallback, a.sigma_fb, q, last, d);
-            if (last && lane == 0) {
+            for (int k = 0; k < NN; ++k) q[k] = Aout[(int64_t)k * a.npts + p0 + i];
+            vp_change<T, n>(av, !(bool)__builtin_signbit(di), di, fallback, a.sigma_fb, q, d);
+            if (lane == 0) {
 #pragma unroll
                 for (int k = 0; k < NN; ++k) Aout[(int64_t)k * a.npts + p0 + i] = q[k];
             }

@@ -188,19 +188,16 @@ __device__ __forceinline__ bool vp_point(const T* a, T* tp, T* tm, T& de, bool f
     return false;
 }
 
-// The change of a point that moves to the other determinant, d = T' - Q =
-// -2 u v^t with (u, v) the singular pair of sigma_min (Lemma 7.1), n = 3, 4.
-// cof(A) = det(A) A^{-t} has the singular vectors of A, and its largest singular
-// value belongs to that pair: the powers of cof^t cof (squared until they have
-// rank one, at most 60 times: two or three do where sigma_n is small) converge to
-// v v^t, and u = s cof v / |cof v|, s the side (sign of the determinant) that the
-// point leaves.  Where sigma_n = sigma_{n-1} to rounding, every direction between
-// their vectors is a closest choice, and the power's largest column is one.
-// have_q: q is Q as it was formed before; then u = q v, so that T' =
-// q (I - 2 v v^t) is as orthogonal as q.  False, d unset, when the cofactors are
-// no more than rounding (rank <= n - 2): the candidates then come from the SVD.
+// The direction v along which a point that moves to the other determinant turns
+// back (Lemma 7.1: T' = Q (I - 2 v v^t), v the right singular vector of sigma_min),
+// n = 3, 4.  cof(A) = det(A) A^{-t} has the singular vectors of A, and its largest
+// singular value belongs to that vector: the powers of cof^t cof (squared until they
+// have rank one, at most 60 times: two or three do where sigma_n is small) converge
+// to v v^t.  Where sigma_n = sigma_{n-1} to rounding, every direction between their
+// vectors is a closest choice, and the power's largest column is one.  False, v
+// unset, when the cofactors are no more than rounding (rank <= n - 2).
 template <typename T, typename Tio, int n>
-__device__ __forceinline__ bool vp_flip(const Tio* a_in, bool plus, const Tio* q, bool have_q, Tio* d)
+__device__ __forceinline__ bool vp_direction(const Tio* a_in, T* v)
 {
     const int ex = scale_exponent<Tio, n>(a_in);
     T a[n * n], C[n * n], M[n * n];
@@ -247,7 +244,6 @@ __device__ __forceinline__ bool vp_flip(const Tio* a_in, bool plus, const Tio* q
     }
     // v: the column with the largest diagonal entry, refined by one more product
     // with cof^t cof (its rounding is then that of one product, not of the powers)
-    T v[n];
     T best = M[0];
 #pragma unroll
     for (int i = 0; i < n; ++i) v[i] = M[i * n];
@@ -258,7 +254,7 @@ __device__ __forceinline__ bool vp_flip(const Tio* a_in, bool plus, const Tio* q
 #pragma unroll
         for (int i = 0; i < n; ++i) v[i] = more ? M[i * n + j] : v[i];
     }
-    T u[n], vv = 0, uu = 0;
+    T u[n], vv = 0;
 #pragma unroll
     for (int i = 0; i < n; ++i) {
         T m = 0;
@@ -278,52 +274,87 @@ __device__ __forceinline__ bool vp_flip(const Tio* a_in, bool plus, const Tio* q
     const T iv = num<T>::rsq(vv);
 #pragma unroll
     for (int i = 0; i < n; ++i) v[i] *= iv;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-        T m = 0;
-#pragma unroll
-        for (int k = 0; k < n; ++k) m += (have_q ? (T)q[i * n + k] : C[i * n + k]) * v[k];
-        u[i] = m;
-        uu += m * m;
-    }
-    if (!(uu > (T)0)) return false;
-    const T iu = have_q ? (T)-2 : (plus ? (T)-2 : (T)2) * num<T>::rsq(uu);
-#pragma unroll
-    for (int i = 0; i < n; ++i)
-#pragma unroll
-        for (int k = 0; k < n; ++k) d[i * n + k] = (Tio)(iu * u[i] * v[k]);
     return true;
 }
 
-// A point of matrix a that leaves the side `plus` (its Delta E is de): the change
-// d = T' - Q, in the plan's precision T with the double fallback of float plans.
-// have_q: q holds Q on entry; T' on return.
+// The same from the SVD, for rank <= n - 2 (the zero matrix gives the first axis).
 template <typename T, int n>
-__device__ __forceinline__ void vp_change(const T* a, bool plus, T de, bool fallback, double sigma_fb, T* q,
-                                          bool have_q, T* d)
+__device__ __forceinline__ void vp_direction_svd(const T* a, T* v)
+{
+    const int ex = scale_exponent<T, n>(a);
+    T W[n][n], V[n][n];
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            W[i][j] = ldexp(a[i * n + j], -ex);
+            V[i][j] = (i == j) ? (T)1 : (T)0;
+        }
+    jacobi_sweeps<T, n>(W, V);
+    T sm = 0;
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+        T w2 = 0;
+#pragma unroll
+        for (int i = 0; i < n; ++i) w2 += W[i][j] * W[i][j];
+        const bool less = j == 0 || w2 < sm;
+        sm = less ? w2 : sm;
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = less ? V[i][j] : v[i];
+    }
+}
+
+// d = -2 (q v) v^t, in the precision of v.
+template <typename T, typename Tio, int n>
+__device__ __forceinline__ void vp_turn(const Tio* q, const T* v, Tio* d)
+{
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+        T u = 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) u += (T)q[i * n + k] * v[k];
+#pragma unroll
+        for (int k = 0; k < n; ++k) d[i * n + k] = (Tio)((T)-2 * u * v[k]);
+    }
+}
+
+// A point of matrix a that leaves the side `plus` (its Delta E is de): d = T' - Q, and
+// T' in q's place, in the plan's precision T with the double fallback of float plans.
+// q is the very Q that stands in the spectra to which d is added: a Q formed again
+// from a (read back by another sum) is another one where sigma_{n-1} + sigma_n is
+// small, by eps / (sigma_{n-1} + sigma_n) of a turn, and Q + d would be as far from
+// orthogonal.  With v alone taken from a, T' is as orthogonal as q wherever v points.
+template <typename T, int n>
+__device__ __forceinline__ void vp_change(const T* a, bool plus, T de, bool fallback, double sigma_fb, T* q, T* d)
 {
     if constexpr (n >= 3) {
-        bool done;
-        if constexpr (sizeof(T) == 4) {
-            const T half = (de < (T)0 ? -de : de) * (T)0.5;
-            done = fallback && (double)half < sigma_fb ? vp_flip<double, T, n>(a, plus, q, have_q, d)
-                                                       : vp_flip<T, T, n>(a, plus, q, have_q, d);
+        const T half = (de < (T)0 ? -de : de) * (T)0.5;
+        bool done = false;
+        if (sizeof(T) == 4 && fallback && (double)half < sigma_fb) {
+            double v[n];
+            done = vp_direction<double, T, n>(a, v);
+            if (done) vp_turn<double, T, n>(q, v, d);
         } else {
-            done = vp_flip<T, T, n>(a, plus, q, have_q, d);
+            T v[n];
+            done = vp_direction<T, T, n>(a, v);
+            if (done) vp_turn<T, T, n>(q, v, d);
         }
-        if (done) {
-#pragma unroll
-            for (int k = 0; k < n * n; ++k) q[k] += d[k];
-            return;
+        if (!done) {
+            T v[n];
+            vp_direction_svd<T, n>(a, v);
+            vp_turn<T, T, n>(q, v, d);
         }
-    }
-    T tp[n * n], tm[n * n], e;
-    // n >= 3: the polar factor is not unique there, in any precision
-    (void)vp_point<T, n>(a, tp, tm, e, n <= 2 && fallback, sigma_fb);
 #pragma unroll
-    for (int k = 0; k < n * n; ++k) {
-        d[k] = plus ? tm[k] - tp[k] : tp[k] - tm[k];
-        q[k] = plus ? tm[k] : tp[k];
+        for (int k = 0; k < n * n; ++k) q[k] += d[k];
+    } else {
+        T tp[n * n], tm[n * n], e;
+        (void)vp_point<T, n>(a, tp, tm, e, fallback, sigma_fb);
+#pragma unroll
+        for (int k = 0; k < n * n; ++k) {
+            const T t = plus ? tm[k] : tp[k];
+            d[k] = t - q[k];
+            q[k] = t;
+        }
     }
 }
 
