@@ -214,6 +214,8 @@ struct mbo_plan_s {
     unsigned long long* vkey = nullptr;  // [batch][npts] listed keys
     unsigned* vcnt = nullptr;            // [batch] listed points
     unsigned* vidx = nullptr;            // [batch][npts] their indices
+    unsigned* vhist2 = nullptr;          // [batch][SEL_HIST2] second histogram
+    unsigned* vover = nullptr;           // [batch] whether it was taken
     // relaxed flows: cached graph of mbo_relaxed_flow, penalty partials
     hipGraphExec_t rexec = nullptr;
     void* rg_A = nullptr;
@@ -1257,8 +1259,8 @@ hipError_t enqueue_volume_step(mbo_plan_t p, int load_flags, const void* Ain, vo
 }
 
 // Workspace of the band-limited volume-preserving iteration (2-D), one
-// allocation: the second set of row spectra, then the listed keys, their counts
-// and indices.
+// allocation: the second set of row spectra, then the listed keys, the counts,
+// second histograms and marks of the selection, and the listed indices.
 mbo_status ensure_volume_fast(mbo_plan_t p)
 {
     const size_t B = (size_t)p->batch, np = B * (size_t)p->npts;
@@ -1271,11 +1273,14 @@ mbo_status ensure_volume_fast(mbo_plan_t p)
     std::memset(&r, 0, sizeof r);
     (void)launch_row_fast_vkey(p->pk, p->n, ilog2((int)p->N[1]), r, dim3(1), nullptr, true);
     (void)hipGetLastError();
-    HIP_TRY(p, hipMalloc(&p->vz, zb + np * 8 + (np + B) * 4));
+    const size_t words = B + B * SEL_HIST2 + B;  // counts, histograms, marks
+    HIP_TRY(p, hipMalloc(&p->vz, zb + np * 8 + (words + np) * 4));
     p->vkey = reinterpret_cast<unsigned long long*>(static_cast<char*>(p->vz) + zb);
     p->vcnt = reinterpret_cast<unsigned*>(p->vkey + np);
-    p->vidx = p->vcnt + B;
-    HIP_TRY(p, launch_fill_i32(reinterpret_cast<int*>(p->vcnt), (int64_t)B, 0, p->stream));
+    p->vhist2 = p->vcnt + B;
+    p->vover = p->vhist2 + B * SEL_HIST2;
+    p->vidx = p->vover + B;
+    HIP_TRY(p, launch_fill_i32(reinterpret_cast<int*>(p->vcnt), (int64_t)words, 0, p->stream));
     p->vz_bytes = zb;
     return MBO_OK;
 }
@@ -1337,6 +1342,8 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
     sa.key = p->vkey;
     sa.idx = p->vidx;
     sa.count = p->vcnt;
+    sa.hist2 = p->vhist2;
+    sa.over = p->vover;
     void *Zin = p->Z, *Zout = p->vz;
     const dim3 rg((unsigned)fast_row_groups(p), (unsigned)p->batch);
     for (int s = first; s <= K; ++s) {

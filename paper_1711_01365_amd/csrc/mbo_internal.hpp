@@ -227,15 +227,18 @@ struct SelArgs {
     uint8_t* mask;           // launch_sel_mark: 1 = selected [batch][npts]
 };
 hipError_t launch_select(int prec, const SelArgs& a, int batch, hipStream_t st);
-// The same selection in three launches, for Delta E values whose cut falls where
-// the values are spread out (along the volume-preserving iteration, near zero):
-// the histogram of the top digit, the points of the digit holding the cut
-// listed (key and index), and one workgroup that ends the search among them.
+// The same selection in three launches: the histogram of the top digit, the points of
+// the digit holding the cut listed (key and index) where they are few, and one
+// workgroup that ends the search among them; where they are many, the second launch
+// takes the histogram of the next digit and the third lists the points of both.
+constexpr int SEL_HIST2 = (1 << 13) + (1 << SEL_BITS);  // bins of the second and the third histogram
 struct SelListArgs {
     SelArgs s;
     unsigned long long* key;  // [batch][npts] keys of the listed points
     unsigned* idx;            // [batch][npts] their point indices
     unsigned* count;          // [batch] listed points, zero between uses
+    unsigned* hist2;          // [batch][SEL_HIST2] further histograms, zero between uses
+    unsigned* over;           // [batch] whether the second histogram was taken
 };
 hipError_t launch_select_list(int prec, const SelListArgs& a, int batch, hipStream_t st);
 hipError_t launch_sel_mark(int prec, const SelArgs& a, int batch, hipStream_t st);

@@ -14,15 +14,17 @@
 // holding the last selected one give its index istar (sel_tie).  Every kernel
 // reads the selection state first and returns at once when its field needs no
 // more work.
+#include <algorithm>
 #include <climits>
 
 #include "mbo_kernels.hpp"
 
 namespace mbo {
 
-// Inclusive scan over a 256-thread workgroup (four waves); total receives the
-// sum over the workgroup.  Every thread must call it.
-__device__ __forceinline__ long long scan256(long long v, long long* sh /* >= 4 */, long long& total)
+// Inclusive scan over a workgroup of NT threads; total receives the sum over the
+// workgroup.  Every thread must call it.
+template <int NT>
+__device__ __forceinline__ long long scan_wg(long long v, long long* sh /* >= NT / 64 */, long long& total)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
@@ -32,11 +34,21 @@ __device__ __forceinline__ long long scan256(long long v, long long* sh /* >= 4 
     }
     if (lane == 63) sh[w] = v;
     __syncthreads();
-    long long add = 0;
-    for (int i = 0; i < w; ++i) add += sh[i];
-    total = sh[0] + sh[1] + sh[2] + sh[3];
+    long long add = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) {
+        const long long x = sh[i];
+        add += i < w ? x : 0;
+        all += x;
+    }
+    total = all;
     __syncthreads();  // sh is free for the next call
     return v + add;
+}
+
+__device__ __forceinline__ long long scan256(long long v, long long* sh, long long& total)
+{
+    return scan_wg<256>(v, sh, total);
 }
 
 template <typename T>
@@ -246,10 +258,100 @@ __global__ void __launch_bounds__(256) sel_tie(const SelArgs a)
 // ---------------------------------------------------------------------------
 // The three-launch selection (SelListArgs)
 // ---------------------------------------------------------------------------
+// Where the cut falls among values that are spread out, as along the iteration once
+// the volume has settled, the first digit holds some thousand points: they are listed
+// and one workgroup ends the search among them.  Where it falls in the bulk (rough
+// data whose domains diffuse away) the digit holds a large part of the field, which one
+// workgroup would read again for every digit.  Above SEL_LIST_LDS points nothing is
+// listed; the same launches take one more digit of SEL_BITS2 bits over the whole grid
+// and, of as many points again, a third, and only the points of these digits are read
+// by the one workgroup.  One iteration of 2048^2, n = 2 in float, 2 % of the points
+// flipped at random: 0.60 ms, listing them all 19.6, by the general passes 0.63; with
+// every value equal the selection alone takes 0.6 ms.
+constexpr unsigned SEL_LIST_LDS = 8192;
+constexpr int SEL_BITS2 = 13;
+constexpr int SEL_NTF = 512;  // threads of sel_finish: large lists 6 to 10 % faster than with 256 or 1024, small ones alike
+constexpr int SEL_NB2 = 1 << SEL_BITS2;
+static_assert(SEL_NB2 + (1 << SEL_BITS) == SEL_HIST2, "the second and the third histogram");
+
+// Search of a histogram of per * NT bins, from the top: the digit at which the running
+// count reaches need, the rank within it and its points.  c: the thread's bins, the
+// first at hi, downwards.  Every thread calls it.
+template <int NT, int per>
+__device__ __forceinline__ void sel_pick(const unsigned (&c)[per], int hi, long long need, long long* sh, int& s_digit,
+                                            long long& s_need, unsigned& s_count)
+{
+    long long sum = 0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) sum += c[i];
+    long long total;
+    const long long incl = scan_wg<NT>(sum, sh, total);
+    const long long excl = incl - sum;
+    if (excl < need && need <= incl) {  // exactly one thread
+        long long acc = excl;
+        int d = hi;
+        unsigned n = 0;
+#pragma unroll
+        for (int i = 0; i < per; ++i) {
+            n = c[i];
+            if (acc + (long long)c[i] >= need) {
+                d = hi - i;
+                break;
+            }
+            acc += c[i];
+        }
+        s_digit = d;
+        s_need = need - acc;
+        s_count = n;
+    }
+    __syncthreads();
+}
+
+// The values of a chunk (NT threads), every load in flight at once.
+template <int NT, typename T>
+__device__ __forceinline__ void sel_load(const T* v, int64_t x0, int64_t npts, T (&val)[SEL_CHUNK / NT])
+{
+#pragma unroll
+    for (int k = 0; k < SEL_CHUNK / NT; ++k) {
+        const int64_t x = x0 + (int64_t)k * NT;
+        val[k] = x < npts ? v[x] : (T)0;
+    }
+}
+
+// Appends the chunk's points with (key >> shift) == pre to the field's list, in no
+// particular order.  Every thread calls it; s_cnt is zero before.
+template <int NT, typename T>
+__device__ __forceinline__ void sel_append(const SelListArgs& la, int b, const T (&val)[SEL_CHUNK / NT], int64_t x0,
+                                           int shift, unsigned long long pre, unsigned& s_cnt, unsigned& s_base)
+{
+    const int64_t npts = la.s.npts;
+    unsigned mine = 0;
+#pragma unroll
+    for (int k = 0; k < SEL_CHUNK / NT; ++k)
+        mine += (x0 + (int64_t)k * NT < npts && (vp_key(val[k]) >> shift) == pre) ? 1u : 0u;
+    unsigned at = mine ? atomicAdd(&s_cnt, mine) : 0u;
+    __syncthreads();
+    if (s_cnt == 0u) return;  // uniform
+    if (threadIdx.x == 0) s_base = atomicAdd(la.count + b, s_cnt);
+    __syncthreads();
+    at += s_base;
+    unsigned long long* lk = la.key + (size_t)b * npts;
+    unsigned* li = la.idx + (size_t)b * npts;
+#pragma unroll
+    for (int k = 0; k < SEL_CHUNK / NT; ++k) {
+        const int64_t x = x0 + (int64_t)k * NT;
+        const unsigned long long key = vp_key(val[k]);
+        if (x < npts && (key >> shift) == pre) {
+            lk[at] = key;
+            li[at] = (unsigned)x;
+            ++at;
+        }
+    }
+}
 
 // The digit holding the cut, found by every workgroup for itself from the
 // histogram (8 KB; one launch fewer than a pick kernel), then the chunk's points
-// of that digit appended to the field's list, in no particular order.
+// of that digit listed, or their next digit added to the second histogram.
 template <typename T>
 __global__ void __launch_bounds__(256) sel_list(const SelListArgs la, int shift)
 {
@@ -257,7 +359,8 @@ __global__ void __launch_bounds__(256) sel_list(const SelListArgs la, int shift)
     __shared__ long long sh[4];
     __shared__ long long s_need;
     __shared__ int s_digit;
-    __shared__ unsigned s_cnt, s_base;
+    __shared__ unsigned s_count, s_cnt, s_base;
+    __shared__ unsigned h2[SEL_NB2];
     const int b = blockIdx.y, tid = threadIdx.x;
     const long long np = a.nplus[b];
     VpSel* st = a.st + b;
@@ -268,164 +371,328 @@ __global__ void __launch_bounds__(256) sel_list(const SelListArgs la, int shift)
             st->need = 0;
             st->ties = 0;
             st->istar = -1;
+            la.over[b] = 0u;
         }
         return;
     }
-    // every load of the chunk in flight while the histogram is scanned
+    // the chunk's loads in flight while the histogram is scanned
     const T* v = reinterpret_cast<const T*>(a.dE) + (size_t)b * a.npts;
     const int64_t x0 = (int64_t)blockIdx.x * SEL_CHUNK + tid;
     T val[SEL_PER];
-#pragma unroll
-    for (int k = 0; k < SEL_PER; ++k) {
-        const int64_t x = x0 + (int64_t)k * 256;
-        val[k] = x < a.npts ? v[x] : (T)0;
-    }
+    sel_load<256>(v, x0, a.npts, val);
     const unsigned* g = a.hist + (size_t)b * (1 << SEL_BITS);
     constexpr int per = (1 << SEL_BITS) / 256;
     const int hi = (1 << SEL_BITS) - 1 - tid * per;
     unsigned c[per];
-    long long sum = 0;
 #pragma unroll
-    for (int i = 0; i < per; ++i) {
-        c[i] = g[hi - i];
-        sum += c[i];
-    }
+    for (int i = 0; i < per; ++i) c[i] = g[hi - i];
     if (tid == 0) s_cnt = 0u;
-    long long total;
-    const long long incl = scan256(sum, sh, total);
-    const long long excl = incl - sum;
-    if (excl < np && np <= incl) {  // exactly one thread
-        long long acc = excl;
-        int d = hi;
-#pragma unroll
-        for (int i = 0; i < per; ++i) {
-            if (acc + (long long)c[i] >= np) {
-                d = hi - i;
-                break;
-            }
-            acc += c[i];
-        }
-        s_digit = d;
-        s_need = np - acc;
-    }
-    __syncthreads();
+    sel_pick<256>(c, hi, np, sh, s_digit, s_need, s_count);
     const unsigned long long digit = (unsigned long long)s_digit;
+    const bool over = s_count > SEL_LIST_LDS;
     if (blockIdx.x == 0 && tid == 0) {
         st->kstar = digit << shift;
         st->need = s_need;
         st->mode = VS_SEARCH;
         st->istar = -1;
+        la.over[b] = over ? 1u : 0u;
     }
-    unsigned mine = 0;
-#pragma unroll
-    for (int k = 0; k < SEL_PER; ++k)
-        mine += (x0 + (int64_t)k * 256 < a.npts && (vp_key(val[k]) >> shift) == digit) ? 1u : 0u;
-    unsigned at = mine ? atomicAdd(&s_cnt, mine) : 0u;
+    if (!over) {  // uniform
+        sel_append<256>(la, b, val, x0, shift, digit, s_cnt, s_base);
+        return;
+    }
+    for (int i = tid; i < SEL_NB2; i += 256) h2[i] = 0u;
     __syncthreads();
-    if (s_cnt == 0u) return;  // uniform
-    if (tid == 0) s_base = atomicAdd(la.count + b, s_cnt);
-    __syncthreads();
-    at += s_base;
-    unsigned long long* lk = la.key + (size_t)b * a.npts;
-    unsigned* li = la.idx + (size_t)b * a.npts;
+    unsigned bin = 0u, run = 0u;  // equal digits that follow each other count once, as in sel_hist
 #pragma unroll
     for (int k = 0; k < SEL_PER; ++k) {
-        const int64_t x = x0 + (int64_t)k * 256;
         const unsigned long long key = vp_key(val[k]);
-        if (x < a.npts && (key >> shift) == digit) {
-            lk[at] = key;
-            li[at] = (unsigned)x;
-            ++at;
+        if (x0 + (int64_t)k * 256 < a.npts && (key >> shift) == digit) {
+            const unsigned d = (unsigned)(key >> (shift - SEL_BITS2)) & (unsigned)(SEL_NB2 - 1);
+            if (run && d != bin) {
+                atomicAdd(&h2[bin], run);
+                run = 0u;
+            }
+            bin = d;
+            ++run;
         }
     }
+    if (run) atomicAdd(&h2[bin], run);
+    __syncthreads();
+    unsigned* g2 = la.hist2 + (size_t)b * SEL_NB2;
+    for (int i = tid; i < SEL_NB2; i += 256)
+        if (h2[i]) atomicAdd(&g2[i], h2[i]);
 }
 
-// The end of the search among the listed points, one workgroup per field:
-// digits of SEL_BITS bits of the key below the first, then, when only some of
-// the points with the last key are selected, of the index from the lower end.
-// The list is copied to LDS when it fits.  Leaves the histogram and the count at
-// zero.
-constexpr int SEL_LIST_LDS = 8192;
-__global__ void __launch_bounds__(256) sel_finish(const SelListArgs la, int shift0, int index_bits)
+// The index of the rank-th point (in index order) with key ks, by one workgroup: counts
+// per chunk, a wave each, then a walk through the chunk that holds it.
+template <int NT, typename T>
+__device__ __forceinline__ long long sel_tie_index(const SelArgs& a, const T* v, unsigned long long ks, long long rank,
+                                                   unsigned* cnt, long long* sh)
 {
+    __shared__ long long s_chunk, s_rank, s_index;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int chunks = (int)a.chunks;
+    for (int c = tid >> 6; c < chunks; c += NT / 64) {
+        unsigned long long n = 0;
+        constexpr int U = 32;  // loads in flight
+        for (int k0 = 0; k0 < SEL_CHUNK / 64; k0 += U) {
+            T val[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int64_t x = (int64_t)c * SEL_CHUNK + (k0 + k) * 64 + lane;
+                val[k] = v[x < a.npts ? x : a.npts - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                n += ((int64_t)c * SEL_CHUNK + (k0 + k) * 64 + lane < a.npts && vp_key(val[k]) == ks) ? 1ull : 0ull;
+        }
+        n = wave_sum(n);
+        if (lane == 0) cnt[c] = (unsigned)n;
+    }
+    if (tid == 0) {
+        s_chunk = 0;
+        s_rank = rank;
+        s_index = -1;
+    }
+    __syncthreads();
+    const int per = (chunks + NT - 1) / NT, c0 = tid * per;
+    long long sum = 0, total;
+    for (int c = c0; c < c0 + per && c < chunks; ++c) sum += cnt[c];
+    long long incl = scan_wg<NT>(sum, sh, total);
+    long long acc = incl - sum;
+    if (acc < rank && rank <= incl)
+        for (int c = c0; c < c0 + per && c < chunks; ++c) {
+            if (acc + cnt[c] >= rank) {
+                s_chunk = c;
+                s_rank = rank - acc;
+                break;
+            }
+            acc += cnt[c];
+        }
+    __syncthreads();
+    constexpr int P = SEL_CHUNK / NT;  // neighbouring points of a thread
+    const int64_t x0 = s_chunk * SEL_CHUNK + (int64_t)tid * P;
+    const long long want = s_rank;
+    bool eq[P];
+    sum = 0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        eq[k] = x0 + k < a.npts && vp_key(x0 + k < a.npts ? v[x0 + k] : (T)0) == ks;
+        sum += eq[k] ? 1 : 0;
+    }
+    incl = scan_wg<NT>(sum, sh, total);
+    acc = incl - sum;
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+        if (eq[k] && ++acc == want) s_index = x0 + k;
+    __syncthreads();
+    return s_index;
+}
+
+// The end of the search among the listed points, by one workgroup per field:
+// digits of SEL_BITS bits of the key below the ones found, then, when only some of
+// the points with the last key are selected, of the index from the lower end.
+// The list is copied to LDS.  Leaves the histograms and the count at zero.
+// Where sel_list took the second histogram, every workgroup of the field finds its
+// digit, lists the chunks' points of both digits and, where these are many too, adds
+// their next bits to a third histogram; the workgroup that finishes last ends the
+// search.  The others' list entries and counts are made visible to it by the
+// device-scope fences on both sides of the finished-workgroup counter.  In float the
+// three digits are the whole key.  In double a list of more than SEL_LIST_LDS points is
+// read by that one workgroup, from where its keys first differ: points whose Delta E
+// agree in 35 bits.
+template <typename T>
+__global__ void __launch_bounds__(SEL_NTF) sel_finish(const SelListArgs la, int shift0, int index_bits)
+{
+    constexpr int NT = SEL_NTF;
     const SelArgs& a = la.s;
-    __shared__ long long sh[4];
+    __shared__ long long sh[NT / 64];
     __shared__ unsigned h[1 << SEL_BITS];
     __shared__ unsigned long long lkey[SEL_LIST_LDS];
     __shared__ unsigned lidx[SEL_LIST_LDS];
-    __shared__ unsigned long long s_pre;
+    __shared__ unsigned long long s_pre, s_and, s_or;
     __shared__ long long s_need;
-    __shared__ unsigned s_cnt;
-    const int b = blockIdx.x, tid = threadIdx.x;
+    __shared__ unsigned s_cnt, s_base, s_last;
+    __shared__ int s_digit;
+    const int b = blockIdx.y, tid = threadIdx.x;
     VpSel* st = a.st + b;
     const long long np = a.nplus[b];
+    const bool none = np <= 0 || np >= a.npts;  // decided by sel_list, nothing listed
+    const bool over = !none && la.over[b] != 0u;
+    if (blockIdx.x > 0 && !over) return;  // uniform
+    const T* v = reinterpret_cast<const T*>(a.dE) + (size_t)b * a.npts;
     unsigned* g = a.hist + (size_t)b * (1 << SEL_BITS);
-    const unsigned M = la.count[b];
-    for (int i = tid; i < (1 << SEL_BITS); i += 256) g[i] = 0u;
-    if (np <= 0 || np >= a.npts) return;  // decided by sel_list, nothing listed
+    unsigned long long pre = st->kstar;
+    int low = shift0;  // key bits below are still open
+    unsigned M;
+    if (!over) {
+        M = la.count[b];
+        for (int i = tid; i < (1 << SEL_BITS); i += NT) g[i] = 0u;
+        if (none) return;
+        __syncthreads();  // every wave has read the count, which is cleared below
+        if (tid == 0) {
+            s_need = st->need;
+            s_cnt = M;
+        }
+    } else {
+        unsigned *g2 = la.hist2 + (size_t)b * SEL_HIST2, *g3 = g2 + SEL_NB2;
+        low -= SEL_BITS2;
+        constexpr int per = SEL_NB2 / NT;
+        const int hi = SEL_NB2 - 1 - tid * per;
+        unsigned c[per];
+#pragma unroll
+        for (int i = 0; i < per; ++i) c[i] = g2[hi - i];
+        sel_pick<NT>(c, hi, st->need, sh, s_digit, s_need, s_cnt);
+        M = s_cnt;
+        pre |= (unsigned long long)s_digit << low;
+        const bool third = M > SEL_LIST_LDS;
+        const bool list = !third || sizeof(T) == 8;
+        constexpr int bits3 = sizeof(T) == 8 ? SEL_BITS : 32 - SEL_BITS - SEL_BITS2;
+        for (int i = tid; i < (1 << bits3); i += NT) h[i] = 0u;
+        unsigned bin = 0u, run = 0u;
+        for (int64_t ch = blockIdx.x; ch < a.chunks; ch += gridDim.x) {
+            const int64_t x0 = ch * SEL_CHUNK + tid;
+            T val[SEL_CHUNK / NT];
+            sel_load<NT>(v, x0, a.npts, val);
+            __syncthreads();  // s_cnt and s_base have been read; h is clear
+            if (tid == 0) s_last = 0u;
+            __syncthreads();
+            if (list) sel_append<NT>(la, b, val, x0, low, pre >> low, s_last, s_base);
+            if (!third) continue;
+#pragma unroll
+            for (int k = 0; k < SEL_CHUNK / NT; ++k) {
+                const unsigned long long key = vp_key(val[k]);
+                if (x0 + (int64_t)k * NT < a.npts && (key >> low) == (pre >> low)) {
+                    const unsigned d = (unsigned)(key >> (low - bits3)) & ((1u << bits3) - 1u);
+                    if (run && d != bin) {
+                        atomicAdd(&h[bin], run);
+                        run = 0u;
+                    }
+                    bin = d;
+                    ++run;
+                }
+            }
+        }
+        if (run) atomicAdd(&h[bin], run);
+        __syncthreads();
+        if (third)
+            for (int i = tid; i < (1 << bits3); i += NT)
+                if (h[i]) atomicAdd(&g3[i], h[i]);
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) s_last = atomicAdd(a.done + b, 1u) == gridDim.x - 1 ? 1u : 0u;
+        __syncthreads();
+        if (s_last == 0u) return;  // uniform
+        __threadfence();
+        if (third) {
+            constexpr int per3 = (1 << SEL_BITS) / NT;
+            const int hi3 = (1 << SEL_BITS) - 1 - tid * per3;
+            unsigned c3[per3];
+#pragma unroll
+            for (int i = 0; i < per3; ++i) c3[i] = g3[hi3 - i];
+            sel_pick<NT>(c3, hi3, s_need, sh, s_digit, s_need, s_cnt);
+            low -= bits3;
+            pre |= (unsigned long long)s_digit << low;
+        }
+        for (int i = tid; i < (1 << SEL_BITS); i += NT) g[i] = 0u;
+        for (int i = tid; i < SEL_HIST2; i += NT) g2[i] = 0u;
+        if (tid == 0) a.done[b] = 0u;
+    }
     const unsigned long long* gk = la.key + (size_t)b * a.npts;
     const unsigned* gi = la.idx + (size_t)b * a.npts;
-    const bool lds = M <= (unsigned)SEL_LIST_LDS;
-    __syncthreads();  // every wave has read the count, which is cleared below
+    const bool lds = M <= SEL_LIST_LDS;
     if (lds)
-        for (unsigned i = tid; i < M; i += 256) {
+        for (unsigned i = tid; i < M; i += NT) {
             lkey[i] = gk[i];
             lidx[i] = gi[i];
         }
     auto key_at = [&](unsigned i) { return lds ? lkey[i] : gk[i]; };
-    auto idx_at = [&](unsigned i) { return lds ? lidx[i] : gi[i]; };
     if (tid == 0) {
-        s_pre = st->kstar;
-        s_need = st->need;
-        s_cnt = M;
+        s_pre = pre;
         la.count[b] = 0u;
     }
     __syncthreads();
-    // one digit: histogram of (value >> sh) over the points for which `in`
-    // holds, then the digit at which the running count, from the top (down) or
-    // the bottom, reaches s_need; s_need becomes the rank within it
-    auto digit = [&](auto value, auto in, int shift, int bits, bool down) -> int {
-        __shared__ int s_d;
-        const int nb = 1 << bits;
-        for (int i = tid; i < nb; i += 256) h[i] = 0u;
-        __syncthreads();
-        for (unsigned i = tid; i < M; i += 256)
-            if (in(i)) atomicAdd(&h[(unsigned)(value(i) >> shift) & (unsigned)(nb - 1)], 1u);
-        __syncthreads();
-        const int per = (nb + 255) / 256;
-        long long sum = 0;
-        for (int i = 0; i < per; ++i) {
-            const int o = tid * per + i;
-            if (o < nb) sum += h[down ? nb - 1 - o : o];
-        }
-        long long total;
-        const long long need = s_need;
-        const long long incl = scan256(sum, sh, total);
-        const long long excl = incl - sum;
-        if (excl < need && need <= incl) {
-            long long acc = excl;
-            for (int i = 0; i < per; ++i) {
-                const int o = tid * per + i;
-                const int d = down ? nb - 1 - o : o;
-                if (acc + (long long)h[d] >= need) {
-                    s_d = d;
-                    s_cnt = h[d];
-                    s_need = need - acc;
-                    break;
-                }
-                acc += h[d];
+    constexpr int U = 8;  // loads in flight
+    // visits the listed keys (or, with the LDS list, the indices) for which `in` holds
+    auto visit = [&](auto value, auto in, auto use) {
+        for (unsigned i0 = tid; i0 < M; i0 += U * NT) {
+            decltype(value(0u)) x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned i = i0 + (unsigned)(u * NT);
+                x[u] = value(i < M ? i : i0);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned i = i0 + (unsigned)(u * NT);
+                if (i < M && in(i, x[u])) use(x[u]);
             }
         }
-        __syncthreads();
-        return s_d;
     };
-    int low = shift0;  // key bits below `low` are still open
+    // one digit: histogram of (value >> sh) over the points for which `in`
+    // holds, then the digit at which the running count, from the top (down) or
+    // the bottom, reaches s_need; s_need becomes the rank within it.  Equal digits that
+    // follow each other in a thread count once (equal values: one bin for them all)
+    auto digit = [&](auto value, auto in, int shift, int bits, bool down) -> int {
+        const int nb = 1 << bits;
+        for (int i = tid; i < nb; i += NT) h[i] = 0u;
+        __syncthreads();
+        unsigned bin = 0u, run = 0u;
+        visit(value, in, [&](auto x) {
+            const unsigned d = (unsigned)(x >> shift) & (unsigned)(nb - 1);
+            if (run && d != bin) {
+                atomicAdd(&h[bin], run);
+                run = 0u;
+            }
+            bin = d;
+            ++run;
+        });
+        if (run) atomicAdd(&h[bin], run);
+        __syncthreads();
+        constexpr int per = (1 << SEL_BITS) / NT;
+        unsigned c[per];
+#pragma unroll
+        for (int i = 0; i < per; ++i) {
+            const int o = tid * per + i;
+            c[i] = o < nb ? h[down ? nb - 1 - o : o] : 0u;
+        }
+        sel_pick<NT>(c, (1 << SEL_BITS) - 1 - tid * per, s_need, sh, s_digit, s_need, s_cnt);
+        const int o = (1 << SEL_BITS) - 1 - s_digit;  // bins counted from the end searched from
+        return down ? nb - 1 - o : o;
+    };
     while (low > 0 && s_need != (long long)s_cnt) {
+        if (!lds) {
+            // the bits that every candidate shares are known
+            if (tid == 0) {
+                s_and = ~0ull;
+                s_or = 0ull;
+            }
+            __syncthreads();
+            unsigned long long all = ~0ull, any = 0ull;
+            const unsigned long long p = s_pre >> low;
+            visit(key_at, [&](unsigned, unsigned long long k) { return (k >> low) == p; },
+                  [&](unsigned long long k) {
+                      all &= k;
+                      any |= k;
+                  });
+            atomicAnd(&s_and, all);
+            atomicOr(&s_or, any);
+            __syncthreads();
+            const unsigned long long diff = s_and ^ s_or;
+            low = diff ? 64 - __clzll((long long)diff) : 0;
+            const unsigned long long same = (s_and >> low) << low;
+            __syncthreads();
+            if (tid == 0) s_pre = same;
+            __syncthreads();
+            if (low == 0) break;  // uniform
+        }
         const int bits = low < SEL_BITS ? low : SEL_BITS;
         const int top = low;
         low -= bits;
-        const unsigned long long pre = s_pre >> top;
-        const int d = digit(key_at, [&](unsigned i) { return (key_at(i) >> top) == pre; }, low, bits, true);
+        const unsigned long long p = top < 64 ? s_pre >> top : 0ull;
+        const int d = digit(key_at, [&](unsigned, unsigned long long k) { return top >= 64 || (k >> top) == p; }, low,
+                            bits, true);
         if (tid == 0) s_pre |= (unsigned long long)d << low;
         __syncthreads();
     }
@@ -440,21 +707,28 @@ __global__ void __launch_bounds__(256) sel_finish(const SelListArgs la, int shif
         return;
     }
     // the need-th smallest index among the points with key ks
-    unsigned ipre = 0u;
-    int ilow = index_bits;
-    while (ilow > 0) {
-        const int bits = ilow < SEL_BITS ? ilow : SEL_BITS;
-        const int top = ilow;
-        ilow -= bits;
-        const unsigned pre = ipre >> top;
-        const int d = digit(idx_at, [&](unsigned i) { return key_at(i) == ks && (idx_at(i) >> top) == pre; }, ilow,
-                            bits, false);
-        ipre |= (unsigned)d << ilow;
+    long long istar;
+    if (lds) {
+        unsigned ipre = 0u;
+        int ilow = index_bits;
+        while (ilow > 0) {
+            const int bits = ilow < SEL_BITS ? ilow : SEL_BITS;
+            const int top = ilow;
+            ilow -= bits;
+            const unsigned p = ipre >> top;
+            const int d = digit([&](unsigned i) { return lidx[i]; },
+                                [&](unsigned i, unsigned x) { return lkey[i] == ks && (x >> top) == p; }, ilow, bits,
+                                false);
+            ipre |= (unsigned)d << ilow;
+        }
+        istar = (long long)ipre;
+    } else {
+        istar = sel_tie_index<NT>(a, v, ks, s_need, lidx, sh);
     }
     if (tid == 0) {
         st->kstar = ks;
         st->mode = VS_TIES_PART;
-        st->istar = (long long)ipre;
+        st->istar = istar;
     }
 }
 
@@ -512,19 +786,23 @@ hipError_t launch_select(int prec, const SelArgs& a, int batch, hipStream_t st)
 
 hipError_t launch_select_list(int prec, const SelListArgs& a, int batch, hipStream_t st)
 {
-    if (a.s.chunks <= 0 || batch <= 0 || a.s.npts > (1ll << 31)) return hipErrorInvalidValue;
+    if (a.s.chunks <= 0 || batch <= 0 || a.s.npts > (1ll << 31) || a.s.chunks > (int64_t)SEL_LIST_LDS)
+        return hipErrorInvalidValue;  // (2-D plans have at most 1024 chunks)
     const dim3 gc((unsigned)a.s.chunks, (unsigned)batch), bl(256);
+    // the workgroups that sel_finish has beside the first end at once as a rule
+    const dim3 gf((unsigned)std::min<int64_t>(a.s.chunks, std::max(8, 256 / batch)), (unsigned)batch);
     const int shift = (prec == 0 ? 64 : 32) - SEL_BITS;
     int ib = 0;
     while ((1ll << ib) < a.s.npts) ++ib;
     if (prec == 0) {
         hipLaunchKernelGGL((sel_hist<double>), gc, bl, 0, st, a.s, shift, SEL_BITS, 0);
         hipLaunchKernelGGL((sel_list<double>), gc, bl, 0, st, a, shift);
+        hipLaunchKernelGGL((sel_finish<double>), gf, dim3(SEL_NTF), 0, st, a, shift, ib);
     } else {
         hipLaunchKernelGGL((sel_hist<float>), gc, bl, 0, st, a.s, shift, SEL_BITS, 0);
         hipLaunchKernelGGL((sel_list<float>), gc, bl, 0, st, a, shift);
+        hipLaunchKernelGGL((sel_finish<float>), gf, dim3(SEL_NTF), 0, st, a, shift, ib);
     }
-    hipLaunchKernelGGL(sel_finish, dim3((unsigned)batch), bl, 0, st, a, shift, ib);
     return hipGetLastError();
 }
 

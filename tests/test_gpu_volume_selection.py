@@ -1,0 +1,80 @@
+"""The volume-preserving iteration where the cut of the selection falls among many
+points: rough fields, whose domains diffuse away.
+
+Against the general passes (mbo_plan_set_path GENERIC), whose selection does not
+depend on where the cut falls: the same points in double, and never much slower.
+The times are the least of several calls of the same captured graph, each ending in
+its logs; a quarter more than the general passes is the bound (the spread of such
+calls is a few percent).
+"""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+F64, F32, FB = 0, 1, 2
+
+
+def speckled(n, grid, share, seed):
+    """The identity with the last entry -1 at a random share of the points."""
+    rng = np.random.default_rng(seed)
+    A = np.zeros((n, n) + tuple(grid))
+    for k in range(n):
+        A[k, k] = 1.0
+    A[n - 1, n - 1] = np.where(rng.random(grid) < share, -1.0, 1.0)
+    return A
+
+
+def run(A, tau, prec, K, path, n_plus=None, reps=1):
+    import torch
+    from paper_1711_01365_amd import mbo
+    dt = torch.float64 if prec == F64 else torch.float32
+    p = mbo.Plan(A.shape[3:], A.shape[1], tau, precision=prec, batch=A.shape[0])
+    p.set_path(path)
+    X = torch.tensor(A, dtype=dt, device="cuda")
+    best = np.inf
+    for _ in range(reps + 1):
+        Y = X.clone()
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        logs = p.iterate_volume(Y, K, n_plus)
+        best = min(best, time.perf_counter() - t)
+    p.close()
+    return Y.double().cpu().numpy(), logs, best
+
+
+def positive(A):
+    n = A.shape[1]
+    return (np.linalg.det(np.moveaxis(A.reshape(A.shape[0], n, n, -1), -1, 1)) > 0).sum(axis=1)
+
+
+# shares either side of a half (the moved points join or leave), lists just below and
+# far above what one workgroup takes (8192 points), several digits of the second
+# histogram, two fields of which one needs it
+@pytest.mark.parametrize("n,grid", [(1, (128, 128)), (2, (64, 128)), (2, (128, 256)), (3, (256, 128)), (4, (128, 128))])
+@pytest.mark.parametrize("share", [0.02, 0.3, 0.7])
+def test_same_points(n, grid, share):
+    from paper_1711_01365_amd import mbo
+    A = np.stack([speckled(n, grid, share, 3), speckled(n, grid, 0.5, 4)])
+    tau = (6.0 / max(grid)) ** 2 / 2
+    got = run(A, tau, F64, 3, mbo.PATH_BANDED)
+    ref = run(A, tau, F64, 3, mbo.PATH_GENERIC)
+    assert np.array_equal(positive(got[0]), positive(A))
+    assert np.array_equal(got[1]["flips"], ref[1]["flips"])
+    assert np.array_equal(got[1]["n_plus"], ref[1]["n_plus"])
+    # diagonal fields: the closest diagonal matrix is +-1 entry by entry, exactly
+    assert np.abs(got[0] - ref[0]).max() <= 1e-10
+    assert np.abs(got[1]["energy"] - ref[1]["energy"]).max() <= 1e-9 * np.abs(ref[1]["energy"]).max()
+
+
+@pytest.mark.parametrize("n,N,prec", [(2, 1024, FB), (2, 2048, FB), (2, 2048, F64), (3, 2048, FB)])
+def test_time_of_a_cut_in_the_bulk(n, N, prec):
+    from paper_1711_01365_amd import mbo
+    A = speckled(n, (N, N), 0.02, 3)[None]
+    tau = (8.0 / N) ** 2 / 2
+    got = run(A, tau, prec, 2, mbo.PATH_BANDED, reps=5)
+    ref = run(A, tau, prec, 2, mbo.PATH_GENERIC, reps=5)
+    assert np.array_equal(positive(got[0]), positive(A))
+    assert got[2] <= 1.25 * ref[2], (got[2], ref[2])
