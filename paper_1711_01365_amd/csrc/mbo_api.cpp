@@ -216,6 +216,9 @@ struct mbo_plan_s {
     unsigned* vidx = nullptr;            // [batch][npts] their indices
     unsigned* vhist2 = nullptr;          // [batch][SEL_HIST2] second histogram
     unsigned* vover = nullptr;           // [batch] whether it was taken
+    unsigned* vnredo = nullptr;          // [batch] row groups transformed again
+    unsigned* vredo = nullptr;           // [batch][row groups] their list
+    void* vdir = nullptr;                // [batch][n][npts] what volume_fix needs of a point
     // relaxed flows: cached graph of mbo_relaxed_flow, penalty partials
     hipGraphExec_t rexec = nullptr;
     void* rg_A = nullptr;
@@ -1259,8 +1262,9 @@ hipError_t enqueue_volume_step(mbo_plan_t p, int load_flags, const void* Ain, vo
 }
 
 // Workspace of the band-limited volume-preserving iteration (2-D), one
-// allocation: the second set of row spectra, then the listed keys, the counts,
-// second histograms and marks of the selection, and the listed indices.
+// allocation: the second set of row spectra, the other candidates, then the listed keys,
+// the counts, further histograms and marks of the selection, volume_redo's lists and
+// the listed indices.
 mbo_status ensure_volume_fast(mbo_plan_t p)
 {
     const size_t B = (size_t)p->batch, np = B * (size_t)p->npts;
@@ -1272,15 +1276,22 @@ mbo_status ensure_volume_fast(mbo_plan_t p)
     FastRowArgs r;
     std::memset(&r, 0, sizeof r);
     (void)launch_row_fast_vkey(p->pk, p->n, ilog2((int)p->N[1]), r, dim3(1), nullptr, true);
+    VolFixArgs f;
+    std::memset(&f, 0, sizeof f);
+    (void)launch_volume_redo(p->pk, p->n, ilog2((int)p->N[1]), f, dim3(1), nullptr, true);
     (void)hipGetLastError();
-    const size_t words = B + B * SEL_HIST2 + B;  // counts, histograms, marks
-    HIP_TRY(p, hipMalloc(&p->vz, zb + np * 8 + (words + np) * 4));
-    p->vkey = reinterpret_cast<unsigned long long*>(static_cast<char*>(p->vz) + zb);
+    const size_t groups = (size_t)fast_row_groups(p), db = p->n > 1 ? np * p->n * p->esz : 0;
+    const size_t zeros = B + B * SEL_HIST2, words = zeros + B + B + B * groups + np;
+    HIP_TRY(p, hipMalloc(&p->vz, zb + db + np * 8 + words * 4));
+    p->vdir = static_cast<char*>(p->vz) + zb;
+    p->vkey = reinterpret_cast<unsigned long long*>(static_cast<char*>(p->vdir) + db);
     p->vcnt = reinterpret_cast<unsigned*>(p->vkey + np);
     p->vhist2 = p->vcnt + B;
     p->vover = p->vhist2 + B * SEL_HIST2;
-    p->vidx = p->vover + B;
-    HIP_TRY(p, launch_fill_i32(reinterpret_cast<int*>(p->vcnt), (int64_t)words, 0, p->stream));
+    p->vnredo = p->vover + B;
+    p->vredo = p->vnredo + B;
+    p->vidx = p->vredo + B * groups;
+    HIP_TRY(p, launch_fill_i32(reinterpret_cast<int*>(p->vcnt), (int64_t)zeros, 0, p->stream));
     p->vz_bytes = zb;
     return MBO_OK;
 }
@@ -1288,9 +1299,10 @@ mbo_status ensure_volume_fast(mbo_plan_t p)
 // Enqueue mbo_iterate_volume through the band-limited passes.  Per iteration:
 // the heat pass, the row pass that projects every point onto the side that its
 // determinant says and writes Delta E (row_fast_vkey, into the other set of row
-// spectra), the three-launch selection, and volume_fix on the points that the
-// selection moves: 52 us at n = 3, 512^2 in float (heat 7, row 17, selection 15,
-// volume_fix 13), where the general passes (both candidates of every point,
+// spectra), the three-launch selection, volume_fix on the points that the
+// selection moves and volume_redo on rows with many of them: 50 us at n = 3, 512^2 in
+// float (heat 7, row 19, selection 15, volume_fix 8.5, an empty volume_redo 4, by the
+// kernels' own times), where the general passes (both candidates of every point,
 // twice) and the seven-launch selection took 92 (13 + 17.5 + 33 + 27.5).
 // With the caller's own volume the first selection may move most of the
 // points: that iteration runs the general selection and reassignment on the
@@ -1344,6 +1356,7 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
     sa.count = p->vcnt;
     sa.hist2 = p->vhist2;
     sa.over = p->vover;
+    sa.clear = p->vnredo;
     void *Zin = p->Z, *Zout = p->vz;
     const dim3 rg((unsigned)fast_row_groups(p), (unsigned)p->batch);
     for (int s = first; s <= K; ++s) {
@@ -1353,6 +1366,7 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
         r.Zout = Zout;
         r.slot = p->slot;
         r.vde = p->vde;
+        r.vdir = p->vdir;
         r.iter = s;
         r.K = K;
         r.cnt_part = p->cnt_part;
@@ -1364,7 +1378,16 @@ hipError_t enqueue_iterate_volume_fast(mbo_plan_t p, void* A, int K, bool from_a
         VolFixArgs f;
         f.r = r;
         f.vsel = p->vsel;
+        f.redo = p->vredo;
+        f.nredo = p->vnredo;
+        f.groups = rg.x;
         if ((e = launch_volume_fix(p->pk, p->n, f, rg, st)) != hipSuccess) return e;
+        if (r.flags & RF_FORWARD) {
+            f.r.flags = RF_LOAD_REAL | RF_FORWARD;
+            if ((e = launch_volume_redo(p->pk, p->n, ilog2((int)p->N[1]), f, dim3(std::min(rg.x, 512u), rg.y), st)) !=
+                hipSuccess)
+                return e;
+        }
         std::swap(Zin, Zout);
     }
     if ((e = launch_sum_counts(p->cnt_part, fast_row_groups(p), K, first - 1, (int)p->batch, p->flips, p->fallbacks,

@@ -820,8 +820,34 @@ __device__ __forceinline__ void jacobi_finish(T (&W)[n][n], const T (&V)[n][n], 
 }
 
 
+// The column of V that belongs to the shortest column of W (the right singular vector
+// of sigma_min after the sweeps).
 template <typename T, int n>
-__device__ __forceinline__ void polar_jacobi(const T* a_in, T* q, int& dsign, T& smin)
+__device__ __forceinline__ void min_direction(const T (&W)[n][n], const T (&V)[n][n], T (&v)[n])
+{
+    T sm = 0;
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+        T w2 = 0;
+#pragma unroll
+        for (int i = 0; i < n; ++i) w2 += W[i][j] * W[i][j];
+        const bool less = j == 0 || w2 < sm;
+        sm = less ? w2 : sm;
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = less ? V[i][j] : v[i];
+    }
+}
+
+struct NoDirection {
+    template <typename T, int n>
+    __device__ __forceinline__ void operator()(const T (&)[n][n], const T (&)[n][n]) const
+    {
+    }
+};
+
+// dir is handed W and V after the sweeps, before W becomes U.
+template <typename T, int n, typename Dir = NoDirection>
+__device__ __forceinline__ void polar_jacobi(const T* a_in, T* q, int& dsign, T& smin, Dir dir = Dir())
 {
     const int ex = scale_exponent<T, n>(a_in);
     T W[n][n], V[n][n];
@@ -833,6 +859,7 @@ __device__ __forceinline__ void polar_jacobi(const T* a_in, T* q, int& dsign, T&
             V[i][j] = (i == j) ? (T)1 : (T)0;
         }
     jacobi_sweeps<T, n>(W, V);
+    dir(W, V);
     jacobi_finish<T, n>(W, V, ex, q, dsign, smin);
 }
 
@@ -875,9 +902,10 @@ __device__ __forceinline__ void orthonormal_columns(const float (&V0)[n][n], dou
 // float exponent is the double one) and Q is rounded to float as it is formed;
 // the sign of det Q is taken from the rounded Q (orthogonal: |det| = 1 up to
 // rounding).  Both save the registers of a double copy.
-// Returns the smallest singular value.
-template <int n>
-__device__ __forceinline__ double polar_jacobi_warm(const float* a_in, const float (&V0)[n][n], float* q, int& dsign)
+// Returns the smallest singular value; dir as in polar_jacobi.
+template <int n, typename Dir = NoDirection>
+__device__ __forceinline__ double polar_jacobi_warm(const float* a_in, const float (&V0)[n][n], float* q, int& dsign,
+                                                    Dir dir = Dir())
 {
     const int ex = scale_exponent<float, n>(a_in);
     double V[n][n], W[n][n];
@@ -892,6 +920,7 @@ __device__ __forceinline__ double polar_jacobi_warm(const float* a_in, const flo
             W[i][j] = ldexp(v, -ex);
         }
     jacobi_sweeps<double, n>(W, V);
+    dir(W, V);
     double smin;
     jacobi_finish<double, n, float>(W, V, ex, q, dsign, smin);
     return smin;

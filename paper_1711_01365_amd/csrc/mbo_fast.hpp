@@ -209,11 +209,12 @@ struct RowFastShape {
 // FM_ITER the steps that the flags name (projection, load, store), FM_VJP the
 // projection's vector-Jacobian product with the cotangent field a.Gin, FM_VKEY
 // the projection with Delta E of the volume-preserving step into a.vde, FM_RELAX
-// the reaction step of the relaxed flows (GD-1 by the projection of FM_ITER).
-enum { FM_ITER = 0, FM_VJP = 1, FM_VKEY = 2, FM_RELAX = 3 };
+// the reaction step of the relaxed flows (GD-1 by the projection of FM_ITER), FM_REDO
+// nothing (the forward transform of the field's rows into a.Zout).
+enum { FM_ITER = 0, FM_VJP = 1, FM_VKEY = 2, FM_RELAX = 3, FM_REDO = 4 };
 
 template <typename T, int n, int LOG2L, bool PM, int MODE>
-__device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
+__device__ __forceinline__ void row_fast_body(const FastRowArgs& a, unsigned group)
 {
     typedef RowFastShape<T, n, LOG2L> S;
     constexpr int NN = S::NN, PL = S::PL, L = S::L, Tn = S::Tn, RPW = S::RPW, LP = S::LP;
@@ -232,7 +233,7 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     __shared__ int hq_n, hq_claim;
     __shared__ unsigned long long wg_cnt[2];
 
-    const int flags = a.flags;
+    const int flags = MODE == FM_REDO ? RF_LOAD_REAL | RF_FORWARD : a.flags;
     const int b = blockIdx.y;
     const int tid = threadIdx.x;
     if (tid == 0) {
@@ -252,10 +253,10 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
     // take contiguous runs of row groups, so that the groups sharing a line
     // run on one XCD.
     const int64_t nwgx = gridDim.x;
-    const int64_t row0 = RPW * (((nwgx & 7) || !pm) ? (int64_t)blockIdx.x
+    const int64_t row0 = RPW * (((nwgx & 7) || !pm) ? (int64_t)group
                                                     : (int64_t)(blockIdx.x & 7) * (nwgx >> 3) + (blockIdx.x >> 3));
     C* Zb = reinterpret_cast<C*>(a.Z) + (size_t)b * PL * a.rows * W;
-    C* Zo = MODE == FM_VKEY ? reinterpret_cast<C*>(a.Zout) + (size_t)b * PL * a.rows * W : Zb;
+    C* Zo = MODE == FM_VKEY || MODE == FM_REDO ? reinterpret_cast<C*>(a.Zout) + (size_t)b * PL * a.rows * W : Zb;
 
     // Every global load that does not depend on another is issued first (the
     // kept modes of the first round of lines, the twiddles, the previous det
@@ -550,10 +551,12 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
         }
         __syncthreads();
     } else if constexpr (MODE == FM_VKEY) {
-        // Q = U V^t of every point and Delta E = +-2 sigma_min with the sign bit
-        // of det Q (also where sigma_min is 0: volume_fix reads the side there).
+        // Q = U V^t of every point, Delta E = +-2 sigma_min with the sign bit
+        // of det Q (also where sigma_min is 0: volume_fix reads the side there) and the
+        // n values from which volume_fix forms the other candidate (vp_change).
         // Float points below sigma_fb are queued and done in double afterwards.
         T* vde = reinterpret_cast<T*>(a.vde) + (size_t)b * npts;
+        T* vdir = reinterpret_cast<T*>(a.vdir) + (size_t)b * n * npts;
         auto key_out = [&](int64_t xp, T* lrq, T* liq, T (&qv)[NN], int ds, T smin) {
             vde[xp] = ds > 0 ? smin + smin : -(smin + smin);
             finish(xp, lrq, liq, qv, ds, (int8_t)0);
@@ -571,6 +574,10 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                     T tm[NN], de;
                     nfb += vp_point<T, n>(av, qv, tm, de, fallback, a.sigma_fb) ? 1ull : 0ull;
                     const bool plus = de >= (T)0;
+                    if constexpr (n == 2) {
+                        vdir[xp] = plus ? tm[0] : qv[0];
+                        vdir[npts + xp] = plus ? tm[2] : qv[2];
+                    }
                     if (!plus) {
 #pragma unroll
                         for (int k = 0; k < NN; ++k) qv[k] = tm[k];
@@ -580,7 +587,12 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                 } else {
                     int ds;
                     T smin;
-                    polar_jacobi<T, n>(av, qv, ds, smin);
+                    polar_jacobi<T, n>(av, qv, ds, smin, [&](const T(&W)[n][n], const T(&V)[n][n]) {
+                        T v[n];
+                        min_direction<T, n>(W, V, v);
+#pragma unroll
+                        for (int k = 0; k < n; ++k) vdir[k * npts + xp] = v[k];
+                    });
                     if (QUEUE && fallback && (double)smin < a.sigma_fb)
                         fq[atomicAdd(&fq_n, 1)] = (unsigned short)(pp * NP + tid);
                     else
@@ -605,7 +617,13 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a)
                     {
                         // float Jacobi again for its V (sigma_fb = inf: it stops there)
                         (void)polar_jacobi_f32_fb<n>(aq, qv, ds, V, INFINITY);
-                        sm = (float)polar_jacobi_warm<n>(aq, V, qv, ds);
+                        sm = (float)polar_jacobi_warm<n>(
+                            aq, V, qv, ds, [&](const double(&Wd)[n][n], const double(&Vd)[n][n]) {
+                                double v[n];
+                                min_direction<double, n>(Wd, Vd, v);
+#pragma unroll
+                                for (int k = 0; k < n; ++k) vdir[k * npts + xp] = (T)v[k];
+                            });
                     }
                     ++nfb;
                     key_out(xp, lrq, liq, qv, ds, sm);
@@ -934,21 +952,21 @@ template <typename T, int n, int LOG2L, bool PM>
 __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
     row_fast(const FastRowArgs a)
 {
-    row_fast_body<T, n, LOG2L, PM, FM_ITER>(a);
+    row_fast_body<T, n, LOG2L, PM, FM_ITER>(a, blockIdx.x);
 }
 
 template <typename T, int n, int LOG2L>
 __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
     row_fast_vjp(const FastRowArgs a)
 {
-    row_fast_body<T, n, LOG2L, false, FM_VJP>(a);
+    row_fast_body<T, n, LOG2L, false, FM_VJP>(a, blockIdx.x);
 }
 
 template <typename T, int n, int LOG2L>
 __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS), (RowFastShape<T, n, LOG2L>::WAVES))
     row_fast_relax(const FastRowArgs a)
 {
-    row_fast_body<T, n, LOG2L, false, FM_RELAX>(a);
+    row_fast_body<T, n, LOG2L, false, FM_RELAX>(a, blockIdx.x);
 }
 
 // n = 4: the Jacobi of every point with its singular values takes more than 128
@@ -961,7 +979,7 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS),
                                           : RowFastShape<T, n, LOG2L>::WAVES))
     row_fast_vkey(const FastRowArgs a)
 {
-    row_fast_body<T, n, LOG2L, false, FM_VKEY>(a);
+    row_fast_body<T, n, LOG2L, false, FM_VKEY>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -969,36 +987,33 @@ __global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS),
 // ---------------------------------------------------------------------------
 // One workgroup per row_fast workgroup (at least 512 points, whole rows).  A
 // point whose membership differs from the sign of its Delta E changes from Q to
-// the candidate of the other determinant, T = Q - 2 u v^t (Lemma 7.1).  Few do:
-// the selection moves the cut only as far as the volume drifted in one step.
-// Each of them is read back from the kept row modes by a direct sum (16 lanes
-// per point), the change T - Q is formed by vp_change from Q as row_fast_vkey left
-// it in the field, and added to the row spectra that row_fast_vkey wrote, again by
-// direct sums over the kept modes.  Rows without such points end after reading Delta E and the det signs.
-// Bound by its chain of memory round trips (flags, spectra, projection, spectra),
-// not by the 300 to 660 points in 140 to 230 rows that it treats: 13 us at 512^2,
-// n = 3 in float, where transforming every row again took 27.
-// Threads: 512 in float up to n = 3 (32 points at a time; two workgroups per CU),
-// else 256.  Dynamic LDS: the twiddle table.
-template <typename T, int n>
-struct VolumeFixShape {
-    static constexpr int NT = sizeof(T) == 4 && n <= 3 ? 512 : 256;
-    static constexpr int WAVES = NT == 512 ? 4 : 1;
-};
+// the candidate of the other determinant (Lemma 7.1, vp_change), in the field and in
+// the row spectra that row_fast_vkey wrote.  Once the volume has settled few do: the
+// selection moves the cut only as far as the volume drifted in one step, and the change
+// is added to their rows' spectra by direct sums over the kept modes.  A workgroup with
+// more than VFIX_DIRECT of them (rough data) lists itself for volume_redo, which
+// transforms those rows again.  Rows without such points end after reading Delta E and
+// the det signs.
+// Bound by its chain of memory round trips (flags, point, spectra), not by the 300 to
+// 660 points in 140 to 230 rows that it treats at 512^2, n = 3 in float: 8.5 us, and 4 for
+// the empty volume_redo (13 with the points read back from the spectra).  A step of
+// 2048^2, n = 3, from a field with 30 % of the points flipped, all of which change side:
+// 0.74 ms; with direct sums for each of them 6.2, by the general passes 1.23.
+// Dynamic LDS: the twiddle table.
+constexpr int VFIX_NT = 512;
+constexpr int VFIX_DIRECT = 64;
 
 template <typename T, int n>
-__global__ void __launch_bounds__((VolumeFixShape<T, n>::NT), (VolumeFixShape<T, n>::WAVES))
-    volume_fix(const VolFixArgs f)
+__global__ void __launch_bounds__(VFIX_NT, 4) volume_fix(const VolFixArgs f)
 {
-    constexpr int NN = n * n, PL = (NN + 1) / 2, NT = VolumeFixShape<T, n>::NT, NB = NT / 16, PER = 2048 / NT;
+    constexpr int NN = n * n, PL = (NN + 1) / 2, NT = VFIX_NT, PER = 2048 / NT;
     typedef typename cx<T>::type C;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* twl = reinterpret_cast<C*>(smem_raw);
     const FastRowArgs& a = f.r;
     __shared__ unsigned short list[2048];
     __shared__ int wcnt[PER][NT / 64];
-    __shared__ T delta[NB][2 * PL];
-    __shared__ int xs[NB], rs[NB];  // column and row (within the workgroup) of each point in work
+    __shared__ T delta[VFIX_DIRECT][2 * PL];
     __shared__ unsigned wflip[NT / 64];
     const int b = blockIdx.y, tid = threadIdx.x, L = a.L, W = a.W, c = a.band;
     const int lg = 31 - __clz(L), rpw = L >= 512 ? 1 : 512 >> lg;
@@ -1061,95 +1076,67 @@ __global__ void __launch_bounds__((VolumeFixShape<T, n>::NT), (VolumeFixShape<T,
         if (all) a.cnt_part[((int64_t)b * a.K + (a.iter - 1)) * gridDim.x + blockIdx.x] += all;
     }
     if (m == 0) return;  // uniform
-    __syncthreads();     // the list is written
-
-    for (int i = tid; i < L; i += NT) twl[i] = reinterpret_cast<const C*>(a.tw)[i];
-    const C* tw = reinterpret_cast<const C*>(a.tw);
-    const C* Zi = reinterpret_cast<const C*>(a.Z) + (size_t)b * PL * a.rows * W;
+    const bool forward = (a.flags & RF_FORWARD) != 0, direct = forward && m <= VFIX_DIRECT;
+    if (forward && !direct && tid == 0)
+        f.redo[(size_t)b * gridDim.x + atomicAdd(f.nredo + b, 1u)] = blockIdx.x;
+    if (direct)
+        for (int i = tid; i < L; i += NT) twl[i] = reinterpret_cast<const C*>(a.tw)[i];
+    __syncthreads();  // the list is written
+    T* Aout = reinterpret_cast<T*>(a.slot ? *a.slot : a.Aout) + field_base(a.foff, b, NN * a.npts) + p0;
+    const T* vdir = reinterpret_cast<const T*>(a.vdir) + (size_t)b * n * a.npts + p0;
+    for (int j = tid; j < m; j += NT) {
+        const int i = list[j];
+        T q[NN], v[n], d[NN];
+#pragma unroll
+        for (int k = 0; k < NN; ++k) q[k] = Aout[(int64_t)k * a.npts + i];
+#pragma unroll
+        for (int k = 0; k < n; ++k) v[k] = n > 1 ? vdir[(int64_t)k * a.npts + i] : (T)0;
+        vp_change<T, n>(!(bool)__builtin_signbit(vde[i]), v, q, d);
+#pragma unroll
+        for (int k = 0; k < NN; ++k) Aout[(int64_t)k * a.npts + i] = q[k];
+        if (direct) {
+#pragma unroll
+            for (int k = 0; k < NN; ++k) delta[j][k] = d[k];
+            if (NN & 1) delta[j][NN] = (T)0;
+        }
+    }
+    if (!direct) return;
+    __syncthreads();
+    // a thread owns its (plane, mode) pairs, the points of a row follow each other in
+    // the list
     C* Zo = reinterpret_cast<C*>(a.Zout) + (size_t)b * PL * a.rows * W;
-    T* Aout = reinterpret_cast<T*>(a.slot ? *a.slot : a.Aout) + field_base(a.foff, b, NN * a.npts);
-    const int lane = tid & 15, g = tid >> 4;
-    const bool fallback = (a.flags & RF_FALLBACK) != 0;
-    for (int j0 = 0; j0 < m; j0 += NB) {
-        const int nb = m - j0 < NB ? m - j0 : NB;
-        if (g < nb) {
-            const int i = list[j0 + g];
-            const int x = i & (L - 1);
-            const int64_t row = row0 + (i >> lg);
-            if (lane == 0) {
-                xs[g] = x;
-                rs[g] = i >> lg;
-            }
-            T av[2 * PL];
-#pragma unroll
-            for (int k = 0; k < 2 * PL; ++k) av[k] = (T)0;
-            // four modes per lane and step, every load of a step in flight
-            for (int w0 = lane; w0 < W; w0 += 64) {
-                C t[4], z[4][PL];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int w = w0 + 16 * q < W ? w0 + 16 * q : 0;
-                    const int kx = (W == L || w <= c) ? w : L - W + w;  // unused slots hold zeros
-                    t[q] = tw[(kx * x) & (L - 1)];
-#pragma unroll
-                    for (int p = 0; p < PL; ++p) z[q][p] = Zi[((size_t)p * a.rows + row) * W + w];
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (w0 + 16 * q >= W) continue;
-#pragma unroll
-                    for (int p = 0; p < PL; ++p) {
-                        av[2 * p] += z[q][p].x * t[q].x + z[q][p].y * t[q].y;  // z exp(+2 pi i kx x / L)
-                        av[2 * p + 1] += z[q][p].y * t[q].x - z[q][p].x * t[q].y;
-                    }
-                }
-            }
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1)
-#pragma unroll
-                for (int k = 0; k < 2 * PL; ++k) av[k] += __shfl_xor(av[k], o, 64);
-            const T di = vde[i];
-            T d[NN], q[NN];
-#pragma unroll
-            for (int k = 0; k < NN; ++k) q[k] = Aout[(int64_t)k * a.npts + p0 + i];
-            vp_change<T, n>(av, !(bool)__builtin_signbit(di), di, fallback, a.sigma_fb, q, d);
-            if (lane == 0) {
-#pragma unroll
-                for (int k = 0; k < NN; ++k) Aout[(int64_t)k * a.npts + p0 + i] = q[k];
-            }
-            if (lane == 0) {
-#pragma unroll
-                for (int k = 0; k < NN; ++k) delta[g][k] = d[k];
-                if (NN & 1) delta[g][NN] = (T)0;
-            }
-        }
-        __syncthreads();
-        // spectra of the rows of these points: a thread owns its (plane, mode)
-        // pairs, the points of a row follow each other in the list
-        if (a.flags & RF_FORWARD) {
-            for (int e = tid; e < PL * W; e += NT) {
-                const int p = e / W, w = e - p * W;
-                if (W != L && w > c && w < W - c) continue;  // unused slot: stays zero
-                const int kx = (W == L || w <= c) ? w : L - W + w;
-                int j = 0;
-                while (j < nb) {
-                    const int r = rs[j];
-                    C* z = &Zo[((size_t)p * a.rows + row0 + r) * W + w];
-                    C v = *z;
-                    int j1 = j;
-                    while (j1 < nb && rs[j1] == r) ++j1;
+    for (int e = tid; e < PL * W; e += NT) {
+        const int p = e / W, w = e - p * W;
+        if (W != L && w > c && w < W - c) continue;  // unused slot: stays zero
+        const int kx = (W == L || w <= c) ? w : L - W + w;
+        int j = 0;
+        while (j < m) {
+            const int r = list[j] >> lg;
+            C* z = &Zo[((size_t)p * a.rows + row0 + r) * W + w];
+            C v = *z;
+            int j1 = j;
+            while (j1 < m && list[j1] >> lg == r) ++j1;
 #pragma unroll 4
-                    for (; j < j1; ++j) {
-                        const C t = twl[(kx * xs[j]) & (L - 1)];
-                        const T dr = delta[j][2 * p], di = delta[j][2 * p + 1];
-                        v.x += dr * t.x - di * t.y;  // (dr + i di) exp(-2 pi i kx x / L)
-                        v.y += dr * t.y + di * t.x;
-                    }
-                    *z = v;
-                }
+            for (; j < j1; ++j) {
+                const C t = twl[(kx * (list[j] & (L - 1))) & (L - 1)];
+                const T dr = delta[j][2 * p], di = delta[j][2 * p + 1];
+                v.x += dr * t.x - di * t.y;  // (dr + i di) exp(-2 pi i kx x / L)
+                v.y += dr * t.y + di * t.x;
             }
+            *z = v;
         }
-        __syncthreads();  // delta is free for the next points
+    }
+}
+
+// The rows that volume_fix listed: their spectra from the field again.  As a rule the
+// list is empty and the workgroups end at once.
+template <typename T, int n, int LOG2L>
+__global__ void __launch_bounds__((RowFastShape<T, n, LOG2L>::THREADS)) volume_redo(const VolFixArgs f)
+{
+    const unsigned m = f.nredo[blockIdx.y];
+    for (unsigned i = blockIdx.x; i < m; i += gridDim.x) {
+        row_fast_body<T, n, LOG2L, false, FM_REDO>(f.r, f.redo[(size_t)blockIdx.y * f.groups + i]);
+        __syncthreads();  // the lines in LDS have been read
     }
 }
 

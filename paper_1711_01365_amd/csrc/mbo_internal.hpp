@@ -239,6 +239,7 @@ struct SelListArgs {
     unsigned* count;          // [batch] listed points, zero between uses
     unsigned* hist2;          // [batch][SEL_HIST2] further histograms, zero between uses
     unsigned* over;           // [batch] whether the second histogram was taken
+    unsigned* clear;          // [batch] set to zero (volume_fix's count)
 };
 hipError_t launch_select_list(int prec, const SelListArgs& a, int batch, hipStream_t st);
 hipError_t launch_sel_mark(int prec, const SelArgs& a, int batch, hipStream_t st);
@@ -451,6 +452,7 @@ struct FastRowArgs {
     const void* Gin;         // row_fast_vjp: cotangent field [batch][n*n][npts]
     void* Zout;              // row_fast_vkey: row spectra written (Z is read)
     void* vde;               // row_fast_vkey: Delta E per point [batch][npts]
+    void* vdir;              // row_fast_vkey: n values of the other candidate [batch][n][npts] (n >= 2)
     int relax_kind;          // row_fast_relax: 1 = GD-1, 3 = GD-3
     double relax_c;          // row_fast_relax: dt / eps^2
 };
@@ -459,6 +461,9 @@ struct FastRowArgs {
 struct VolFixArgs {
     FastRowArgs r;           // Z: spectra read by row_fast_vkey, Zout: the spectra it wrote
     const VpSel* vsel;       // finished selection of each field [batch]
+    unsigned* redo;          // [batch][groups] workgroups whose rows are transformed again
+    unsigned* nredo;         // [batch] their number, zero before volume_fix
+    unsigned groups;         // row_fast workgroups per field
 };
 
 struct FastColArgs {
@@ -524,6 +529,9 @@ int heat_fast_adj_tile(int log2L);
 hipError_t launch_row_fast_vkey(int prec, int n, int log2L, const FastRowArgs& a, dim3 grid, hipStream_t st,
                                 bool prepare = false);
 hipError_t launch_volume_fix(int prec, int n, const VolFixArgs& a, dim3 grid, hipStream_t st);
+// the rows that volume_fix listed (a.r.flags = RF_LOAD_REAL | RF_FORWARD)
+hipError_t launch_volume_redo(int prec, int n, int log2L, const VolFixArgs& a, dim3 grid, hipStream_t st,
+                              bool prepare = false);
 // The relaxed flows' passes (2-D, every mode kept): row_fast_relax steps the points
 // by the reaction term, the column pass in mode HF_RESOLVENT (tiles of
 // resolvent_fast_tile columns).

@@ -364,6 +364,7 @@ __global__ void __launch_bounds__(256) sel_list(const SelListArgs la, int shift)
     const int b = blockIdx.y, tid = threadIdx.x;
     const long long np = a.nplus[b];
     VpSel* st = a.st + b;
+    if (blockIdx.x == 0 && tid == 0) la.clear[b] = 0u;
     if (np <= 0 || np >= a.npts) {  // uniform
         if (blockIdx.x == 0 && tid == 0) {
             st->mode = np <= 0 ? VS_NONE : VS_ALL;

@@ -188,172 +188,39 @@ __device__ __forceinline__ bool vp_point(const T* a, T* tp, T* tm, T& de, bool f
     return false;
 }
 
-// The direction v along which a point that moves to the other determinant turns
-// back (Lemma 7.1: T' = Q (I - 2 v v^t), v the right singular vector of sigma_min),
-// n = 3, 4.  cof(A) = det(A) A^{-t} has the singular vectors of A, and its largest
-// singular value belongs to that vector: the powers of cof^t cof (squared until they
-// have rank one, at most 60 times: two or three do where sigma_n is small) converge
-// to v v^t.  Where sigma_n = sigma_{n-1} to rounding, every direction between their
-// vectors is a closest choice, and the power's largest column is one.  False, v
-// unset, when the cofactors are no more than rounding (rank <= n - 2).
-template <typename T, typename Tio, int n>
-__device__ __forceinline__ bool vp_direction(const Tio* a_in, T* v)
-{
-    const int ex = scale_exponent<Tio, n>(a_in);
-    T a[n * n], C[n * n], M[n * n];
-#pragma unroll
-    for (int k = 0; k < n * n; ++k) a[k] = ldexp((T)a_in[k], -ex);
-    cofactor_n<T, n>(a, C);
-#pragma unroll
-    for (int i = 0; i < n; ++i)
-#pragma unroll
-        for (int j = 0; j < n; ++j) {
-            T m = 0;
-#pragma unroll
-            for (int k = 0; k < n; ++k) m += C[k * n + i] * C[k * n + j];
-            M[i * n + j] = m;
-        }
-#pragma unroll 1
-    for (int it = 0; it < 60; ++it) {
-        T tr = 0;
-#pragma unroll
-        for (int i = 0; i < n; ++i) tr += M[i * n + i];
-        // cofactors below their rounding (the entries of a are below 1), or NaN
-        if (it == 0 && !(tr > (T)(64 * n * n) * num<T>::eps * num<T>::eps)) return false;
-        const T inv = (T)1 / tr;
-        T f2 = 0;
-#pragma unroll
-        for (int k = 0; k < n * n; ++k) {
-            M[k] *= inv;
-            f2 += M[k] * M[k];
-        }
-        if ((T)1 - f2 < (T)8 * num<T>::eps) break;  // 1 - f2 = 0 for rank one
-        T S[n * n];
-#pragma unroll
-        for (int i = 0; i < n; ++i)
-#pragma unroll
-            for (int j = i; j < n; ++j) {
-                T m = 0;
-#pragma unroll
-                for (int k = 0; k < n; ++k) m += M[i * n + k] * M[k * n + j];
-                S[i * n + j] = m;
-                S[j * n + i] = m;
-            }
-#pragma unroll
-        for (int k = 0; k < n * n; ++k) M[k] = S[k];
-    }
-    // v: the column with the largest diagonal entry, refined by one more product
-    // with cof^t cof (its rounding is then that of one product, not of the powers)
-    T best = M[0];
-#pragma unroll
-    for (int i = 0; i < n; ++i) v[i] = M[i * n];
-#pragma unroll
-    for (int j = 1; j < n; ++j) {
-        const bool more = M[j * n + j] > best;
-        best = more ? M[j * n + j] : best;
-#pragma unroll
-        for (int i = 0; i < n; ++i) v[i] = more ? M[i * n + j] : v[i];
-    }
-    T u[n], vv = 0;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-        T m = 0;
-#pragma unroll
-        for (int k = 0; k < n; ++k) m += C[i * n + k] * v[k];
-        u[i] = m;
-    }
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-        T m = 0;
-#pragma unroll
-        for (int k = 0; k < n; ++k) m += C[k * n + i] * u[k];
-        v[i] = m;
-        vv += m * m;
-    }
-    if (!(vv > (T)0)) return false;
-    const T iv = num<T>::rsq(vv);
-#pragma unroll
-    for (int i = 0; i < n; ++i) v[i] *= iv;
-    return true;
-}
-
-// The same from the SVD, for rank <= n - 2 (the zero matrix gives the first axis).
+// A point that moves to the other determinant: T' in q's place from Q and the n values
+// v that the step kept of it, d = T' - Q.
+//   n >= 3: v is the right singular vector of sigma_min, T' = Q (I - 2 v v^t), the
+//     reversal of that direction (Lemma 7.1).  With Q and v of one decomposition, and Q
+//     the one that stands in the spectra to which d is added, T' is as orthogonal as Q
+//     wherever v points (where sigma_{n-1} = sigma_n to rounding it is any vector between
+//     theirs, and every choice is closest).
+//   n = 2: v = (c, s) of the other candidate (vp_candidates); plus: the side it leaves.
+//   n = 1: T' = -Q, v is not used.
 template <typename T, int n>
-__device__ __forceinline__ void vp_direction_svd(const T* a, T* v)
+__device__ __forceinline__ void vp_change(bool plus, const T* v, T* q, T* d)
 {
-    const int ex = scale_exponent<T, n>(a);
-    T W[n][n], V[n][n];
+    if constexpr (n == 1) {
+        d[0] = (T)-2 * q[0];
+        q[0] = -q[0];
+    } else if constexpr (n == 2) {
+        const T t[4] = {v[0], plus ? v[1] : -v[1], v[1], plus ? -v[0] : v[0]};
 #pragma unroll
-    for (int i = 0; i < n; ++i)
-#pragma unroll
-        for (int j = 0; j < n; ++j) {
-            W[i][j] = ldexp(a[i * n + j], -ex);
-            V[i][j] = (i == j) ? (T)1 : (T)0;
+        for (int k = 0; k < 4; ++k) {
+            d[k] = t[k] - q[k];
+            q[k] = t[k];
         }
-    jacobi_sweeps<T, n>(W, V);
-    T sm = 0;
-#pragma unroll
-    for (int j = 0; j < n; ++j) {
-        T w2 = 0;
-#pragma unroll
-        for (int i = 0; i < n; ++i) w2 += W[i][j] * W[i][j];
-        const bool less = j == 0 || w2 < sm;
-        sm = less ? w2 : sm;
-#pragma unroll
-        for (int i = 0; i < n; ++i) v[i] = less ? V[i][j] : v[i];
-    }
-}
-
-// d = -2 (q v) v^t, in the precision of v.
-template <typename T, typename Tio, int n>
-__device__ __forceinline__ void vp_turn(const Tio* q, const T* v, Tio* d)
-{
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-        T u = 0;
-#pragma unroll
-        for (int k = 0; k < n; ++k) u += (T)q[i * n + k] * v[k];
-#pragma unroll
-        for (int k = 0; k < n; ++k) d[i * n + k] = (Tio)((T)-2 * u * v[k]);
-    }
-}
-
-// A point of matrix a that leaves the side `plus` (its Delta E is de): d = T' - Q, and
-// T' in q's place, in the plan's precision T with the double fallback of float plans.
-// q is the very Q that stands in the spectra to which d is added: a Q formed again
-// from a (read back by another sum) is another one where sigma_{n-1} + sigma_n is
-// small, by eps / (sigma_{n-1} + sigma_n) of a turn, and Q + d would be as far from
-// orthogonal.  With v alone taken from a, T' is as orthogonal as q wherever v points.
-template <typename T, int n>
-__device__ __forceinline__ void vp_change(const T* a, bool plus, T de, bool fallback, double sigma_fb, T* q, T* d)
-{
-    if constexpr (n >= 3) {
-        const T half = (de < (T)0 ? -de : de) * (T)0.5;
-        bool done = false;
-        if (sizeof(T) == 4 && fallback && (double)half < sigma_fb) {
-            double v[n];
-            done = vp_direction<double, T, n>(a, v);
-            if (done) vp_turn<double, T, n>(q, v, d);
-        } else {
-            T v[n];
-            done = vp_direction<T, T, n>(a, v);
-            if (done) vp_turn<T, T, n>(q, v, d);
-        }
-        if (!done) {
-            T v[n];
-            vp_direction_svd<T, n>(a, v);
-            vp_turn<T, T, n>(q, v, d);
-        }
-#pragma unroll
-        for (int k = 0; k < n * n; ++k) q[k] += d[k];
     } else {
-        T tp[n * n], tm[n * n], e;
-        (void)vp_point<T, n>(a, tp, tm, e, fallback, sigma_fb);
 #pragma unroll
-        for (int k = 0; k < n * n; ++k) {
-            const T t = plus ? tm[k] : tp[k];
-            d[k] = t - q[k];
-            q[k] = t;
+        for (int i = 0; i < n; ++i) {
+            T u = 0;
+#pragma unroll
+            for (int k = 0; k < n; ++k) u += q[i * n + k] * v[k];
+#pragma unroll
+            for (int k = 0; k < n; ++k) {
+                d[i * n + k] = (T)-2 * u * v[k];
+                q[i * n + k] += d[i * n + k];
+            }
         }
     }
 }
