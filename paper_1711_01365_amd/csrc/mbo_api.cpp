@@ -251,9 +251,11 @@ mbo_status fail(mbo_plan_t p, mbo_status s, const char* fmt, ...)
 #define HIP_TRY(plan, expr)                                                                   \
     do {                                                                                       \
         hipError_t e_ = (expr);                                                                \
-        if (e_ != hipSuccess)                                                                  \
+        if (e_ != hipSuccess) {                                                                \
+            (void)hipGetLastError(); /* reported here, not by the next launch as well */       \
             return fail(plan, e_ == hipErrorOutOfMemory ? MBO_ERR_ALLOC : MBO_ERR_HIP,         \
                         "%s failed: %s", #expr, hipGetErrorString(e_));                        \
+        }                                                                                      \
     } while (0)
 
 template <typename T>
@@ -573,8 +575,6 @@ void config_fast(mbo_plan_t p)
 // (w >= W - c), exp(-4 pi^2 tau kx^2) / N1; 0 in the unused slots.
 mbo_status build_fast_tables(mbo_plan_t p)
 {
-    free_dev(p->lam_col);
-    p->lam_y = nullptr;
     if (!p->fast) return MBO_OK;
     const int W = p->band_W, c = p->band_c;
     const int64_t N1 = p->N[p->d - 1];
@@ -811,6 +811,31 @@ void prepare_fast_kernels(mbo_plan_t p)
             (void)launch_heat_fast(p->pk, ilog2((int)p->N[0]), tx, h, dim3(1), nullptr, true);
     }
     (void)hipGetLastError();
+}
+
+// Layout and tables of the band-limited passes for the plan's tau and path.  On failure
+// the plan keeps the ones it has: the new tables are built beside them.
+mbo_status rebuild_fast(mbo_plan_t p)
+{
+    void *const col = p->lam_col, *const y = p->lam_y;
+    const bool fast = p->fast;
+    const int c = p->band_c, W = p->band_W, tx = p->fast_tx;
+    p->lam_col = p->lam_y = nullptr;
+    config_fast(p);
+    const mbo_status s = build_fast_tables(p);
+    if (s != MBO_OK) {
+        free_dev(p->lam_col);
+        p->lam_col = col;
+        p->lam_y = y;
+        p->fast = fast;
+        p->band_c = c;
+        p->band_W = W;
+        p->fast_tx = tx;
+        return s;
+    }
+    if (col) (void)hipFree(col);
+    prepare_fast_kernels(p);
+    return MBO_OK;
 }
 
 // Energy partials per field and iterate: one per wave of the heat pass.
@@ -1627,9 +1652,7 @@ mbo_status plan_init(mbo_plan_t p, const int64_t* foff_host)
     HIP_TRY(p, hipMalloc(&p->lam_row, nt * (size_t)p->N[0] * p->esz));
     HIP_TRY(p, hipMalloc(&p->lam_inner, nt * (size_t)(p->npts / p->N[0]) * p->esz));
     if ((s = build_symbol_tables(p)) != MBO_OK) return s;
-    config_fast(p);
-    if ((s = build_fast_tables(p)) != MBO_OK) return s;
-    prepare_fast_kernels(p);
+    if ((s = rebuild_fast(p)) != MBO_OK) return s;
     HIP_TRY(p, hipMalloc(&p->mu_row, (size_t)p->N[0] * p->esz));
     HIP_TRY(p, hipMalloc(&p->mu_inner, (size_t)(p->npts / p->N[0]) * p->esz));
     if ((s = build_laplace_tables(p)) != MBO_OK) return s;
@@ -3022,15 +3045,21 @@ mbo_status mbo_plan_set_tau(mbo_plan_t p, double tau)
     if (tau == p->tau) return MBO_OK;  // tables, kept band and graphs stay (an adjoint sets its tau twice a step)
     HIP_TRY(p, hipSetDevice(p->device));
     HIP_TRY(p, hipStreamSynchronize(p->stream));  // tables may be in use by queued work
+    const double before = p->tau;
     p->tau = tau;
-    drop_graph(p);  // the energy reduction bakes tau into its arguments
-    mbo_status s = build_symbol_tables(p);
-    if (s != MBO_OK) return s;
-    // the kept modes depend on tau (the logs' partial count may change with them)
+    mbo_status s = rebuild_fast(p);
+    if (s != MBO_OK) {
+        p->tau = before;
+        return s;
+    }
+    // the kept modes depend on tau (the logs' partial count may change with them), and
+    // the energy reduction bakes tau into its arguments
     drop_logs(p);
-    config_fast(p);
-    if ((s = build_fast_tables(p)) != MBO_OK) return s;
-    prepare_fast_kernels(p);
+    s = build_symbol_tables(p);
+    if (s != MBO_OK) {
+        p->tau = 0.0;  // the tables are of no tau: the next call builds them
+        return s;
+    }
     return MBO_OK;
 }
 
@@ -3045,12 +3074,14 @@ mbo_status mbo_plan_set_path(mbo_plan_t p, mbo_path path)
     drop_graph(p);
     std::vector<mbo_plan_t> plans = p->group ? p->members : std::vector<mbo_plan_t>(1, p);
     for (mbo_plan_t m : plans) {
+        const int before = m->path;
         m->path = pv;
+        const mbo_status s = rebuild_fast(m);
+        if (s != MBO_OK) {
+            m->path = before;
+            return p == m ? s : fail(p, s, "%s", m->err.c_str());
+        }
         drop_logs(m);  // the heat pass's partial count may change
-        config_fast(m);
-        const mbo_status s = build_fast_tables(m);
-        if (s != MBO_OK) return p == m ? s : fail(p, s, "%s", m->err.c_str());
-        prepare_fast_kernels(m);
     }
     return MBO_OK;
 }
