@@ -390,8 +390,12 @@ mbo_status mbo_project_volume(mbo_plan_t plan, const void* A_in, void* A_out, co
  *                                     with det > 0);
  *   flips       [batch][max_iter]     points whose det sign changed;
  *   fallbacks   [batch][max_iter]     points evaluated in double.
- * Runs as one captured HIP graph (re-used while A, max_iter, the energy request
- * and whether n_plus is given stay the same); synchronises at the end. */
+ * Runs as one captured HIP graph (re-used while max_iter, the energy request,
+ * whether n_plus is given and, by the general passes or with n_plus, A stay the same);
+ * synchronises at the end.  A holds intermediate fields during the call.  The first
+ * call allocates Delta E per point and, for the band-limited passes (d = 2), a second
+ * set of kept modes and 12 bytes and (n > 1) n elements per point; where that is
+ * refused the call runs the general passes. */
 mbo_status mbo_iterate_volume(mbo_plan_t plan, void* A, int max_iter, const int64_t* n_plus,
                               int64_t* n_plus_used, double* energy, int64_t* flips, int64_t* fallbacks);
 
@@ -520,7 +524,10 @@ mbo_status mbo_step_static(int64_t N0, int64_t N1, int n, mbo_precision prec, do
  *     dtau[b] += <G~_b, d/dtau e^{tau Delta} A_prev_b>   (device, [batch], double;
  *                                                        skipped when NULL)
  *     G      <- e^{tau Delta} G~  (= Gbar_{s-1}; the heat operator is self-adjoint).
- * Plan-owned workspaces of two fields are allocated on the first call.  No
+ * Plan-owned workspace is allocated on the first call: by the general passes two
+ * fields; by the band-limited ones (d = 2) the kept modes of one, with dtau only, and for
+ * n = 4 and double n = 3 two fields more.  Where the modes are refused memory the call
+ * runs the general passes, as mbo_diffuse_dtau does.  No
  * NaN check (a non-finite input propagates).  G must not alias A_prev. */
 mbo_status mbo_step_vjp(mbo_plan_t plan, const void* A_prev, void* G, double* dtau);
 

@@ -1295,7 +1295,7 @@ mbo_status ensure_volume_fast(mbo_plan_t p)
     const size_t B = (size_t)p->batch, np = B * (size_t)p->npts;
     const size_t zb = B * p->PL * (size_t)p->N[0] * p->band_W * 2 * p->esz;  // a multiple of 256
     if (p->vz && p->vz_bytes >= zb) return MBO_OK;
-    drop_graph(p);  // a captured iteration holds the old buffer
+    if (p->vz) drop_graph(p);  // a captured iteration holds the old buffer
     free_dev(p->vz);
     p->vz_bytes = 0;
     FastRowArgs r;
@@ -1476,9 +1476,10 @@ hipError_t enqueue_iterate_volume_general(mbo_plan_t p, void* A, int K, bool fro
     return hipSuccess;
 }
 
-hipError_t enqueue_iterate_volume(mbo_plan_t p, void* A, int K, bool from_a0, bool want_energy, hipStream_t st)
+hipError_t enqueue_iterate_volume(mbo_plan_t p, void* A, int K, bool fast, bool from_a0, bool want_energy,
+                                  hipStream_t st)
 {
-    const hipError_t e = p->fast && p->d == 2 ? enqueue_iterate_volume_fast(p, A, K, from_a0, want_energy, st)
+    const hipError_t e = fast ? enqueue_iterate_volume_fast(p, A, K, from_a0, want_energy, st)
                                               : enqueue_iterate_volume_general(p, A, K, from_a0, want_energy, st);
     return e == hipSuccess ? enqueue_export_logs(p, K, true, st) : e;
 }
@@ -2024,7 +2025,8 @@ mbo_status grow(mbo_plan_t p, T*& ptr, size_t& have, size_t bytes)
 }
 
 // The adjoint's band-limited column passes (2-D): launch grid, partials per
-// field, workspaces and dynamic-LDS limits, and one pass.
+// field, workspaces and dynamic-LDS limits, and one pass.  Without memory for the
+// transformed columns (MBO_ERR_ALLOC) the calls run the general passes.
 dim3 adj_heat_grid(mbo_plan_t p)
 {
     const int tx = heat_fast_adj_tile(ilog2((int)p->N[0]));
@@ -2083,8 +2085,6 @@ mbo_status step_vjp_fast(mbo_plan_t p, const void* A_prev, void* G, double* dtau
 {
     hipStream_t st = p->stream;
     const bool fused = row_fast_vjp_served(p->pk, p->n);
-    const mbo_status s = ensure_adjoint(p, dtau != nullptr);
-    if (s != MBO_OK) return s;
     const size_t fbytes = (size_t)p->batch * p->n * p->n * (size_t)p->npts * p->esz;
     if (!fused && !p->ws_a) HIP_TRY(p, hipMalloc(&p->ws_a, fbytes));
     if (!fused && !p->ws_g) HIP_TRY(p, hipMalloc(&p->ws_g, fbytes));
@@ -2132,8 +2132,6 @@ mbo_status step_vjp_fast(mbo_plan_t p, const void* A_prev, void* G, double* dtau
 // the same passes (2-D): the sums are those of step_vjp_fast.
 mbo_status diffuse_dtau_fast(mbo_plan_t p, const void* A, void* out, const void* G, double* dot, hipStream_t st)
 {
-    const mbo_status s = ensure_adjoint(p, G != nullptr);
-    if (s != MBO_OK) return s;
     FastRowArgs r0 = fast_row_args(p);
     r0.Ain = A;
     r0.flags = RF_LOAD_REAL | RF_FORWARD;
@@ -3201,7 +3199,13 @@ mbo_status mbo_diffuse_dtau(mbo_plan_t p, const void* A, void* out, const void* 
     if (!out && !want_dot) return fail(p, MBO_ERR_INVALID_ARG, "neither out nor (G, dot) given");
     if ((G == nullptr) != (dot == nullptr)) return fail(p, MBO_ERR_INVALID_ARG, "G and dot go together");
     HIP_TRY(p, hipSetDevice(p->device));
-    if (p->fast && p->d == 2 && !(want_dot && out == G)) {  // out is written before G is read
+    bool fast = p->fast && p->d == 2 && !(want_dot && out == G);  // out is written before G is read
+    if (fast) {
+        const mbo_status s = ensure_adjoint(p, want_dot);
+        if (s != MBO_OK && s != MBO_ERR_ALLOC) return s;
+        fast = s == MBO_OK;
+    }
+    if (fast) {
         const mbo_status s = diffuse_dtau_fast(p, A, out, want_dot ? G : nullptr, p->dsum, p->stream);
         if (s != MBO_OK) return s;
     } else {
@@ -3297,7 +3301,11 @@ mbo_status mbo_step_vjp(mbo_plan_t p, const void* A_prev, void* G, double* dtau)
     if (!A_prev || !G) return fail(p, MBO_ERR_INVALID_ARG, "A_prev / G is NULL");
     if (A_prev == (const void*)G) return fail(p, MBO_ERR_INVALID_ARG, "G must not alias A_prev");
     HIP_TRY(p, hipSetDevice(p->device));
-    if (p->fast && p->d == 2) return step_vjp_fast(p, A_prev, G, dtau);
+    if (p->fast && p->d == 2) {
+        const mbo_status s = ensure_adjoint(p, dtau != nullptr);
+        if (s == MBO_OK) return step_vjp_fast(p, A_prev, G, dtau);
+        if (s != MBO_ERR_ALLOC) return s;
+    }
     const size_t fbytes = (size_t)p->batch * p->n * p->n * (size_t)p->npts * p->esz;
     if (!p->ws_a) HIP_TRY(p, hipMalloc(&p->ws_a, fbytes));
     if (!p->ws_g) HIP_TRY(p, hipMalloc(&p->ws_g, fbytes));
@@ -3608,10 +3616,14 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
     mbo_status s;
     if ((s = ensure_logs(p, K)) != MBO_OK) return s;
     if ((s = ensure_volume(p)) != MBO_OK) return s;
-    if (p->fast && p->d == 2 && (s = ensure_volume_fast(p)) != MBO_OK) return s;
+    // without memory for the band-limited passes' workspace, the general ones
+    bool fast = p->fast && p->d == 2;
+    if (fast && (s = ensure_volume_fast(p)) != MBO_OK) {
+        if (s != MBO_ERR_ALLOC) return s;
+        fast = false;
+    }
     if (!from_a0 && (s = upload_nplus(p, n_plus)) != MBO_OK) return s;
-    const int key = (want_energy ? 1 : 0) | (from_a0 ? 2 : 0);
-    const bool fast = p->fast && p->d == 2;
+    const int key = (want_energy ? 1 : 0) | (from_a0 ? 2 : 0) | (fast ? 4 : 0);
     if (fast) HIP_TRY(p, set_slot_field(p, A, p->stream));
     const void* field = fast && from_a0 ? nullptr : A;
     if (use_graphs()) {
@@ -3620,7 +3632,7 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
             p->vexec = nullptr;
             hipGraph_t g = nullptr;
             HIP_TRY(p, hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
-            hipError_t e = enqueue_iterate_volume(p, A, K, from_a0, want_energy, p->cap);
+            hipError_t e = enqueue_iterate_volume(p, A, K, fast, from_a0, want_energy, p->cap);
             hipError_t e2 = hipStreamEndCapture(p->cap, &g);
             if (e != hipSuccess || e2 != hipSuccess) {
                 if (g) (void)hipGraphDestroy(g);
@@ -3639,7 +3651,7 @@ mbo_status mbo_iterate_volume(mbo_plan_t p, void* A, int max_iter, const int64_t
         }
         HIP_TRY(p, hipGraphLaunch(p->vexec, p->stream));
     } else {
-        HIP_TRY(p, enqueue_iterate_volume(p, A, K, from_a0, want_energy, p->stream));
+        HIP_TRY(p, enqueue_iterate_volume(p, A, K, fast, from_a0, want_energy, p->stream));
     }
     unsigned long long bad = 0;
     if ((s = read_logs(p, K, 0.0, p->stream, nullptr, energy, flips, nullptr, fallbacks, nullptr, &bad)) != MBO_OK)

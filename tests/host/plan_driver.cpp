@@ -68,11 +68,72 @@ static void set_tau(int d)
     CHECK(fake::held == 0);
 }
 
+// The band-limited volume-preserving iteration takes workspace that the general passes
+// do without: where it is refused the call runs those, and the next call tries again.
+static void volume_memory()
+{
+    const int64_t N[2] = {64, 64};
+    mbo_plan_t p = nullptr;
+    CHECK(mbo_plan(&p, 2, N, 3, 2, 1e-3, MBO_F32, 0.0, nullptr) == MBO_OK);
+    if (!p) return;
+    std::vector<float> A((size_t)2 * 9 * 64 * 64, 1.0f);
+    std::vector<double> E((size_t)2 * 4);
+    int64_t used[2];
+    for (int round = 0; round < 2; ++round) {
+        fake::reset();
+        fake::fail_above = 150000;  // the spectra take more, Delta E (32 KB) and the logs less
+        CHECK(mbo_iterate_volume(p, A.data(), 3, nullptr, used, E.data(), nullptr, nullptr) == MBO_OK);
+        CHECK(fake::count("row_fast_vkey") == 0 && fake::count("volume_fix") == 0);
+        CHECK(fake::count("row_vp") == (round == 0 ? 6 : 0));  // the captured call is kept
+        CHECK(fake::count("graph") == 1);
+    }
+    fake::fail_above = 0;
+    fake::reset();
+    CHECK(mbo_iterate_volume(p, A.data(), 3, nullptr, used, E.data(), nullptr, nullptr) == MBO_OK);
+    CHECK(fake::count("row_fast_vkey") == 3 && fake::count("volume_fix") == 3 && fake::count("row_vp") == 0);
+    CHECK(mbo_plan_destroy(p) == MBO_OK);
+    CHECK(fake::held == 0);
+}
+
+// The same of the adjoint's calls.
+static void adjoint_memory()
+{
+    const int64_t N[2] = {64, 64};
+    for (int n = 2; n <= 4; ++n) {
+        mbo_plan_t p = nullptr;
+        CHECK(mbo_plan(&p, 2, N, n, 1, 1e-3, MBO_F64, 0.0, nullptr) == MBO_OK);
+        if (!p) return;
+        CHECK(mbo_plan_set_path(p, MBO_PATH_FULL) == MBO_OK);  // spectra larger than a field
+        std::vector<double> A((size_t)n * n * 64 * 64, 1.0), G(A.size()), O(A.size());
+        double dtau = 0.0, dot = 0.0;
+        const size_t field = A.size() * 8, spec = (size_t)(n * n + 1) / 2 * 64 * 64 * 16;
+        fake::fail_above = n == 3 ? field : spec - 1;  // n = 2, 4: as large as a field
+        fake::reset();
+        CHECK(mbo_diffuse_dtau(p, A.data(), O.data(), G.data(), &dot) == MBO_OK);
+        CHECK(fake::count("heat_fast_adj") == 0 && fake::count("col") == 1);
+        if (n == 3) {
+            CHECK(mbo_step_vjp(p, A.data(), G.data(), &dtau) == MBO_OK);
+            CHECK(fake::count("heat_fast_adj") == 0 && fake::count("vjp") == 1);
+        } else {
+            CHECK(mbo_step_vjp(p, A.data(), G.data(), &dtau) == MBO_ERR_ALLOC);  // the general passes need two fields
+        }
+        fake::fail_above = 0;
+        fake::reset();
+        CHECK(mbo_step_vjp(p, A.data(), G.data(), &dtau) == MBO_OK);
+        CHECK(mbo_diffuse_dtau(p, A.data(), O.data(), G.data(), &dot) == MBO_OK);
+        CHECK(fake::count("heat_fast_adj") > 0 && fake::count("col") == 0);
+        CHECK(mbo_plan_destroy(p) == MBO_OK);
+        CHECK(fake::held == 0);
+    }
+}
+
 int main(int argc, char** argv)
 {
     const char* s = argc > 1 ? argv[1] : "";
     if (!std::strcmp(s, "set_tau_2d")) set_tau(2);
     else if (!std::strcmp(s, "set_tau_3d")) set_tau(3);
+    else if (!std::strcmp(s, "volume_memory")) volume_memory();
+    else if (!std::strcmp(s, "adjoint_memory")) adjoint_memory();
     else return 2;
     if (!bad) std::printf("ok\n");
     return bad;
