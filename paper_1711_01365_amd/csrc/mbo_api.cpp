@@ -2419,9 +2419,23 @@ mbo_status sfail(mbo_surface_t s, mbo_status st, const char* fmt, ...)
 #define SHIP(surf, expr)                                                                      \
     do {                                                                                      \
         hipError_t e_ = (expr);                                                               \
-        if (e_ != hipSuccess)                                                                 \
+        if (e_ != hipSuccess) {                                                               \
+            (void)hipGetLastError(); /* reported here, not by the next launch as well */      \
             return sfail(surf, e_ == hipErrorOutOfMemory ? MBO_ERR_ALLOC : MBO_ERR_HIP,       \
                          "%s failed: %s", #expr, hipGetErrorString(e_));                      \
+        }                                                                                     \
+    } while (0)
+
+// An allocation that the surface can do without: null where memory is short.
+#define SHIP_OPTIONAL(surf, ptr, bytes)                                                       \
+    do {                                                                                      \
+        const hipError_t o_ = hipMalloc((void**)&(ptr), (bytes));                             \
+        if (o_ == hipErrorOutOfMemory) {                                                      \
+            (void)hipGetLastError();                                                          \
+            (ptr) = nullptr;                                                                  \
+        } else {                                                                              \
+            SHIP(surf, o_);                                                                   \
+        }                                                                                     \
     } while (0)
 
 void surface_free(mbo_surface_t s)
@@ -2545,9 +2559,11 @@ mbo_status build_bins_t(mbo_surface_t s, const std::vector<double>& pts, const s
             i = e;
         }
         if (inside && gr.size() < (size_t)1 << 30) {
-            SHIP(s, hipMalloc((void**)&s->groups, gr.size() * sizeof(SurfGroup)));
-            SHIP(s, hipMemcpy(s->groups, gr.data(), gr.size() * sizeof(SurfGroup), hipMemcpyHostToDevice));
-            s->ngroups = (int)gr.size();
+            SHIP_OPTIONAL(s, s->groups, gr.size() * sizeof(SurfGroup));
+            if (s->groups) {
+                SHIP(s, hipMemcpy(s->groups, gr.data(), gr.size() * sizeof(SurfGroup), hipMemcpyHostToDevice));
+                s->ngroups = (int)gr.size();
+            }
         }
     }
     if ((st = upload_as(s, &B.pos, pos)) != MBO_OK) return st;
@@ -2639,7 +2655,7 @@ SurfArgs surf_args(mbo_surface_t s, const mbo_surface_s::Bins& B)
     return a;
 }
 
-// Device state of the volume-preserving step, allocated on first use.
+// The flip counters of K steps.
 hipError_t grow_flips(mbo_surface_t s, int K)
 {
     if (s->flips_K >= K) return hipSuccess;
@@ -2653,9 +2669,9 @@ hipError_t grow_flips(mbo_surface_t s, int K)
 // Tables and workspace of the separable spreading (launch_surface_sep) for the
 // cells of lattice corners corner[c] = dx (i, j, k), in canonical order.  Leaves
 // s->sep.t1 null, and the cell kernels in use, when the lattice's lines do not fit
-// in LDS or its two intermediate fields (zeros outside the band included) would be
-// more than 512 MiB and more than eight times the field: thin bands of wide
-// lattices.  Their traffic is what bounds the passes, and the cell kernels' work
+// in LDS, its two intermediate fields (zeros outside the band included) are refused
+// memory, or would be more than 512 MiB and more than eight times the field: thin bands
+// of wide lattices.  Their traffic is what bounds the passes, and the cell kernels' work
 // does not depend on the lattice.
 mbo_status build_sep(mbo_surface_t s, const std::vector<std::array<double, 3>>& corners, const double* nx,
                      const double* nw)
@@ -2763,7 +2779,8 @@ mbo_status build_sep(mbo_surface_t s, const std::vector<std::array<double, 3>>& 
         o_wt[d] = off;
         off += up(wt[d].size() * s->esz);
     }
-    SHIP(s, hipMalloc(&s->sep_block, off));
+    SHIP_OPTIONAL(s, s->sep_block, off);
+    if (!s->sep_block) return MBO_OK;
     char* base = static_cast<char*>(s->sep_block);
     SHIP(s, hipMemcpy(base + o_run, run.data(), run.size() * sizeof(SepRun), hipMemcpyHostToDevice));
     SHIP(s, hipMemcpy(base + o_cs, col_start.data(), col_start.size() * 8, hipMemcpyHostToDevice));
@@ -2785,6 +2802,7 @@ mbo_status build_sep(mbo_surface_t s, const std::vector<std::array<double, 3>>& 
     return MBO_OK;
 }
 
+// Device state of the volume-preserving step, allocated on first use.
 mbo_status ensure_surface_volume(mbo_surface_t s)
 {
     if (s->wsel) return MBO_OK;

@@ -127,6 +127,45 @@ static void adjoint_memory()
     }
 }
 
+// A surface whose axis passes or interpolation groups are refused memory is created with
+// the cell kernels or the general interpolation.
+static void surface_memory()
+{
+    int cells = 0, general = 0, refused = 0;
+    for (int k = 0;; ++k) {
+        mbo_surface_t s = nullptr;
+        fake::fail_in = k;  // the k-th allocation of the creation, none for 0
+        const mbo_status st = mbo_surface_sphere(&s, 1.0, 0.2, 3, 0.01, 1e-4, 2, MBO_F32, nullptr);
+        const bool hit = k > 0 && fake::fail_in == 0;
+        fake::fail_in = 0;
+        CHECK(hit || st == MBO_OK);
+        if (!s) {
+            CHECK(st == MBO_ERR_ALLOC);
+            CHECK(fake::held == 0);
+            ++refused;
+            continue;
+        }
+        int64_t m = 0, nc = 0;
+        int grid = 0;
+        double w = 0.0;
+        CHECK(mbo_surface_info(s, &m, &nc, &grid, &w) == MBO_OK);
+        std::vector<float> A((size_t)4 * (size_t)m, 1.0f), B(A.size());
+        fake::reset();
+        CHECK(mbo_surface_diffuse(s, A.data(), B.data()) == MBO_OK);
+        const bool sep = fake::count("surface_sep") == 1, gr = fake::count("interp_groups") == 1;
+        CHECK(sep || (fake::count("spread_cells") == 1 && fake::count("surface_gather") == 1));
+        CHECK(gr || fake::count("surface_interp") == 1);
+        CHECK(hit || (sep && gr));
+        cells += !sep;
+        general += !gr;
+        CHECK(mbo_surface_destroy(s) == MBO_OK);
+        CHECK(fake::held == 0);
+        if (k > 0 && !hit) break;
+    }
+    CHECK(cells == 1 && general == 1);
+    CHECK(refused > 5);
+}
+
 int main(int argc, char** argv)
 {
     const char* s = argc > 1 ? argv[1] : "";
@@ -134,6 +173,7 @@ int main(int argc, char** argv)
     else if (!std::strcmp(s, "set_tau_3d")) set_tau(3);
     else if (!std::strcmp(s, "volume_memory")) volume_memory();
     else if (!std::strcmp(s, "adjoint_memory")) adjoint_memory();
+    else if (!std::strcmp(s, "surface_memory")) surface_memory();
     else return 2;
     if (!bad) std::printf("ok\n");
     return bad;
