@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -122,7 +123,7 @@ struct mbo_plan_s {
     double* ws_dot = nullptr;
     size_t ws_spec_bytes = 0, ws_dot_bytes = 0;
     bool adj_ready = false;  // their dynamic-LDS limits are set
-    unsigned long long* counters = nullptr;  // project: [0] nonfinite, [1] fallbacks, zero between calls
+    unsigned long long* counters = nullptr;  // project: [0] nonfinite, [1] fallbacks, zero between calls (behind tw[0])
 
     // per-field diffusion times (fields of a batched plan): tables per field
     bool per_field_tau = false;
@@ -265,6 +266,51 @@ void free_dev(T*& p)
     p = nullptr;
 }
 
+// Pinned buffers for the logs of small calls, shared by all plans: allocating one takes
+// 28 us and freeing it 250 (a program's first small call on a plan some 40), so a plan
+// gives its buffer back here, after its stream has finished.  At most PINNED_KEPT are
+// kept; larger ones are the plan's alone.
+constexpr size_t PINNED_WORDS = 512, PINNED_KEPT = 16;
+struct PinnedPool {
+    std::mutex m;
+    std::vector<unsigned long long*> kept;
+};
+
+PinnedPool& pinned_pool()
+{
+    static PinnedPool* pool = new PinnedPool;  // never destroyed: plans may outlive static objects
+    return *pool;
+}
+
+hipError_t pinned_alloc(unsigned long long** ptr, size_t* words)
+{
+    if (*words <= PINNED_WORDS) {
+        *words = PINNED_WORDS;
+        PinnedPool& pool = pinned_pool();
+        std::lock_guard<std::mutex> lock(pool.m);
+        if (!pool.kept.empty()) {
+            *ptr = pool.kept.back();
+            pool.kept.pop_back();
+            return hipSuccess;
+        }
+    }
+    return hipHostMalloc((void**)ptr, *words * 8, hipHostMallocPortable);
+}
+
+void pinned_free(unsigned long long* ptr, size_t words)
+{
+    if (!ptr) return;
+    if (words == PINNED_WORDS) {
+        PinnedPool& pool = pinned_pool();
+        std::lock_guard<std::mutex> lock(pool.m);
+        if (pool.kept.size() < PINNED_KEPT) {
+            pool.kept.push_back(ptr);
+            return;
+        }
+    }
+    (void)hipHostFree(ptr);
+}
+
 void drop_graph(mbo_plan_t p)
 {
     if (p->gexec) (void)hipGraphExecDestroy(p->gexec);
@@ -302,10 +348,8 @@ void destroy(mbo_plan_t p)
         p->tw[a] = nullptr;
     }
     free_dev(p->lam_row);
-    free_dev(p->lam_inner);
     free_dev(p->lam_col);
     free_dev(p->mu_row);
-    free_dev(p->mu_inner);
     free_dev(p->dpart);
     free_dev(p->dsum);
     free_dev(p->ws_a);
@@ -314,9 +358,8 @@ void destroy(mbo_plan_t p)
     free_dev(p->ws_dot);
     free_dev(p->taus_dev);
     free_dev(p->foff_dev);
-    free_dev(p->counters);
     free_dev(p->log_block);
-    if (p->log_host) (void)hipHostFree(p->log_host);
+    pinned_free(p->log_host, p->log_host_words);
     p->log_host = nullptr;
     free_dev(p->slot);
     free_dev(p->vde);
@@ -384,9 +427,8 @@ mbo_status build_symbol_tables(mbo_plan_t p)
                 for (int64_t x = 0; x < p->N[2]; ++x) inner.push_back(ly[(size_t)y] * lx[(size_t)x]);
         }
     }
-    mbo_status s = upload(p, p->lam_row, row);
-    if (s != MBO_OK) return s;
-    return upload(p, p->lam_inner, inner);
+    row.insert(row.end(), inner.begin(), inner.end());  // side by side
+    return upload(p, p->lam_row, row);
 }
 
 // -4 pi^2 k^2 per index of an axis (same wrap-around as axis_symbol).
@@ -414,9 +456,8 @@ mbo_status build_laplace_tables(mbo_plan_t p)
         for (int64_t y = 0; y < p->N[1]; ++y)
             for (int64_t x = 0; x < p->N[2]; ++x) inner[(size_t)(y * p->N[2] + x)] = ly[(size_t)y] + lx[(size_t)x];
     }
-    mbo_status s = upload(p, p->mu_row, row);
-    if (s != MBO_OK) return s;
-    return upload(p, p->mu_inner, inner);
+    row.insert(row.end(), inner.begin(), inner.end());  // side by side
+    return upload(p, p->mu_row, row);
 }
 
 // Kept half-width of the row axis for the band-limited passes (2-D).  The
@@ -907,11 +948,12 @@ mbo_status ensure_logs(mbo_plan_t p, int K)
         // one more word per field: the volume-preserving step's counts
         const size_t hw = words + (size_t)p->batch;
         if (p->log_host_words < hw) {
-            if (p->log_host) (void)hipHostFree(p->log_host);
+            pinned_free(p->log_host, p->log_host_words);
             p->log_host = nullptr;
             p->log_host_words = 0;
-            HIP_TRY(p, hipHostMalloc((void**)&p->log_host, hw * 8, hipHostMallocDefault));
-            p->log_host_words = hw;
+            size_t got = hw;
+            HIP_TRY(p, pinned_alloc(&p->log_host, &got));
+            p->log_host_words = got;
         }
         HIP_TRY(p, hipMalloc(&p->log_block, (words + ep + cp) * 8));
         p->epart = static_cast<double*>(p->log_block) + words;
@@ -1639,23 +1681,26 @@ mbo_status plan_init(mbo_plan_t p, const int64_t* foff_host)
     const size_t zbytes = (size_t)batch * p->PL * (size_t)p->npts * 2 * p->esz;
     HIP_TRY(p, hipMalloc(&p->Z, zbytes));
     HIP_TRY(p, hipMalloc((void**)&p->sgn, (size_t)batch * (size_t)p->npts));
-    HIP_TRY(p, hipMalloc((void**)&p->counters, 4 * sizeof(unsigned long long)));
-    const unsigned long long zero[4] = {0, 0, 0, 0};
-    HIP_TRY(p, hipMemcpy(p->counters, zero, sizeof zero, hipMemcpyHostToDevice));
     for (int a = 0; a < p->d; ++a) {
         for (int b = 0; b < a; ++b)
             if (p->N[b] == p->N[a]) p->tw[a] = p->tw[b];
         if (p->tw[a]) continue;
-        HIP_TRY(p, hipMalloc(&p->tw[a], (size_t)p->N[a] * 2 * p->esz));
-        if ((s = upload(p, p->tw[a], twiddles(p->N[a]))) != MBO_OK) return s;
+        std::vector<double> tw = twiddles(p->N[a]);
+        // the first table is followed by the zeroed counters (one allocation and copy)
+        if (a == 0) tw.resize(tw.size() + 32 / p->esz, 0.0);
+        HIP_TRY(p, hipMalloc(&p->tw[a], tw.size() * p->esz));
+        if ((s = upload(p, p->tw[a], tw)) != MBO_OK) return s;
+        if (a == 0)
+            p->counters = reinterpret_cast<unsigned long long*>(static_cast<char*>(p->tw[0]) +
+                                                                (size_t)p->N[0] * 2 * p->esz);
     }
     const size_t nt = p->per_field_tau ? (size_t)batch : 1;
-    HIP_TRY(p, hipMalloc(&p->lam_row, nt * (size_t)p->N[0] * p->esz));
-    HIP_TRY(p, hipMalloc(&p->lam_inner, nt * (size_t)(p->npts / p->N[0]) * p->esz));
+    HIP_TRY(p, hipMalloc(&p->lam_row, nt * (size_t)(p->N[0] + p->npts / p->N[0]) * p->esz));
+    p->lam_inner = static_cast<char*>(p->lam_row) + nt * (size_t)p->N[0] * p->esz;
     if ((s = build_symbol_tables(p)) != MBO_OK) return s;
     if ((s = rebuild_fast(p)) != MBO_OK) return s;
-    HIP_TRY(p, hipMalloc(&p->mu_row, (size_t)p->N[0] * p->esz));
-    HIP_TRY(p, hipMalloc(&p->mu_inner, (size_t)(p->npts / p->N[0]) * p->esz));
+    HIP_TRY(p, hipMalloc(&p->mu_row, (size_t)(p->N[0] + p->npts / p->N[0]) * p->esz));
+    p->mu_inner = static_cast<char*>(p->mu_row) + (size_t)p->N[0] * p->esz;
     if ((s = build_laplace_tables(p)) != MBO_OK) return s;
     // dot partials: one per row workgroup, sized for any rows-per-workgroup choice
     HIP_TRY(p, hipMalloc((void**)&p->dpart,
@@ -3864,6 +3909,10 @@ mbo_status surface_create(mbo_surface_t* out, int kind, double radius, double dx
     (void)hipGetLastError();
     // spreading: by one pass per axis of the lattice where that serves the band ...
     if ((st = build_sep(s, corners, nx, nw)) != MBO_OK) return bail(st);
+    if (s->sep.t1) {
+        (void)launch_surface_sep(s->pk, s->sep, nullptr, s->grid->lds_max);
+        (void)hipGetLastError();
+    }
     // ... else whole cells when the cell kernel's LDS (tile plus per-wave
     // scratch) fits with at least one wave, else sample by sample
     s->U = s->w + (int)std::ceil(dx * (nx[p - 1] - nx[0]) / s->h * (1.0 + 1e-4) + 1e-4);

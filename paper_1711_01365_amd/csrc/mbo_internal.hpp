@@ -316,7 +316,8 @@ struct SurfSepArgs {
     void* t2;                // [n*n][len[0]][Ng][Ng]
     void* Z;                 // grid [PL][Ng^3] complex
 };
-hipError_t launch_surface_sep(int prec, const SurfSepArgs& a, hipStream_t st);
+// prepare_lds: nothing is launched, the kernels' dynamic-LDS limit is set to so many bytes
+hipError_t launch_surface_sep(int prec, const SurfSepArgs& a, hipStream_t st, size_t prepare_lds = 0);
 int sep_tile(int len_x, int len_y, size_t esz, size_t lds_max);  // 0: the lines do not fit
 size_t sep_z_lds(int p, int len_z, int Ng, size_t esz);
 

@@ -303,30 +303,31 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? 8 : 4) surface_interp_gr
 // Launchers
 // ---------------------------------------------------------------------------
 template <typename T, int P>
-static hipError_t sep_z_p(const SurfSepArgs& a, hipStream_t st)
+static hipError_t sep_z_p(const SurfSepArgs& a, hipStream_t st, size_t prepare_lds)
 {
     constexpr int AB = P <= 4 ? P * P : P;
     const int nt = a.Ng > 256 ? a.Ng : 256, E = nt / a.Ng;
     const size_t lds = (size_t)E * AB * a.len[2] * sizeof(T);
-    const void* f = reinterpret_cast<const void*>(&sep_z<T, P, AB>);
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    if (prepare_lds)
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&sep_z<T, P, AB>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)prepare_lds);
     const dim3 g((unsigned)a.ncols, (unsigned)(((a.nn + E - 1) / E) * (AB == P * P ? 1 : P)));
     hipLaunchKernelGGL((sep_z<T, P, AB>), g, dim3(nt), lds, st, a);
     return hipGetLastError();
 }
 
 template <typename T, int ZT>
-static hipError_t sep_yx(const SurfSepArgs& a, hipStream_t st)
+static hipError_t sep_yx(const SurfSepArgs& a, hipStream_t st, size_t prepare_lds)
 {
     const size_t ly = (size_t)2 * (a.len[1] + 2 * SEP_PAD) * ZT * sizeof(T);
     const size_t lx = (size_t)2 * (a.len[0] + 2 * SEP_PAD) * ZT * sizeof(T);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sep_y<T, ZT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)ly);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sep_x<T, ZT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lx);
-    if (e != hipSuccess) return e;
+    if (prepare_lds) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sep_y<T, ZT>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)prepare_lds);
+        if (e != hipSuccess) return e;
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&sep_x<T, ZT>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)prepare_lds);
+    }
     const unsigned zt = (unsigned)(a.Ng / ZT);
     hipLaunchKernelGGL((sep_y<T, ZT>), dim3((unsigned)a.len[0], zt, (unsigned)((a.nn + 1) / 2)), dim3(256), ly, st,
                        a);
@@ -352,32 +353,32 @@ size_t sep_z_lds(int p, int len_z, int Ng, size_t esz)
 }
 
 template <typename T>
-static hipError_t sep_t(const SurfSepArgs& a, hipStream_t st)
+static hipError_t sep_t(const SurfSepArgs& a, hipStream_t st, size_t prepare_lds)
 {
     if (a.Ng < 64 || a.Ng > 512 || a.Ng % 32 || a.ncols < 1) return hipErrorInvalidValue;
     hipError_t e = hipErrorInvalidValue;
     switch (a.p) {
-    case 1: e = sep_z_p<T, 1>(a, st); break;
-    case 2: e = sep_z_p<T, 2>(a, st); break;
-    case 3: e = sep_z_p<T, 3>(a, st); break;
-    case 4: e = sep_z_p<T, 4>(a, st); break;
-    case 5: e = sep_z_p<T, 5>(a, st); break;
-    case 6: e = sep_z_p<T, 6>(a, st); break;
-    case 7: e = sep_z_p<T, 7>(a, st); break;
-    case 8: e = sep_z_p<T, 8>(a, st); break;
+    case 1: e = sep_z_p<T, 1>(a, st, prepare_lds); break;
+    case 2: e = sep_z_p<T, 2>(a, st, prepare_lds); break;
+    case 3: e = sep_z_p<T, 3>(a, st, prepare_lds); break;
+    case 4: e = sep_z_p<T, 4>(a, st, prepare_lds); break;
+    case 5: e = sep_z_p<T, 5>(a, st, prepare_lds); break;
+    case 6: e = sep_z_p<T, 6>(a, st, prepare_lds); break;
+    case 7: e = sep_z_p<T, 7>(a, st, prepare_lds); break;
+    case 8: e = sep_z_p<T, 8>(a, st, prepare_lds); break;
     }
     if (e != hipSuccess) return e;
     switch (a.zt) {
-    case 32: return sep_yx<T, 32>(a, st);
-    case 16: return sep_yx<T, 16>(a, st);
-    case 8: return sep_yx<T, 8>(a, st);
+    case 32: return sep_yx<T, 32>(a, st, prepare_lds);
+    case 16: return sep_yx<T, 16>(a, st, prepare_lds);
+    case 8: return sep_yx<T, 8>(a, st, prepare_lds);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_surface_sep(int prec, const SurfSepArgs& a, hipStream_t st)
+hipError_t launch_surface_sep(int prec, const SurfSepArgs& a, hipStream_t st, size_t prepare_lds)
 {
-    return prec == 0 ? sep_t<double>(a, st) : sep_t<float>(a, st);
+    return prec == 0 ? sep_t<double>(a, st, prepare_lds) : sep_t<float>(a, st, prepare_lds);
 }
 
 template <typename T, int W2>

@@ -3,6 +3,7 @@
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 
 namespace fake {
 int fail_in = 0;
@@ -10,12 +11,15 @@ size_t fail_above = 0, held = 0;
 std::map<std::string, int> launches;
 std::vector<std::string> order;
 mbo::FastColArgs heat;
+int host_allocs = 0, host_frees = 0;
 static std::map<void*, size_t> size_of;
+static std::mutex mutex;
 static hipError_t last = hipSuccess;  // until hipGetLastError, also by the next launcher
 
 static hipError_t note(const char* name, hipStream_t st, bool prepare = false)
 {
     if (prepare) return hipSuccess;
+    std::lock_guard<std::mutex> lock(mutex);
     ++launches[name];
     order.push_back(std::string(name) + "@" + std::to_string((unsigned long long)(uintptr_t)st));
     return hipGetLastError();
@@ -25,6 +29,7 @@ static hipError_t note(const char* name, hipStream_t st, bool prepare = false)
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n)
 {
+    std::lock_guard<std::mutex> lock(fake::mutex);
     if (fake::fail_in > 0 && --fake::fail_in == 0) return fake::last = hipErrorOutOfMemory;
     if (fake::fail_above && n > fake::fail_above) return fake::last = hipErrorOutOfMemory;
     *p = std::malloc(n ? n : 1);
@@ -34,6 +39,7 @@ hipError_t hipMalloc(void** p, size_t n)
 }
 hipError_t hipFree(void* p)
 {
+    std::lock_guard<std::mutex> lock(fake::mutex);
     if (p) {
         fake::held -= fake::size_of.at(p);
         fake::size_of.erase(p);
@@ -43,11 +49,15 @@ hipError_t hipFree(void* p)
 }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned)
 {
+    std::lock_guard<std::mutex> lock(fake::mutex);
+    ++fake::host_allocs;
     *p = std::calloc(n ? n : 1, 1);
     return hipSuccess;
 }
 hipError_t hipHostFree(void* p)
 {
+    std::lock_guard<std::mutex> lock(fake::mutex);
+    ++fake::host_frees;
     std::free(p);
     return hipSuccess;
 }
@@ -196,7 +206,10 @@ hipError_t launch_row_vp(int, int, int, const RowArgs&, dim3, dim3, size_t, hipS
 {
     return note("row_vp", st, prepare);
 }
-hipError_t launch_surface_sep(int, const SurfSepArgs&, hipStream_t st) { return note("surface_sep", st); }
+hipError_t launch_surface_sep(int, const SurfSepArgs&, hipStream_t st, size_t prepare_lds)
+{
+    return note("surface_sep", st, prepare_lds != 0);
+}
 int sep_tile(int len_x, int len_y, size_t esz, size_t lds_max)
 {
     return (size_t)2 * ((len_x > len_y ? len_x : len_y) + 16) * esz * 8 <= lds_max ? 8 : 0;

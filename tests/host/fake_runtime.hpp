@@ -16,6 +16,7 @@ extern std::map<std::string, int> launches;  // by launcher
 extern std::vector<std::string> order;       // the launches in order, with their stream ("name@stream")
 extern mbo::FastColArgs heat;     // arguments of the last launch_heat_fast
 extern size_t held;               // bytes of device memory in use
+extern int host_allocs, host_frees;  // of pinned memory
 inline int count(const std::string& n) { return launches.count(n) ? launches[n] : 0; }
 inline void reset()
 {

@@ -2,7 +2,9 @@
 // Each scenario prints "ok" or what went wrong; run by tests/test_host_runtime.py.
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <thread>
 #include <vector>
 
 #include "fake_runtime.hpp"
@@ -166,6 +168,54 @@ static void surface_memory()
     CHECK(refused > 5);
 }
 
+// Pinned buffers of small logs outlive their plans: plans that come and go use the same
+// one, at most 16 are kept, a large one is the plan's own, and threads share them.
+static void pinned_buffers()
+{
+    const int64_t N[2] = {64, 64};
+    std::vector<double> A((size_t)4 * 64 * 64, 1.0), B(A.size());
+    auto plan = [&] {
+        mbo_plan_t p = nullptr;
+        CHECK(mbo_plan(&p, 2, N, 2, 1, 1e-3, MBO_F64, 0.0, nullptr) == MBO_OK);
+        return p;
+    };
+    for (int i = 0; i < 5; ++i) {
+        mbo_plan_t p = plan();
+        CHECK(mbo_project(p, A.data(), B.data(), nullptr) == MBO_OK);
+        CHECK(mbo_plan_destroy(p) == MBO_OK);
+    }
+    CHECK(fake::host_allocs == 1 && fake::host_frees == 0);
+    std::vector<mbo_plan_t> many;
+    for (int i = 0; i < 40; ++i) {
+        many.push_back(plan());
+        CHECK(mbo_project(many.back(), A.data(), B.data(), nullptr) == MBO_OK);
+    }
+    CHECK(fake::host_allocs == 40);
+    for (mbo_plan_t p : many) CHECK(mbo_plan_destroy(p) == MBO_OK);
+    CHECK(fake::host_frees == 24);
+    mbo_plan_t p = plan();
+    std::vector<int64_t> flips(2000);
+    CHECK(mbo_iterate(p, A.data(), 2000, 0.0, nullptr, nullptr, flips.data(), nullptr, nullptr) == MBO_OK);
+    CHECK(fake::host_allocs == 41);
+    CHECK(mbo_plan_destroy(p) == MBO_OK);
+    CHECK(fake::host_frees == 25);
+    std::vector<std::thread> th;
+    for (int t = 0; t < 4; ++t)
+        th.emplace_back([&, t] {
+            std::vector<double> X((size_t)4 * 64 * 64, 1.0);
+            for (int i = 0; i < 20; ++i) {
+                mbo_plan_t q = nullptr;
+                if (mbo_plan(&q, 2, N, 2, 1, 1e-3, MBO_F64, 0.0, nullptr) != MBO_OK) std::abort();
+                double e = 0.0;
+                if (mbo_energy(q, X.data(), &e) != MBO_OK) std::abort();
+                (void)mbo_plan_destroy(q);
+            }
+        });
+    for (std::thread& t : th) t.join();
+    CHECK(fake::host_allocs == 41 && fake::host_frees == 25);
+    CHECK(fake::held == 0);
+}
+
 int main(int argc, char** argv)
 {
     const char* s = argc > 1 ? argv[1] : "";
@@ -174,6 +224,7 @@ int main(int argc, char** argv)
     else if (!std::strcmp(s, "volume_memory")) volume_memory();
     else if (!std::strcmp(s, "adjoint_memory")) adjoint_memory();
     else if (!std::strcmp(s, "surface_memory")) surface_memory();
+    else if (!std::strcmp(s, "pinned_buffers")) pinned_buffers();
     else return 2;
     if (!bad) std::printf("ok\n");
     return bad;
