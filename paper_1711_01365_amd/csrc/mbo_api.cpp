@@ -246,17 +246,17 @@ mbo_status fail(mbo_plan_t p, mbo_status s, const char* fmt, ...)
     va_end(ap);
     if (p) p->err = buf;
     else g_plan_error = buf;
+    // an error reported here is not reported by the next launch as well
+    if (s == MBO_ERR_HIP || s == MBO_ERR_ALLOC) (void)hipGetLastError();
     return s;
 }
 
 #define HIP_TRY(plan, expr)                                                                   \
     do {                                                                                       \
         hipError_t e_ = (expr);                                                                \
-        if (e_ != hipSuccess) {                                                                \
-            (void)hipGetLastError(); /* reported here, not by the next launch as well */       \
+        if (e_ != hipSuccess)                                                                  \
             return fail(plan, e_ == hipErrorOutOfMemory ? MBO_ERR_ALLOC : MBO_ERR_HIP,         \
                         "%s failed: %s", #expr, hipGetErrorString(e_));                        \
-        }                                                                                      \
     } while (0)
 
 template <typename T>
@@ -3180,7 +3180,11 @@ mbo_status mbo_plan_set_stream(mbo_plan_t p, void* hip_stream)
 {
     if (!p) return MBO_ERR_INVALID_ARG;
     p->stream = (hipStream_t)hip_stream;
-    for (mbo_plan_t m : p->members) m->stream = (hipStream_t)hip_stream;
+    p->slot_A = nullptr;  // a write of the field's pointer may still be queued on the old stream
+    for (mbo_plan_t m : p->members) {
+        m->stream = (hipStream_t)hip_stream;
+        m->slot_A = nullptr;
+    }
     return MBO_OK;
 }
 

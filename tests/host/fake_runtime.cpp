@@ -7,6 +7,7 @@
 
 namespace fake {
 int fail_in = 0;
+bool fail_instantiate = false;
 size_t fail_above = 0, held = 0;
 std::map<std::string, int> launches;
 std::vector<std::string> order;
@@ -115,6 +116,7 @@ hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g)
 }
 hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t)
 {
+    if (fake::fail_instantiate) return fake::last = hipErrorOutOfMemory;
     *e = (hipGraphExec_t)std::malloc(1);
     return hipSuccess;
 }

@@ -12,6 +12,7 @@
 namespace fake {
 extern int fail_in;               // > 0: the fail_in-th hipMalloc from now is refused
 extern size_t fail_above;         // > 0: every hipMalloc of more bytes is refused
+extern bool fail_instantiate;     // hipGraphInstantiate is refused
 extern std::map<std::string, int> launches;  // by launcher
 extern std::vector<std::string> order;       // the launches in order, with their stream ("name@stream")
 extern mbo::FastColArgs heat;     // arguments of the last launch_heat_fast

@@ -1,9 +1,11 @@
 // Host side of plans under refused allocations and changed streams (fake_runtime.hpp).
 // Each scenario prints "ok" or what went wrong; run by tests/test_host_runtime.py.
 #include <cmath>
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <string>
 #include <thread>
 #include <vector>
 
@@ -216,6 +218,46 @@ static void pinned_buffers()
     CHECK(fake::held == 0);
 }
 
+// The device word of the field's pointer is written on the stream that reads it: also
+// when a call that wrote it ended early on another stream.
+static void field_word()
+{
+    const int64_t N[2] = {64, 64};
+    std::vector<double> A((size_t)2 * 4 * 64 * 64, 1.0);
+    hipStream_t s1 = nullptr, s2 = nullptr;
+    CHECK(hipStreamCreateWithFlags(&s1, 0) == hipSuccess && hipStreamCreateWithFlags(&s2, 0) == hipSuccess);
+    auto at = [](const char* n, hipStream_t s) { return std::string(n) + "@" + std::to_string((unsigned long long)(uintptr_t)s); };
+    for (int batched = 0; batched < 2; ++batched) {
+        mbo_plan_t p = nullptr;
+        if (batched) {
+            mbo_field_desc d[2];
+            std::memset(d, 0, sizeof d);
+            for (int i = 0; i < 2; ++i) {
+                d[i].d = 2;
+                d[i].N[0] = d[i].N[1] = 64;
+                d[i].n = 2;
+                d[i].tau = 1e-3;
+            }
+            CHECK(mbo_plan_batched(&p, 2, d, MBO_F64, 0.0, 0, s1) == MBO_OK);
+        } else {
+            CHECK(mbo_plan(&p, 2, N, 2, 1, 1e-3, MBO_F64, 0.0, s1) == MBO_OK);
+        }
+        if (!p) return;
+        fake::fail_instantiate = true;
+        CHECK(mbo_iterate(p, A.data(), 2, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr) != MBO_OK);
+        fake::fail_instantiate = false;
+        fake::reset();
+        CHECK(mbo_plan_set_stream(p, s2) == MBO_OK);
+        CHECK(mbo_iterate(p, A.data(), 2, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr) == MBO_OK);
+        CHECK(fake::count("set_slot") == 1 && fake::order.front() == at("set_slot", s2));
+        CHECK(mbo_iterate(p, A.data(), 2, 0.0, nullptr, nullptr, nullptr, nullptr, nullptr) == MBO_OK);
+        CHECK(fake::count("set_slot") == 1);
+        CHECK(mbo_plan_destroy(p) == MBO_OK);
+    }
+    CHECK(hipStreamDestroy(s1) == hipSuccess && hipStreamDestroy(s2) == hipSuccess);
+    CHECK(fake::held == 0);
+}
+
 int main(int argc, char** argv)
 {
     const char* s = argc > 1 ? argv[1] : "";
@@ -225,6 +267,7 @@ int main(int argc, char** argv)
     else if (!std::strcmp(s, "adjoint_memory")) adjoint_memory();
     else if (!std::strcmp(s, "surface_memory")) surface_memory();
     else if (!std::strcmp(s, "pinned_buffers")) pinned_buffers();
+    else if (!std::strcmp(s, "field_word")) field_word();
     else return 2;
     if (!bad) std::printf("ok\n");
     return bad;

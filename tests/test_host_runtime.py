@@ -27,7 +27,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["set_tau_2d", "set_tau_3d", "volume_memory", "adjoint_memory",
-                                      "surface_memory", "pinned_buffers"])
+                                      "surface_memory", "pinned_buffers", "field_word"])
 def test_scenario(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr[-3000:]
