@@ -35,6 +35,8 @@
 //              FFT, store in place.
 #pragma once
 
+#include <type_traits>
+
 #include "mbo_kernels.hpp"
 #include "mbo_volume.hpp"
 
@@ -135,6 +137,24 @@ __device__ __forceinline__ void first_stage(T& x, T& y, T ax, T ay, T bx, T by, 
     turn(vx, vy, p);
     x += vx;
     y += vy;
+}
+
+// go(integral_constant<log2L>) for the row lengths of the band-limited passes, 8 to 2048.
+template <typename Go>
+static inline hipError_t with_row_length(int log2L, Go go)
+{
+    switch (log2L) {
+    case 3: return go(std::integral_constant<int, 3>());
+    case 4: return go(std::integral_constant<int, 4>());
+    case 5: return go(std::integral_constant<int, 5>());
+    case 6: return go(std::integral_constant<int, 6>());
+    case 7: return go(std::integral_constant<int, 7>());
+    case 8: return go(std::integral_constant<int, 8>());
+    case 9: return go(std::integral_constant<int, 9>());
+    case 10: return go(std::integral_constant<int, 10>());
+    case 11: return go(std::integral_constant<int, 11>());
+    }
+    return hipErrorInvalidValue;
 }
 
 // Shape of a row-pass workgroup: 512 points (512/L rows) for L <= 512, one row

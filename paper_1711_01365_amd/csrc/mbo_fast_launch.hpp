@@ -36,18 +36,7 @@ template <typename T, int n>
 static hipError_t row_fast_n(int log2L, const FastRowArgs& a, dim3 g, hipStream_t st, bool prepare,
                              hipEvent_t ev0, hipEvent_t ev1)
 {
-    switch (log2L) {
-    case 3: return row_fast_pm<T, n, 3>(a, g, st, prepare, ev0, ev1);
-    case 4: return row_fast_pm<T, n, 4>(a, g, st, prepare, ev0, ev1);
-    case 5: return row_fast_pm<T, n, 5>(a, g, st, prepare, ev0, ev1);
-    case 6: return row_fast_pm<T, n, 6>(a, g, st, prepare, ev0, ev1);
-    case 7: return row_fast_pm<T, n, 7>(a, g, st, prepare, ev0, ev1);
-    case 8: return row_fast_pm<T, n, 8>(a, g, st, prepare, ev0, ev1);
-    case 9: return row_fast_pm<T, n, 9>(a, g, st, prepare, ev0, ev1);
-    case 10: return row_fast_pm<T, n, 10>(a, g, st, prepare, ev0, ev1);
-    case 11: return row_fast_pm<T, n, 11>(a, g, st, prepare, ev0, ev1);
-    }
-    return hipErrorInvalidValue;
+    return with_row_length(log2L, [&](auto lg) { return row_fast_pm<T, n, lg.value>(a, g, st, prepare, ev0, ev1); });
 }
 
 template <typename T>

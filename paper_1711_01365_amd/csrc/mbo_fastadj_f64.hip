@@ -1,4 +1,4 @@
-// The adjoint step's band-limited passes in double (n = 2, 3).
+// The adjoint step's band-limited passes in double (the row pass for n = 2).
 #include "mbo_fastadj_launch.hpp"
 
 namespace mbo {
@@ -6,7 +6,6 @@ namespace mbo {
 hipError_t launch_row_fast_vjp_f64(int n, int log2L, const FastRowArgs& a, dim3 g, hipStream_t st, bool prepare)
 {
     if (n == 2) return row_fast_vjp_n<double, 2>(log2L, a, g, st, prepare);
-    if (n == 3) return row_fast_vjp_n<double, 3>(log2L, a, g, st, prepare);
     return hipErrorInvalidValue;
 }
 

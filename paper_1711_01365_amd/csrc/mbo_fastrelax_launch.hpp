@@ -23,18 +23,7 @@ static hipError_t row_fast_relax_go(const FastRowArgs& a, dim3 g, hipStream_t st
 template <typename T, int n>
 static hipError_t row_fast_relax_n(int log2L, const FastRowArgs& a, dim3 g, hipStream_t st, bool prepare)
 {
-    switch (log2L) {
-    case 3: return row_fast_relax_go<T, n, 3>(a, g, st, prepare);
-    case 4: return row_fast_relax_go<T, n, 4>(a, g, st, prepare);
-    case 5: return row_fast_relax_go<T, n, 5>(a, g, st, prepare);
-    case 6: return row_fast_relax_go<T, n, 6>(a, g, st, prepare);
-    case 7: return row_fast_relax_go<T, n, 7>(a, g, st, prepare);
-    case 8: return row_fast_relax_go<T, n, 8>(a, g, st, prepare);
-    case 9: return row_fast_relax_go<T, n, 9>(a, g, st, prepare);
-    case 10: return row_fast_relax_go<T, n, 10>(a, g, st, prepare);
-    case 11: return row_fast_relax_go<T, n, 11>(a, g, st, prepare);
-    }
-    return hipErrorInvalidValue;
+    return with_row_length(log2L, [&](auto lg) { return row_fast_relax_go<T, n, lg.value>(a, g, st, prepare); });
 }
 
 template <typename T>
