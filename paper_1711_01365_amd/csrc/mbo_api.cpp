@@ -271,26 +271,19 @@ void free_dev(T*& p)
 // gives its buffer back here, after its stream has finished.  At most PINNED_KEPT are
 // kept; larger ones are the plan's alone.
 constexpr size_t PINNED_WORDS = 512, PINNED_KEPT = 16;
-struct PinnedPool {
+struct {
     std::mutex m;
-    std::vector<unsigned long long*> kept;
-};
-
-PinnedPool& pinned_pool()
-{
-    static PinnedPool* pool = new PinnedPool;  // never destroyed: plans may outlive static objects
-    return *pool;
-}
+    unsigned long long* kept[PINNED_KEPT];
+    size_t count;
+} pinned_pool;  // no destructor runs: plans may outlive static objects
 
 hipError_t pinned_alloc(unsigned long long** ptr, size_t* words)
 {
     if (*words <= PINNED_WORDS) {
         *words = PINNED_WORDS;
-        PinnedPool& pool = pinned_pool();
-        std::lock_guard<std::mutex> lock(pool.m);
-        if (!pool.kept.empty()) {
-            *ptr = pool.kept.back();
-            pool.kept.pop_back();
+        std::lock_guard<std::mutex> lock(pinned_pool.m);
+        if (pinned_pool.count) {
+            *ptr = pinned_pool.kept[--pinned_pool.count];
             return hipSuccess;
         }
     }
