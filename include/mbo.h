@@ -37,11 +37,15 @@
  *             with det = +1 is returned; the zero matrix maps to the identity.
  *             n = 1 is sign thresholding with sgn(0) = +1 (Remark 1.2).
  * Ownership   the caller owns every field buffer; the plan owns its workspace,
- *             tables and graphs and frees them in mbo_plan_destroy.  No call
- *             reads a caller pointer after it returns (a captured band-limited
- *             iteration takes the field from a device word that each call sets;
- *             other captured iterations are keyed by the field pointer and
- *             re-captured when it changes).
+ *             tables, graphs and pinned host buffers (five words per field and
+ *             iteration logged) and frees them in mbo_plan_destroy; the process
+ *             keeps up to 16 small pinned buffers (4 KB) of destroyed plans for
+ *             others.  A call that synchronises is done with the caller's buffers
+ *             when it returns; one that is said to be asynchronous uses them until
+ *             the plan's stream has passed it.  No call uses the pointers of an
+ *             earlier one (a captured band-limited iteration takes the field from
+ *             a device word that each call sets; other captured iterations are
+ *             keyed by the field pointer and re-captured when it changes).
  * Streams     all device work is enqueued on the plan's HIP stream.  Calls that
  *             return host values (mbo_energy, the logs of mbo_iterate)
  *             synchronise that stream before returning.  A plan must not be used
@@ -98,10 +102,11 @@ typedef enum {
  * at most eta max|A|, far below the rounding of the transforms.  A plan whose
  * tau and grid leave nothing to drop runs the same kernels with every mode kept.
  * MBO_PATH_FULL runs the same kernels with every mode kept; MBO_PATH_GENERIC the
- * general kernels (any d, any row length).  mbo_diffuse, mbo_step, mbo_energy
- * and, for d = 2, mbo_step_vjp, mbo_diffuse_dtau, mbo_iterate_volume and (n <= 3,
- * every mode kept) mbo_relaxed_flow run the kernels that mbo_iterate runs; the
- * other calls always use the general ones.
+ * general kernels (any d, any row length).  mbo_diffuse, mbo_step, mbo_energy of
+ * MBO_F64 plans and, for d = 2, mbo_step_vjp, mbo_diffuse_dtau, mbo_iterate_volume
+ * (with n_plus: from the second step on) and (n <= 3, every mode kept)
+ * mbo_relaxed_flow run the kernels that mbo_iterate runs; the other calls always use
+ * the general ones.
  * The band-limited kernels serve d = 2 with a first axis of at least 64 points
  * (every last axis a plan accepts) and d = 3 with first axes of 64 or 128 points
  * (float plans) or of at most 128 points and their product of at most 8192 (double);
@@ -126,11 +131,12 @@ mbo_status mbo_plan(mbo_plan_t* out, int d, const int64_t* N, int n, int64_t bat
 mbo_status mbo_plan_destroy(mbo_plan_t plan);
 
 /* Change the diffusion time; the heat-symbol tables are rebuilt (nothing is done
- * when tau is the plan's own already). */
+ * when tau is the plan's own already).  MBO_ERR_ALLOC leaves the plan as it was. */
 mbo_status mbo_plan_set_tau(mbo_plan_t plan, double tau);
 
-/* Choose the kernels of mbo_iterate and the calls that share them (see mbo_path; a batched plan applies the
- * choice to every field class).  Synchronises the plan's stream; a captured
+/* Choose the kernels of mbo_iterate and the calls that share them (see mbo_path; a
+ * batched plan applies the choice to every field class).  On error the plan (a batched
+ * one: the field class it stopped at, and those after it) keeps its path.  Synchronises the plan's stream; a captured
  * iteration graph is rebuilt on the next mbo_iterate.  MBO_ERR_INVALID_ARG for an
  * unknown path. */
 mbo_status mbo_plan_set_path(mbo_plan_t plan, mbo_path path);

@@ -294,10 +294,9 @@ void pinned_free(unsigned long long* ptr, size_t words)
 {
     if (!ptr) return;
     if (words == PINNED_WORDS) {
-        PinnedPool& pool = pinned_pool();
-        std::lock_guard<std::mutex> lock(pool.m);
-        if (pool.kept.size() < PINNED_KEPT) {
-            pool.kept.push_back(ptr);
+        std::lock_guard<std::mutex> lock(pinned_pool.m);
+        if (pinned_pool.count < PINNED_KEPT) {
+            pinned_pool.kept[pinned_pool.count++] = ptr;
             return;
         }
     }
@@ -1713,8 +1712,8 @@ mbo_status plan_init(mbo_plan_t p, const int64_t* foff_host)
 }
 
 // Wait for the iteration logs of plan p (stream st) and store them for field row
-// map[b] (or b) of the caller's arrays; counts the
-// projections that met NaN/Inf into *bad.  Also evaluates kernel timing.
+// map[b] (or b) of the caller's arrays; counts the projections that met NaN/Inf into
+// *bad.  Also evaluates kernel timing.
 mbo_status read_logs(mbo_plan_t p, int K, double tol, hipStream_t st, int* iters_done, double* energy,
                      int64_t* flips, double* delta, int64_t* fallbacks, const std::vector<int>* map,
                      unsigned long long* bad)
@@ -1918,9 +1917,10 @@ mbo_status autotune_plan(mbo_plan_t p)
         if (t < best) best = t;
         else p->xcd_remap = 1;
     }
-    // The general kernels serve the plan's other calls (the volume-preserving
-    // iteration, relaxed flows, the adjoint, energies): their shapes are timed
-    // on the general path, keeping the XCD order the band-limited passes chose.
+    // The general kernels serve float energies, mbo_project_volume, the first step of a
+    // volume-preserving iteration with the caller's volume, relaxed flows with n = 4 and
+    // in 3-D, 3-D adjoints and volume-preserving iterations, and mbo_relaxed_energy: their
+    // shapes are timed on the general path, keeping the XCD order the band-limited passes chose.
     p->fast = false;
     drop_logs(p);
     s = ensure_logs(p, reps);

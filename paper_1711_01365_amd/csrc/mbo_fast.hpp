@@ -19,7 +19,8 @@
 //              1024 and 2048 points, one row: the line groups of its packed
 //              planes load their kept modes straight into the FFT register
 //              layout (lane t holds x[t + e L/8]), inverse-FFT (inside one wave
-//              for L <= 512, in L/512 waves or with workgroup exchanges beyond) and leave the lines in LDS; 512 threads or more, one to
+//              for L <= 512, in L/512 waves or with workgroup exchanges beyond) and
+//              leave the lines in LDS; 512 threads or more, one to
 //              four points each, project (Lemma 1.1) with the det-sign,
 //              fallback, non-finite and change diagnostics; the line groups
 //              forward-FFT and store the kept modes.  Float plans with n = 3
@@ -291,10 +292,10 @@ __device__ __forceinline__ void row_fast_body(const FastRowArgs& a, unsigned gro
     Twiddles<T, LOG2L> tw;
     T r[1][8], im[1][8];
     // Transform j is part q of line j / R; line j is row rl, packed plane
-    // pl of the workgroup (LDS line rl*PL + pl).  Spectra are stored row by row (Z[plane][row][w]) or, for
-    // the 3-D plane pass, plane by plane (Z[plane][w][row]): there the lines
-    // of one plane go to neighbouring groups, so that a wave's stores of one
-    // mode cover consecutive rows.
+    // pl of the workgroup (LDS line rl*PL + pl).  Spectra are stored row by row
+    // (Z[plane][row][w]) or, for the 3-D plane pass, plane by plane
+    // (Z[plane][w][row]): there the lines of one plane go to neighbouring groups, so
+    // that a wave's stores of one mode cover consecutive rows.
     auto line_of = [&](int j, int& rl, int& pl) {
         if (pm) {
             rl = j % RPW;
