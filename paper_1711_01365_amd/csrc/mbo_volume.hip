@@ -420,7 +420,7 @@ __global__ void __launch_bounds__(256) sel_list(const SelListArgs la, int shift)
     }
     if (run) atomicAdd(&h2[bin], run);
     __syncthreads();
-    unsigned* g2 = la.hist2 + (size_t)b * SEL_NB2;
+    unsigned* g2 = la.hist2 + (size_t)b * SEL_HIST2;
     for (int i = tid; i < SEL_NB2; i += 256)
         if (h2[i]) atomicAdd(&g2[i], h2[i]);
 }

@@ -86,3 +86,71 @@ def test_two_steps_are_one_and_one(n, grid, prec):
     good = same & (s[:, -2] - s[:, -1] >= 0.1)
     assert good.sum() >= 0.25 * good.size
     assert np.abs(x - y)[good].max() <= tol
+
+
+def flipped(n, grid, share, seed):
+    """Smooth rotations near the identity, the last column negated at a random share of
+    the points: most of them change side in the first step, in every row."""
+    rng = np.random.default_rng(seed)
+    X, Y = np.meshgrid(np.arange(grid[0]) / grid[0], np.arange(grid[1]) / grid[1], indexing="ij")
+    S = np.zeros(tuple(grid) + (n, n))
+    for i in range(n):
+        for j in range(i):
+            p, q = rng.uniform(size=2)
+            S[..., i, j] = 0.3 * np.sin(2 * np.pi * (X + p)) + 0.3 * np.cos(2 * np.pi * (Y + q))
+            S[..., j, i] = -S[..., i, j]
+    Q = np.linalg.solve(np.eye(n) + S, np.eye(n) - S)
+    Q[..., -1] *= np.where(rng.random(tuple(grid)) < share, -1.0, 1.0)[..., None]
+    return np.ascontiguousarray(np.moveaxis(Q, (2, 3), (0, 1)))
+
+
+# every row length of volume_redo, whole lines and parts, with all and with the kept modes
+@pytest.mark.parametrize("n,L,prec", [(n, L, F64) for n in (1, 2, 3, 4) for L in (8, 16, 32, 64, 128, 256, 512, 1024)] +
+                         [(1, 2048, F64), (2, 2048, F64)] +
+                         [(n, L, FB) for n in (1, 2, 3, 4) for L in (8, 64, 512, 1024, 2048)])
+def test_rows_transformed_again(n, L, prec):
+    import torch
+    from paper_1711_01365_amd import mbo
+    dt = torch.float64 if prec == F64 else torch.float32
+    grid = (64, L)
+    tau = (6.0 / max(grid)) ** 2 / 2
+    A0 = torch.tensor(np.stack([flipped(n, grid, 0.3, 5), flipped(n, grid, 0.6, 6)]), dtype=dt, device="cuda")
+    p = mbo.Plan(grid, n, tau, precision=prec, batch=2)
+    assert p.path()[0] != mbo.PATH_GENERIC
+    X, Y = A0.clone(), A0.clone()
+    two = p.iterate_volume(X, 2, None)
+    one = p.iterate_volume(Y, 1, None)
+    more = p.iterate_volume(Y, 1, None)
+    # more than the 64 per row_fast workgroup that are added by direct sums
+    assert one["flips"].min() > 0.2 * 64 * L
+    tol = 2e-11 if prec == F64 else 2e-5
+    e = np.abs(two["energy"] - np.concatenate([one["energy"][:, :1], more["energy"]], axis=1))
+    assert e.max() <= tol * np.abs(two["energy"]).max()
+    assert np.array_equal(two["n_plus"], more["n_plus"])
+    x, y = X.double().cpu().numpy(), Y.double().cpu().numpy()
+    if prec == F64:
+        assert np.array_equal(two["flips"][:, 1], more["flips"][:, 0])
+        p.set_path(mbo.PATH_GENERIC)
+        Z = A0.clone()
+        ref = p.iterate_volume(Z, 2, None)
+        assert np.array_equal(two["flips"], ref["flips"])
+        z = Z.cpu().numpy()
+    p.close()
+    for b in range(2):
+        u, v = points(x[b]), points(y[b])
+        same = np.sign(np.linalg.det(u)) == np.sign(np.linalg.det(v))
+        assert (~same).sum() <= 0.01 * same.size
+        s = np.linalg.svd(points(diffused(one_step(A0[b], tau, prec, n, grid), tau)), compute_uv=False)
+        good = same & ((s[:, -2] - s[:, -1] >= 0.1) if n > 1 else (s[:, 0] >= 0.1))
+        assert np.abs(u - v)[good].max() <= tol
+        if prec == F64:
+            assert np.abs(u - points(z[b]))[good].max() <= 1e-10
+
+
+def one_step(A, tau, prec, n, grid):
+    from paper_1711_01365_amd import mbo
+    p = mbo.Plan(grid, n, tau, precision=prec)
+    X = A[None].clone()
+    p.iterate_volume(X, 1, None)
+    p.close()
+    return X.double().cpu().numpy()[0]
